@@ -151,6 +151,16 @@ lpf_status lpf_chain_stats(int cx, int cy, int64_t *out);
  * [0, 4096] or nb_want < 1; sets no message. */
 lpf_status lpf_plan_check(int cx, int cy, int64_t nb_want, int64_t *out);
 
+/* Host run of the launch plan of lpf_full (no device, no context): the counts of one phase of a
+ * byte image (row-major W*H, nonzero = phase 1; host) in canonical order (HALF layout), taken by
+ * the plan's own steps on the host with every access checked against its array.  R, S, waves and
+ * lds_bytes fix fields of the shape as in lpf_set_full_shape (0 = automatic).  Returns
+ * LPF_E_INVAL for a bad argument (W or H above 4096 among them), when a vector is not counted
+ * exactly once or when an access leaves its array; LPF_E_UNSUPPORTED when the image's rows do
+ * not fit in LDS (lpf_full then reads rows from device memory); sets no message. */
+lpf_status lpf_cover_counts(const uint8_t *img, int W, int H, int cx, int cy, int phase, int R,
+                            int S, int waves, int lds_bytes, uint32_t *counts);
+
 /* Throughput probe (diagnostic; not part of the method): one launch of nwg workgroups of 256
  * threads whose lanes each run 8 independent dependency chains for `iters` iterations of
  *   kind 0: two funnel shifts (v_alignbit_b32), a 3-input AND (v_bitop3_b32) and a 3-input OR

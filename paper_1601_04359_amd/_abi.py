@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import os
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -57,6 +58,7 @@ _sig("lpf_full_enhanced", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _i32, _P, 
 _sig("lpf_full_noalloc", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _i32, _P, _P)
 _sig("lpf_chain_stats", _i32, _i32, _i32, _P)
 _sig("lpf_plan_check", _i32, _i32, _i32, _i64, _P)
+_sig("lpf_cover_counts", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _P)
 _sig("lpf_peak_probe", _i32, _P, _i32, _i64, _i32, _P, ctypes.POINTER(ctypes.c_double), _P)
 _sig("lpf_set_full_shape", _i32, _P, _i32, _i32, _i32, _i32)
 _sig("lpf_delta_swap", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _P, _i32, _P, _P)
@@ -231,6 +233,20 @@ def lpf_plan_check(cx: int, cy: int, nb_want: int) -> dict:
     if st != LPF_OK:
         raise LpfError(st, f"lpf_plan_check({cx}, {cy}, {nb_want})")
     return {"bins": out[0], "pieces": out[1], "max_members": out[2], "walk": out[3]}
+
+
+def lpf_cover_counts(img: np.ndarray, cx: int, cy: int, phase: int, R: int = 0, S: int = 0,
+                     waves: int = 0, lds_bytes: int = 0) -> np.ndarray:
+    """Host run of lpf_full's launch plan (no device): counts of one phase of a byte image, HALF
+    layout; raises LpfError when a check fails or the rows do not fit in LDS."""
+    img = np.ascontiguousarray(img, np.uint8)
+    H, W = img.shape
+    out = np.zeros(lpf_num_vectors(cx, cy), np.uint32)
+    st = _lib.lpf_cover_counts(img.ctypes.data, W, H, cx, cy, phase, R, S, waves, lds_bytes,
+                               out.ctypes.data)
+    if st != LPF_OK:
+        raise LpfError(st, f"lpf_cover_counts({W}, {H}, {cx}, {cy})")
+    return out
 
 
 def lpf_peak_probe(ctx: int, kind: int, iters: int, nwg: int, sink: torch.Tensor,

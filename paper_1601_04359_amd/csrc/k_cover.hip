@@ -1,0 +1,431 @@
+// Full evaluation of the lineal path function on gfx950: paths covered by words.
+//
+// The paper's Alg. "L2_eval" tests, for every segment and every translation, the segment's
+// pixels one by one.  Here 32 translations (start pixels) share one 32-bit word, a lane owns R
+// consecutive words of one row, and for a path with pixel offsets p_k the lane forms
+//     A = AND_k (image shifted by p_k)    -> bit b set <=> every pixel of the segment is in phase
+// and popcounts A.  One phase is counted per workgroup (the staged image is complemented for
+// phase 0), so every product is an AND.
+//
+// Which pixels are taken together is the plan's work (plan_cover.hip): a workgroup owns a group
+// of neighbouring slopes and, for each row tile, stages the rows in LDS with their periodic halo,
+// builds up to kCoverWords masks beside them (mask bit = the AND over a pixel pattern that the
+// group's paths repeat, from that pixel on), and its waves walk the group's prefix trees.  A
+// record is one or two steps (a funnel shift per word and step, one 3-input AND per word for two
+// steps), after which a count may be taken and the product be saved; a later record can go on
+// from a saved product.  Records are wave-uniform and read on the scalar unit.
+//
+// A count of zero over the wave's rows ends everything that extends that path there (the paper's
+// enhanced evaluation, Sec. 3.2): the walk goes on at the record's jump target.
+#include "cover.h"
+
+namespace lpf {
+
+namespace {
+
+// Bits s .. s + 31 (mod W) of a packed row, 0 <= s < W.  Bits past W in the row's last word are
+// never used.
+__device__ __forceinline__ uint32_t periodic32(const uint32_t *__restrict__ row, int W, int s) {
+  const int q = s >> 5, sh = s & 31;
+  const int n = W - s;  // bits left in the row
+  if (n >= 32) return __builtin_amdgcn_alignbit(sh ? row[q + 1] : 0u, row[q], sh);
+  if (W >= 32) {
+    const uint32_t hi = sh + n > 32 ? row[q + 1] : 0u;
+    return (__builtin_amdgcn_alignbit(hi, row[q], sh) & ((1u << n) - 1u)) | (row[0] << n);
+  }
+  uint32_t v = 0;
+  for (int b = 0, x = s; b < 32; ++b) {
+    v |= ((row[0] >> x) & 1u) << b;
+    x = x + 1 == W ? 0 : x + 1;
+  }
+  return v;
+}
+
+// Word e of a row extended periodically; mirror: of the row reversed (bit j is pixel W - 1 - j).
+__device__ __forceinline__ uint32_t ext_word(const uint32_t *__restrict__ row, int W, int e,
+                                             bool mirror) {
+  int s = 32 * e;
+  if (s >= W) s -= W;
+  if (s >= W) s %= W;  // rows narrower than the window only
+  if (!mirror) return periodic32(row, W, s);
+  // pixels W - 1 - s down to W - 32 - s
+  int t = W - 32 - s;
+  if (t < 0) t += W;
+  if (t < 0) t = (t % W + W) % W;
+  return __builtin_bitreverse32(periodic32(row, W, t));
+}
+
+// Sum over the wave of v, valid in lane 63 (every lane active).
+__device__ __forceinline__ uint32_t wave_sum63(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);   // quad_perm 2,3,0,1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false);  // row_mirror
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
+// The start pixels of a lane's words: full words below the row's last one, which keeps the bits
+// below W mod 32; none for rows past the image; with a position set its members (srow: the row's
+// mask words, k_start_sets).
+template <int R, bool SAMPLE>
+__device__ __forceinline__ void start_pixels(uint32_t (&A)[R], int w0, int W, bool row_ok,
+                                             const uint32_t *__restrict__ srow) {
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int left = W - 32 * (w0 + i);  // pixels of the row from this word on
+    const bool some = row_ok && left > 0;
+    if constexpr (SAMPLE) {
+      A[i] = some ? srow[w0 + i] : 0u;
+    } else {
+      A[i] = some ? (left >= 32 ? 0xffffffffu : (1u << left) - 1u) : 0u;
+    }
+  }
+}
+
+// The records [r, r1) for the lane's R words at `base` (its row's first word in array 0).
+template <int R, bool SAMPLE>
+__device__ __forceinline__ void walk(const int4 *__restrict__ recs, int r, int r1,
+                                     const uint32_t *__restrict__ base, int w0, int W, bool row_ok,
+                                     bool full, const uint32_t *__restrict__ srow,
+                                     uint32_t *__restrict__ slots, int lane) {
+  uint32_t A[R], S1[R], S2[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) A[i] = S1[i] = S2[i] = 0u;
+  int4 rec = recs[r];
+  while (r < r1) {
+    const int4 nxt = recs[r + 1];
+    const uint32_t x = (uint32_t)rec.x;
+    const uint32_t *p0 = base + (x & 0xffffu);
+    uint32_t d0[R + 1];
+#pragma unroll
+    for (int c = 0; c <= R; ++c) d0[c] = p0[c];
+    const int restore = (x >> kRecRestore) & 3;
+    if (restore) {
+      if (restore == 1) {
+        if (full) {
+#pragma unroll
+          for (int i = 0; i < R; ++i) A[i] = 0xffffffffu;
+        } else {
+          start_pixels<R, SAMPLE>(A, w0, W, row_ok, srow);
+        }
+      } else if (restore == 2) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) A[i] = S1[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < R; ++i) A[i] = S2[i];
+      }
+    }
+    const uint32_t sh0 = (x >> 16) & 31u;
+    if (x & kRecTwo) {
+      const uint32_t y = (uint32_t)rec.y;
+      const uint32_t *p1 = base + (y & 0xffffu);
+      const uint32_t sh1 = (y >> 16) & 31u;
+      uint32_t d1[R + 1];
+#pragma unroll
+      for (int c = 0; c <= R; ++c) d1[c] = p1[c];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const uint32_t t0 = __builtin_amdgcn_alignbit(d0[i + 1], d0[i], sh0);
+        const uint32_t t1 = __builtin_amdgcn_alignbit(d1[i + 1], d1[i], sh1);
+        A[i] = __builtin_amdgcn_bitop3_b32(A[i], t0, t1, 0x80);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < R; ++i) A[i] &= __builtin_amdgcn_alignbit(d0[i + 1], d0[i], sh0);
+    }
+    const int save = (x >> kRecSave) & 3;
+    if (save == 1) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) S1[i] = A[i];
+    } else if (save == 2) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) S2[i] = A[i];
+    }
+    ++r;
+    if (x & kRecCount) {
+      uint32_t n = 0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) n += __popc(A[i]);
+      n = wave_sum63(n);
+      const uint32_t all = __builtin_amdgcn_readlane(n, 63);
+      if (all == 0u) {
+        r = rec.w;
+        rec = recs[r];
+        continue;
+      }
+      if (lane == 63) atomicAdd(slots + rec.z, n);
+    }
+    rec = nxt;
+  }
+}
+
+// Count of vector `idx` = (dx, dy) for phase slot p, in the image's output layout (the GRID
+// layout also fills -v, eq. (symmetry)); ADD: a part of it (several workgroups per group), added
+// to entries that are zero before the launch.
+template <bool ADD>
+__device__ __forceinline__ void put_count(const CoverImg &I, uint32_t *__restrict__ out, int p,
+                                          const MemDesc &v, uint32_t c) {
+  auto put = [&](size_t i) {
+    if constexpr (ADD) {
+      if (c) atomicAdd(out + i, c);
+    } else {
+      out[i] = c;
+    }
+  };
+  if (I.layout == 0) {
+    put((size_t)p * I.nv + v.idx);
+  } else {
+    const int gw = 2 * I.cx + 1;
+    const size_t g = (size_t)gw * (2 * I.cy + 1);
+    const size_t i = (size_t)p * g + (size_t)(v.dy + I.cy) * gw + (v.dx + I.cx);
+    const size_t j = (size_t)p * g + (size_t)(I.cy - v.dy) * gw + (I.cx - v.dx);
+    put(i);
+    if (j != i) put(j);
+  }
+}
+
+// One mask of C consecutive dwords per lane and item: item i is chunk i / rows of row i mod rows,
+// so that a wave's lanes read consecutive rows (distinct banks), C + 1 dwords for C funnel
+// shifts.  The last chunk of a row is moved back to end with the row (its overlap is written
+// twice with the same values).
+template <int C>
+__device__ __forceinline__ void build_mask(const CoverGroup &g, const uint32_t *__restrict__ bops,
+                                           int b0, int b1, uint32_t *__restrict__ lds,
+                                           uint32_t *__restrict__ dst) {
+  const int chunks = (g.wid + C - 1) / C;
+  const int items = chunks * g.rows;
+  for (int i = threadIdx.x; i < items; i += blockDim.x) {
+    const int ch = (int)__umulhi((uint32_t)i, g.rows_magic);
+    const int y = i - ch * g.rows;
+    const int d = max(0, y - g.tile + 1);
+    const int at = y * g.rst + max(0, (d * g.sh_a - g.sh_b) >> 16) + min(ch * C, g.wid - C);
+    uint32_t v[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = 0xffffffffu;
+    for (int b = b0; b < b1; ++b) {
+      const uint32_t op = bops[b];
+      const uint32_t *q = lds + at + (op & 0xffffu);
+      const uint32_t sh = (op >> 16) & 31u;
+      uint32_t t[C + 1];
+#pragma unroll
+      for (int c = 0; c <= C; ++c) t[c] = q[c];
+#pragma unroll
+      for (int c = 0; c < C; ++c) v[c] &= __builtin_amdgcn_alignbit(t[c + 1], t[c], sh);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) dst[at + c] = v[c];
+  }
+}
+
+// One group of one phase over the tiles split, split + nsplit, ... of the image (one workgroup).
+// phase 1 counts set pixels, phase 0 clear ones; p: the phase's place in the output.
+template <int R, bool SAMPLE>
+__device__ __forceinline__ void cover_group(const CoverImg &I, int gi, int phase, int p, int split,
+                                            const uint64_t *__restrict__ bits,
+                                            const uint32_t *__restrict__ sample,
+                                            uint32_t *__restrict__ out,
+                                            uint32_t *__restrict__ lds) {
+  const CoverGroup &g = I.groups[gi];
+  const int ntiles = g.ntiles * I.nct;
+  if (split >= ntiles) return;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rpw = 64 / I.S;
+  const int strip = lane / rpw, r_in = lane - strip * rpw;
+  const int SR = I.S * R;
+  uint32_t *slots = lds + (1 + g.nw) * g.asz + kCoverPad;
+  for (int t = tid; t < g.nmem; t += nt) slots[t] = 0u;
+  const int wpr = 2 * ((I.W + 63) >> 6);
+  const int swd = (I.W + 31) >> 5;
+  const uint32_t *rows = reinterpret_cast<const uint32_t *>(bits);
+  const uint32_t flip = phase ? 0u : 0xffffffffu;
+  const bool mirror = g.mirror != 0;
+  const int piece = wave / I.nwb, bw = wave - piece * I.nwb;
+  const int r0 = I.piece_off[g.piece0 + piece], r1 = I.piece_off[g.piece0 + piece + 1];
+  const int cells = g.rows * g.wid;
+  for (int tile = split; tile < ntiles; tile += I.nsplit) {
+    const int ct = tile / g.ntiles;
+    const int e0 = ct * SR;
+    const int Y0 = (tile - ct * g.ntiles) * g.tile;
+    __syncthreads();  // every wave is done with the previous tile
+    for (int i = tid; i < cells; i += nt) {
+      const int y = (int)__umulhi((uint32_t)i, g.wid_magic);
+      const int d = max(0, y - g.tile + 1);
+      const int e = max(0, (d * g.sh_a - g.sh_b) >> 16) + i - y * g.wid;
+      int r = Y0 + y;
+      if (r >= I.H) r -= I.H;
+      if (r >= I.H) r %= I.H;
+      lds[y * g.rst + e] = flip ^ ext_word(rows + (size_t)r * wpr, I.W, e0 + e, mirror);
+    }
+    for (int a = 1; a <= g.nw; ++a) {
+      __syncthreads();
+      build_mask<(R >= 7 ? 8 : R + 1)>(g, I.bops, g.bop[a - 1], g.bop[a], lds, lds + a * g.asz);
+    }
+    __syncthreads();
+    const int rows_here = min(g.tile, I.H - Y0);
+    if (r0 < r1) {
+      for (int row0 = bw * rpw; row0 < rows_here; row0 += I.nwb * rpw) {
+        const int row = row0 + r_in;
+        const int w0 = e0 + strip * R;
+        const bool row_ok = row < rows_here;
+        const bool full = !SAMPLE && __all(row_ok && 32 * (w0 + R) <= I.W);
+        const uint32_t *srow =
+            SAMPLE ? sample + (size_t)((mirror ? I.H : 0) + Y0 + (row_ok ? row : 0)) * swd : nullptr;
+        walk<R, SAMPLE>(I.recs, r0, r1, lds + row * g.rst + strip * R, w0, I.W, row_ok, full, srow,
+                        slots, lane);
+      }
+    }
+  }
+  __syncthreads();
+  if (I.nsplit == 1) {
+    for (int t = tid; t < g.nmem; t += nt) put_count<false>(I, out, p, I.mems[g.mem0 + t], slots[t]);
+  } else {
+    for (int t = tid; t < g.nmem; t += nt) put_count<true>(I, out, p, I.mems[g.mem0 + t], slots[t]);
+  }
+}
+
+__global__ void k_cover_zero(uint32_t *__restrict__ out, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = 0u;
+}
+
+// The counts that several workgroups add to, zeroed in one launch for a whole batch: image
+// blockIdx.y's, when its groups are split.
+__global__ void k_cover_zero_batch(const CoverImg *__restrict__ imgs,
+                                   const int64_t *__restrict__ counts_off, int nph,
+                                   uint32_t *__restrict__ counts) {
+  const CoverImg &I = imgs[blockIdx.y];
+  if (I.nsplit <= 1) return;
+  const int64_t n = (int64_t)nph * (I.layout == 0 ? (int64_t)I.nv
+                                                  : (int64_t)(2 * I.cx + 1) * (2 * I.cy + 1));
+  uint32_t *out = counts + counts_off[blockIdx.y];
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = 0u;
+}
+
+// Start pixels of a Monte-Carlo position set as mask words: [0] rows as they are, [1] rows
+// reversed (for the mirrored groups); bits past W clear.
+__global__ void k_start_sets(const uint32_t *__restrict__ src, int W, int H, int swd, int wpr,
+                             uint32_t *__restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 2 * H * swd) return;
+  const int r = i / swd, e = i - r * swd;
+  const bool mirror = r >= H;
+  const uint32_t *row = src + (size_t)(mirror ? r - H : r) * wpr;
+  const int left = W - 32 * e;
+  out[i] = ext_word(row, W, e, mirror) & (left >= 32 ? 0xffffffffu : (1u << left) - 1u);
+}
+
+// Workgroup b: phase b mod nph, then split, of the group at place b / (nph nsplit) of the order.
+template <int R, bool SAMPLE>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+k_cover(CoverImg I, const int32_t *__restrict__ order, unsigned phase_mask,
+        const uint64_t *__restrict__ bits, const uint32_t *__restrict__ sample,
+        uint32_t *__restrict__ out) {
+  extern __shared__ uint32_t lds[];
+  const int both = phase_mask == 3u ? 1 : 0;
+  const int p = blockIdx.x & both, b = blockIdx.x >> both;
+  const int gi = b / I.nsplit;
+  cover_group<R, SAMPLE>(I, order[gi], both ? p : (int)(phase_mask >> 1), p, b - gi * I.nsplit,
+                         bits, sample, out, lds);
+}
+
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+k_cover_batch(const CoverImg *__restrict__ imgs, const int64_t *__restrict__ bits_off,
+              const int64_t *__restrict__ counts_off, const int4 *__restrict__ items,
+              unsigned phase_mask, const uint64_t *__restrict__ pool,
+              uint32_t *__restrict__ counts) {
+  extern __shared__ uint32_t lds[];
+  const int4 it = items[blockIdx.x];
+  const CoverImg &I = imgs[it.x];
+  const uint64_t *bits = pool + bits_off[it.x];
+  uint32_t *out = counts + counts_off[it.x];
+  const int phase = it.z, p = phase_mask == 3u ? phase : 0;
+  switch (I.R) {
+#define LPF_R(r) \
+  case r: cover_group<r, false>(I, it.y, phase, p, it.w, bits, nullptr, out, lds); break;
+    LPF_R(1) LPF_R(2) LPF_R(3) LPF_R(4) LPF_R(5) LPF_R(6) LPF_R(7) LPF_R(8)
+    LPF_R(9) LPF_R(10) LPF_R(11) LPF_R(12) LPF_R(13) LPF_R(14) LPF_R(15) LPF_R(16)
+#undef LPF_R
+  }
+}
+
+using CoverKernel = void (*)(CoverImg, const int32_t *, unsigned, const uint64_t *,
+                             const uint32_t *, uint32_t *);
+CoverKernel cover_kernel(int R, bool sample) {
+  switch (R) {
+#define LPF_R(r) \
+  case r: return sample ? k_cover<r, true> : k_cover<r, false>;
+    LPF_R(1) LPF_R(2) LPF_R(3) LPF_R(4) LPF_R(5) LPF_R(6) LPF_R(7) LPF_R(8)
+    LPF_R(9) LPF_R(10) LPF_R(11) LPF_R(12) LPF_R(13) LPF_R(14) LPF_R(15) LPF_R(16)
+#undef LPF_R
+  }
+  return nullptr;
+}
+
+}  // namespace
+
+hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, int ngroups, const int32_t *order,
+                        size_t lds_bytes, unsigned phase_mask, const uint64_t *bits,
+                        const uint32_t *sample, uint32_t *out, hipStream_t stream) {
+  const CoverKernel k = cover_kernel(I.R, sample != nullptr);
+  if (!k || I.R != sh.R || I.S != sh.S || sh.wpg < 1 || sh.wpg > 16 || I.nwb < 1 ||
+      sh.wpg % I.nwb || 64 % I.S)
+    return hipErrorInvalidValue;
+  const int nph = phase_mask == 3u ? 2 : 1;
+  if (I.nsplit > 1) {
+    const int64_t n = (int64_t)nph * (I.layout == 0 ? (int64_t)I.nv
+                                                    : (int64_t)(2 * I.cx + 1) * (2 * I.cy + 1));
+    hipLaunchKernelGGL(k_cover_zero, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)),
+                       dim3(256), 0, stream, out, n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3(ngroups * nph * I.nsplit), dim3(64 * sh.wpg), lds_bytes, stream, I, order,
+                     phase_mask, bits, sample, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_start_sets(const uint64_t *sample, int W, int H, uint32_t *out,
+                             hipStream_t stream) {
+  const int swd = (W + 31) / 32, n = 2 * H * swd;
+  hipLaunchKernelGGL(k_start_sets, dim3((n + 255) / 256), dim3(256), 0, stream,
+                     reinterpret_cast<const uint32_t *>(sample), W, H, swd, 2 * ((W + 63) / 64), out);
+  return hipGetLastError();
+}
+
+hipError_t launch_cover_zero(const CoverImg *imgs, const int64_t *counts_off, int n_images,
+                             unsigned phase_mask, uint32_t *counts, hipStream_t stream) {
+  hipLaunchKernelGGL(k_cover_zero_batch, dim3(64, n_images), dim3(256), 0, stream, imgs,
+                     counts_off, phase_mask == 3u ? 2 : 1, counts);
+  return hipGetLastError();
+}
+
+hipError_t launch_cover_batch(const CoverImg *imgs, const int64_t *bits_off,
+                              const int64_t *counts_off, const int4 *items, int n_items, int wpg,
+                              size_t lds_bytes, unsigned phase_mask, const uint64_t *pool,
+                              uint32_t *counts, hipStream_t stream) {
+  hipLaunchKernelGGL(k_cover_batch, dim3(n_items), dim3(64 * wpg), lds_bytes, stream, imgs,
+                     bits_off, counts_off, items, phase_mask, pool, counts);
+  return hipGetLastError();
+}
+
+hipError_t prepare_cover_kernels(int max_lds_bytes) {
+  hipError_t e = hipFuncSetAttribute((const void *)k_cover_batch,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
+  for (int R = 1; R <= 16; ++R)
+    for (int s = 0; s < 2; ++s) {
+      hipError_t r = hipFuncSetAttribute((const void *)cover_kernel(R, s),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
+      if (r != hipSuccess) e = r;
+    }
+  return e;
+}
+
+}  // namespace lpf

@@ -74,7 +74,11 @@ hipError_t launch_ext(const uint64_t *bits, int W, int H, int we, uint32_t *ext,
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------ full kernel
+// ------------------------------------------------------------------------------ chain walk
+//
+// The full evaluation by one walk per chain, pixel by pixel: for images whose rows do not fit in
+// LDS (rows read from device memory) and, without tables, for lpf_full_noalloc.  Everything else
+// is counted by the cover kernel (k_cover.hip).
 //
 // Chains.  Every segment path is taken from (0,0) in the order of its major axis, and the first
 // l + 1 pixels of the path of a vector v are, up to a translation, often the whole path of a
@@ -292,13 +296,15 @@ __device__ __forceinline__ void walk_chain(const uint32_t *__restrict__ base, in
 // tile; each count is then written once.
 // CANON: no chain tables; bin b takes the canonical vectors b, b + nbins, b + 2 nbins, ... as
 // chains of one member each (interleaving spreads long and short vectors evenly).
-// GLOB: rows are read from the extended image in device memory (one tile, I.lds_rows rows of
-// E with a periodic halo), for halos too large for LDS; only the count slots live in LDS.
+// CANON stages the rows of each tile in LDS; otherwise rows are read from the extended image in
+// device memory (one tile, I.lds_rows rows of E with a periodic halo) and only the count slots
+// live in LDS.
 // SAMPLE: I.sample holds a Monte-Carlo position set (the approximation's instance).
-template <int R, bool SKIP, bool CANON = false, bool GLOB = false, bool SAMPLE = false>
+template <int R, bool SKIP, bool CANON, bool SAMPLE>
 __device__ __forceinline__ void process_item(const FullImg &I, int bin, int wpg,
                                              unsigned phase_mask, uint32_t *__restrict__ lds,
                                              uint32_t *__restrict__ slots) {
+  constexpr bool GLOB = !CANON;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rpw = 64 / I.S;
@@ -419,13 +425,13 @@ __device__ __forceinline__ void process_item(const FullImg &I, int bin, int wpg,
   }
 }
 
-// One image, one workgroup per bin.  At most 128 registers per lane (four waves per SIMD): at
-// the usual staging sizes LDS already limits a CU to two workgroups of eight waves.
-template <int R, bool SKIP, bool GLOB = false, bool SAMPLE = false>
+// One image whose rows do not fit in LDS, one workgroup per bin of chains.  At most 128 registers
+// per lane (four waves per SIMD).
+template <int R, bool SKIP, bool SAMPLE>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
-k_lpf_full(FullImg I, int wpg, unsigned phase_mask, int cnt_off) {
+k_lpf_full(FullImg I, int wpg, unsigned phase_mask) {
   extern __shared__ uint32_t lds[];
-  process_item<R, SKIP, false, GLOB, SAMPLE>(I, blockIdx.x, wpg, phase_mask, lds, lds + cnt_off);
+  process_item<R, SKIP, false, SAMPLE>(I, blockIdx.x, wpg, phase_mask, lds, lds);
 }
 
 // One image without chain tables (canonical vectors interleaved over the bins).
@@ -433,52 +439,7 @@ template <int R>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
 k_lpf_full_canon(FullImg I, int wpg, unsigned phase_mask, int cnt_off) {
   extern __shared__ uint32_t lds[];
-  process_item<R, false, true>(I, blockIdx.x, wpg, phase_mask, lds, lds + cnt_off);
-}
-
-// Many images, persistent workgroups drawing work items (image, bin) from a device counter in
-// descending cost order until the list is exhausted (every wave reaches the exit test).  The
-// counts pool is read from `args` (written before each replay of the captured launch); image i's
-// counts start at counts_off[i].
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
-k_lpf_batch(const FullImg *__restrict__ imgs, const BatchArgs *__restrict__ args,
-            const int64_t *__restrict__ counts_off, const int2 *__restrict__ items, int n_items,
-            int *__restrict__ counter, int wpg, unsigned phase_mask, int cnt_off) {
-  extern __shared__ uint32_t lds[];
-  __shared__ int s_item;
-  uint32_t *const counts = args->counts;
-  for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
-    __syncthreads();
-    const int it = s_item;
-    __syncthreads();
-    if (it >= n_items) break;
-    const int2 w = items[it];
-    FullImg I = imgs[w.x];
-    I.out = counts + counts_off[w.x];
-    if (!I.glob) {
-      switch (I.R) {
-        case 1: process_item<1, false>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 2: process_item<2, false>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 4: process_item<4, false>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 8: process_item<8, false>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        default: process_item<16, false>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-      }
-    } else {
-      switch (I.R) {
-        case 1: process_item<1, false, false, true>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 2: process_item<2, false, false, true>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 4: process_item<4, false, false, true>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        case 8: process_item<8, false, false, true>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-        default: process_item<16, false, false, true>(I, w.y, wpg, phase_mask, lds, lds + cnt_off); break;
-      }
-    }
-    __syncthreads();  // the item's counts are written and its rows no longer read
-  }
-}
-
-__global__ void k_reset_counter(int *counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) counter[0] = 0;
+  process_item<R, false, true, false>(I, blockIdx.x, wpg, phase_mask, lds, lds + cnt_off);
 }
 
 size_t full_lds_bytes(const FullShape &sh, int wpg) {
@@ -496,26 +457,16 @@ static bool shape_ok(const FullImg &I, const FullShape &sh) {
 template <int R, bool SKIP>
 static hipError_t launch_full_r(const FullImg &I, const FullShape &sh, unsigned phase_mask,
                                 hipStream_t stream) {
-  if (!shape_ok(I, sh) || I.glob != sh.glob) return hipErrorInvalidValue;
+  if (!shape_ok(I, sh) || !I.glob || !sh.glob) return hipErrorInvalidValue;
   const size_t lds = full_lds_bytes(sh, sh.wpg);
-  const int cnt_off = sh.glob ? 0 : sh.lds_rows * sh.rst;
   const dim3 g(sh.nbins), b(64 * sh.wpg);
   if constexpr (SKIP) {  // the enhanced evaluation has no Monte-Carlo variant
     if (I.sample) return hipErrorInvalidValue;
-    if (sh.glob)
-      hipLaunchKernelGGL((k_lpf_full<R, true, true>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
-    else
-      hipLaunchKernelGGL((k_lpf_full<R, true>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
+    hipLaunchKernelGGL((k_lpf_full<R, true, false>), g, b, lds, stream, I, sh.wpg, phase_mask);
   } else if (I.sample) {
-    if (sh.glob)
-      hipLaunchKernelGGL((k_lpf_full<R, false, true, true>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
-    else
-      hipLaunchKernelGGL((k_lpf_full<R, false, false, true>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
+    hipLaunchKernelGGL((k_lpf_full<R, false, true>), g, b, lds, stream, I, sh.wpg, phase_mask);
   } else {
-    if (sh.glob)
-      hipLaunchKernelGGL((k_lpf_full<R, false, true>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
-    else
-      hipLaunchKernelGGL((k_lpf_full<R, false>), g, b, lds, stream, I, sh.wpg, phase_mask, cnt_off);
+    hipLaunchKernelGGL((k_lpf_full<R, false, false>), g, b, lds, stream, I, sh.wpg, phase_mask);
   }
   return hipGetLastError();
 }
@@ -566,11 +517,11 @@ hipError_t launch_full(const FullImg &I, const FullShape &sh, unsigned phase_mas
 int full_wgs_per_cu(int R, bool skip, int wpg, size_t lds_bytes) {
   const void *f = nullptr;
   switch (R) {
-    case 1: f = skip ? (const void *)k_lpf_full<1, true> : (const void *)k_lpf_full<1, false>; break;
-    case 2: f = skip ? (const void *)k_lpf_full<2, true> : (const void *)k_lpf_full<2, false>; break;
-    case 4: f = skip ? (const void *)k_lpf_full<4, true> : (const void *)k_lpf_full<4, false>; break;
-    case 8: f = skip ? (const void *)k_lpf_full<8, true> : (const void *)k_lpf_full<8, false>; break;
-    default: f = skip ? (const void *)k_lpf_full<16, true> : (const void *)k_lpf_full<16, false>; break;
+    case 1: f = skip ? (const void *)k_lpf_full<1, true, false> : (const void *)k_lpf_full<1, false, false>; break;
+    case 2: f = skip ? (const void *)k_lpf_full<2, true, false> : (const void *)k_lpf_full<2, false, false>; break;
+    case 4: f = skip ? (const void *)k_lpf_full<4, true, false> : (const void *)k_lpf_full<4, false, false>; break;
+    case 8: f = skip ? (const void *)k_lpf_full<8, true, false> : (const void *)k_lpf_full<8, false, false>; break;
+    default: f = skip ? (const void *)k_lpf_full<16, true, false> : (const void *)k_lpf_full<16, false, false>; break;
   }
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * wpg, lds_bytes) != hipSuccess)
@@ -578,99 +529,15 @@ int full_wgs_per_cu(int R, bool skip, int wpg, size_t lds_bytes) {
   return n > 0 ? n : 1;
 }
 
-hipError_t launch_batch(const FullImg *imgs, const BatchArgs *args, const int64_t *counts_off,
-                        const int2 *items, int n_items, int *counter, int wpg,
-                        unsigned phase_mask, size_t lds_bytes, int cnt_off, int n_wg,
-                        hipStream_t stream) {
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, stream, counter);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_lpf_batch, dim3(n_wg), dim3(64 * wpg), lds_bytes, stream, imgs, args,
-                     counts_off, items, n_items, counter, wpg, phase_mask, cnt_off);
-  return hipGetLastError();
-}
-
-// The buffers of one lpf_batch call, written on the call's stream before the captured launch.
-__global__ void k_batch_args(BatchArgs *args, const uint64_t *pool, uint32_t *counts) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    args->pool = pool;
-    args->counts = counts;
-  }
-}
-
-hipError_t launch_batch_args(BatchArgs *args, const uint64_t *pool, uint32_t *counts,
-                             hipStream_t stream) {
-  hipLaunchKernelGGL(k_batch_args, dim3(1), dim3(64), 0, stream, args, pool, counts);
-  return hipGetLastError();
-}
-
-// E for many images in one launch: image b's rows at ext_off[b], we[b] dwords per row; the
-// packed images at args->pool + bits_off[b].
-__global__ void k_ext_batch(const FullImg *__restrict__ imgs, const BatchArgs *__restrict__ args,
-                            const int64_t *__restrict__ bits_off, uint32_t *__restrict__ ext,
-                            const int64_t *__restrict__ ext_off) {
-  const int b = blockIdx.z;
-  const FullImg I = imgs[b];
-  const uint64_t *const pool = args->pool;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  if (e >= I.we || y >= (I.glob ? I.lds_rows : I.H)) return;
-  const uint32_t *row = reinterpret_cast<const uint32_t *>(pool + bits_off[b]) +
-                        (size_t)(y % I.H) * 2 * ((I.W + 63) / 64);
-  const int W = I.W;
-  const int s = (int)(((int64_t)32 * e) % W);
-  uint32_t v;
-  if (s + 32 <= W) {
-    const int q = s >> 5, sh = s & 31;
-    v = __builtin_amdgcn_alignbit(sh ? row[q + 1] : 0u, row[q], sh);
-  } else {
-    v = 0;
-    int x = s;
-    for (int t = 0; t < 32; ++t) {
-      v |= ((row[x >> 5] >> (x & 31)) & 1u) << t;
-      x = (x + 1 == W) ? 0 : x + 1;
-    }
-  }
-  ext[ext_off[b] + (size_t)y * I.we + e] = v;
-}
-
-hipError_t launch_ext_batch(const FullImg *imgs, int n_images, int max_we, int max_h,
-                            const BatchArgs *args, const int64_t *bits_off, uint32_t *ext,
-                            const int64_t *ext_off, hipStream_t stream) {
-  dim3 grid((max_we + 63) / 64, max_h, n_images);
-  hipLaunchKernelGGL(k_ext_batch, grid, dim3(64), 0, stream, imgs, args, bits_off, ext, ext_off);
-  return hipGetLastError();
-}
-
 hipError_t prepare_full_kernels(int max_lds_bytes) {
   hipError_t e = hipSuccess;
-  const void *fns[] = {(const void *)k_lpf_full<1, false>, (const void *)k_lpf_full<2, false>,
-                       (const void *)k_lpf_full<4, false>, (const void *)k_lpf_full<8, false>,
-                       (const void *)k_lpf_full<16, false>, (const void *)k_lpf_full<1, true>,
-                       (const void *)k_lpf_full<2, true>, (const void *)k_lpf_full<4, true>,
-                       (const void *)k_lpf_full<8, true>, (const void *)k_lpf_full<16, true>,
-                       (const void *)k_lpf_full<1, false, true>, (const void *)k_lpf_full<2, false, true>,
-                       (const void *)k_lpf_full<4, false, true>, (const void *)k_lpf_full<8, false, true>,
-                       (const void *)k_lpf_full<16, false, true>, (const void *)k_lpf_full<1, true, true>,
-                       (const void *)k_lpf_full<2, true, true>, (const void *)k_lpf_full<4, true, true>,
-                       (const void *)k_lpf_full<8, true, true>, (const void *)k_lpf_full<16, true, true>,
-                       (const void *)k_lpf_full<1, false, false, true>, (const void *)k_lpf_full<2, false, false, true>,
-                       (const void *)k_lpf_full<4, false, false, true>, (const void *)k_lpf_full<8, false, false, true>,
-                       (const void *)k_lpf_full<16, false, false, true>, (const void *)k_lpf_full<1, false, true, true>,
-                       (const void *)k_lpf_full<2, false, true, true>, (const void *)k_lpf_full<4, false, true, true>,
-                       (const void *)k_lpf_full<8, false, true, true>, (const void *)k_lpf_full<16, false, true, true>,
-                       (const void *)k_lpf_full_canon<1>, (const void *)k_lpf_full_canon<2>,
+  const void *fns[] = {(const void *)k_lpf_full_canon<1>, (const void *)k_lpf_full_canon<2>,
                        (const void *)k_lpf_full_canon<4>, (const void *)k_lpf_full_canon<8>,
                        (const void *)k_lpf_full_canon<16>};
   for (const void *f : fns) {
     hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
     if (r != hipSuccess) e = r;
   }
-  // the batch kernel also holds one static LDS word
-  hipError_t r = hipFuncSetAttribute((const void *)k_lpf_batch,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     max_lds_bytes - kBatchStaticLds);
-  if (r != hipSuccess) e = r;
   return e;
 }
 

@@ -1,6 +1,7 @@
 // liblpf C ABI: argument checks, per-context caches and scratch, launch plans.
 // Declarations and the contract of every entry point are in include/lpf.h.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -13,6 +14,7 @@
 #include <vector>
 
 #include "../../include/lpf.h"
+#include "cover.h"
 #include "lpf_internal.h"
 
 using namespace lpf;
@@ -93,8 +95,21 @@ struct FullPlan {
   std::vector<int64_t> bin_cost;  // host: cost of each bin (pixels + overhead per member)
 };
 
+// Cover plan of an image size and cutoff (plan_cover.hip) on the device.  ok = false: its rows do
+// not fit in LDS (the chain walk on rows in device memory is used instead).
+struct CoverPlan {
+  bool ok = false;
+  CoverImg img{};
+  CoverShape sh{};
+  int ngroups = 0;
+  size_t lds_bytes = 0;
+  int32_t *order = nullptr;   // device: groups, most work first
+  std::vector<int64_t> cost;  // host, per group
+  void *mem = nullptr;        // one device allocation behind every table
+};
+
 struct TunedShape {
-  int R = 0, wpg = 0, lds = 0;
+  int R = 0, S = 0, wpg = 0, lds = 0;
   double ms = 0.0;
 };
 
@@ -169,9 +184,8 @@ int bank_score(int rst, int R, int S) {
 }
 
 constexpr int kMaxLds = 160 * 1024;
-// staging budget used when an image needs more than the default: leaves room for the batch
-// kernel's own LDS word
-constexpr int kBigLds = kMaxLds - kBatchStaticLds;
+// staging budget of the chain walk when an image needs more than the default
+constexpr int kBigLds = kMaxLds - 256;
 
 }  // namespace
 
@@ -184,6 +198,8 @@ struct lpf_ctx_s {
   int dev = 0;
   uint32_t *noalloc_scratch = nullptr;  // this device's address of `scratch`
   std::map<std::tuple<int, int, int, int, int, int, int>, FullPlan> full_plans;
+  // cover plans per image size, cutoff and fixed shape fields (R, S, waves, LDS; 0 = free)
+  std::map<std::array<int, 8>, CoverPlan> cover_plans;
   std::map<std::pair<int, int>, ChainSet> chain_sets;  // chains per cutoff (host)
   std::map<std::tuple<int, int, int, int, int>, DeltaPlan> delta_plans;
   std::map<std::tuple<int, int, int>, DiagPlan> diag_plans;  // (cx, cy, chunks)
@@ -198,13 +214,14 @@ struct lpf_ctx_s {
     std::map<std::pair<int, int>, int2 *> walk;
   };
   std::map<std::tuple<int, int, int>, Vec3> vec3;
-  std::map<std::string, struct BatchGraph *> batch_graphs;
-  uint64_t batch_clock = 0;  // use counter of the cached batch graphs
+  std::map<std::string, struct BatchPlan *> batch_plans;
+  uint64_t batch_clock = 0;  // use counter of the cached batch plans
   DevBuf ext, ext3, s2ext, s2acc, sext, rank_buf;
   int s2half = 0;  // lpf_s2: which half of s2acc the next call accumulates into
   std::mutex mu;
   // shape override (autotuner): R, S, wpg, lds budget; 0 = automatic
   int force_R = 0, force_S = 0, force_wpg = 0, force_lds = 0;
+  int tune_count = 0;  // autotuner runs so far: a batch plan made before one does not hold after it
   bool force_run_delta = false;  // lpf_delta_swap through the run-based kernel (comparisons)
 };
 
@@ -255,23 +272,26 @@ struct lpf_anneal_s {
 // device memory the records method may take by itself (records + ones)
 constexpr int64_t kRecBudget = (int64_t)16 << 30;
 
-// A captured lpf_batch launch (extended images, counter reset, persistent kernel).
-// Keyed by the descriptors, phase mask, layout and shape overrides, not by the caller's
-// buffers: those go through `args`, written before each replay.  At most kMaxBatchGraphs are
-// kept; the least recently used is released first.
-struct BatchGraph {
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  FullImg *imgs = nullptr;
-  BatchArgs *args = nullptr;
-  int2 *items = nullptr;
-  int64_t *bits_off = nullptr, *ext_off = nullptr, *counts_off = nullptr;
-  int *counter = nullptr;
-  uint32_t *ext = nullptr;
-  int n_items = 0, n_wg = 0;
+// The launches of one lpf_batch call: its images' plans and the work items, most work first.
+// Keyed by the descriptors, phase mask, layout and shape overrides, not by the caller's buffers.
+// At most kMaxBatchPlans are kept; the least recently used is released first.
+struct BatchPlan {
+  // one launch per workgroup size: 16 waves for images whose rows need more than half of a CU's
+  // LDS, 8 for the others
+  struct Launch {
+    int4 *items = nullptr;
+    int n_items = 0, wpg = 0;
+    size_t lds_bytes = 0;
+  };
+  std::vector<Launch> launches;
+  CoverImg *imgs = nullptr;
+  int64_t *bits_off = nullptr, *counts_off = nullptr;
+  int n_images = 0;
+  bool split = false;     // some image's groups are split: its counts are zeroed first
+  std::vector<int> glob;  // images whose rows do not fit in LDS
   uint64_t last_use = 0;
 };
-constexpr size_t kMaxBatchGraphs = 16;
+constexpr size_t kMaxBatchPlans = 16;
 
 struct lpf_cnn_s {
   lpf_ctx ctx = nullptr;
@@ -282,24 +302,50 @@ struct lpf_cnn_s {
 
 namespace {
 
-void free_batch_graph(BatchGraph *b) {
+void free_batch_plan(BatchPlan *b) {
   if (!b) return;
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
+  for (auto &l : b->launches) (void)hipFree(l.items);
   (void)hipFree(b->imgs);
-  (void)hipFree(b->args);
-  (void)hipFree(b->items);
   (void)hipFree(b->bits_off);
-  (void)hipFree(b->ext_off);
   (void)hipFree(b->counts_off);
-  (void)hipFree(b->counter);
-  (void)hipFree(b->ext);
   delete b;
 }
 
-void release_batch_graphs(lpf_ctx c);
+// The shape fields fixed by lpf_set_full_shape or the autotuner; false (with the reason) when
+// they cannot cover the image.
+struct FixedShape {
+  int R = 0, S = 0, wpg = 0, lds = 0;
+};
+bool fixed_shape(lpf_ctx c, int W, int H, int cx, int cy, FixedShape &f, std::string &why) {
+  f = FixedShape{c->force_R, c->force_S, c->force_wpg, c->force_lds};
+  auto tk = c->tuned.find(std::make_tuple(W, H, cx, cy));
+  if (tk != c->tuned.end()) {
+    // the tuned lanes go together: a forced R or S replaces both
+    if (!f.R && !f.S) {
+      f.R = tk->second.R;
+      f.S = tk->second.S;
+    }
+    if (!f.wpg) f.wpg = tk->second.wpg;
+    if (!f.lds) f.lds = tk->second.lds;
+  }
+  const int swd = (W + 31) / 32;
+  const int R = f.R ? f.R : std::min(16, next_pow2(swd));
+  const int S = c->force_S ? c->force_S : next_pow2((swd + R - 1) / R);
+  if (S > 64) {
+    why = "image too wide for the lane layout (W > 64*R*32)";
+    return false;
+  }
+  if (c->force_S && (long)R * S < swd) {
+    why = "forced tile shape does not cover the row";
+    return false;
+  }
+  return true;
+}
 
-bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, FullShape &sh, std::string &why) {
+// Tile shape of the chain walk: rows staged in LDS, or (rows_in_memory) read from the extended
+// image in device memory.
+bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, bool rows_in_memory, FullShape &sh,
+                  std::string &why) {
   const int swd = (W + 31) / 32;
   const TunedShape *tuned = nullptr;
   auto tk = c->tuned.find(std::make_tuple(W, H, cx, cy));
@@ -335,7 +381,13 @@ bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, FullShape &sh, std::s
   sh.rst = best;
   int budget = fL ? fL : 64 * 1024;
   sh.glob = 0;
-  for (;;) {
+  if (rows_in_memory) {
+    sh.glob = 1;
+    sh.tile = H;
+    sh.rst = sh.we;
+    if (!fW) sh.wpg = 16;
+  }
+  while (!sh.glob) {
     int tile;
     const int slots = kSlotWords * 4;  // count slots of the bin's members
     const int rows_max = (budget - slots) / (sh.rst * 4);
@@ -370,10 +422,12 @@ bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, FullShape &sh, std::s
   return true;
 }
 
+// Plan of the chain walk on rows in device memory.
 lpf_status get_full_plan(lpf_ctx c, int W, int H, int cx, int cy, FullPlan *&plan) {
   FullShape sh{};
   std::string why;
-  if (!choose_shape(c, W, H, cx, cy, sh, why)) return fail(LPF_E_UNSUPPORTED, "lpf_full: " + why);
+  if (!choose_shape(c, W, H, cx, cy, true, sh, why))
+    return fail(LPF_E_UNSUPPORTED, "lpf_full: " + why);
   if (full_lds_bytes(sh, sh.wpg) > (size_t)kMaxLds)
     return fail(LPF_E_UNSUPPORTED, "lpf_full: tile shape needs more than 160 KiB of LDS");
   auto key = std::make_tuple(W, H, cx, cy, sh.R * 1000 + sh.S, sh.wpg, 2 * sh.tile + sh.glob);
@@ -434,9 +488,70 @@ lpf_status get_full_plan(lpf_ctx c, int W, int H, int cx, int cy, FullPlan *&pla
   return LPF_OK;
 }
 
-void release_batch_graphs(lpf_ctx c) {
-  for (auto &kv : c->batch_graphs) free_batch_graph(kv.second);
-  c->batch_graphs.clear();
+// Vectors above which the chain walk is used: a cover plan takes about 40 bytes of records per
+// vector and its construction grows with the summed path lengths.
+constexpr int64_t kCoverVectors = (int64_t)1 << 22;
+
+// The cover plan for an image size and cutoff with the fields of `f` fixed; plan->ok is false when
+// the rows do not fit in LDS.
+lpf_status get_cover_plan(lpf_ctx c, int W, int H, int cx, int cy, const FixedShape &f,
+                          CoverPlan *&plan) {
+  const std::array<int, 8> key = {W, H, cx, cy, f.R, f.S, f.wpg, f.lds};
+  auto it = c->cover_plans.find(key);
+  if (it != c->cover_plans.end()) {
+    plan = &it->second;
+    return LPF_OK;
+  }
+  CoverPlan p;
+  const int64_t nv = lpf_num_vectors(cx, cy);
+  try {
+    CoverHost h;
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->dev);
+    if (nv <= kCoverVectors && plan_cover(W, H, cx, cy, f.R, f.S, f.wpg, f.lds, cus, h)) {
+      std::vector<int32_t> order(h.groups.size());
+      for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
+      std::stable_sort(order.begin(), order.end(),
+                       [&](int a, int b) { return h.cost[a] > h.cost[b]; });
+      // one allocation, each table at a multiple of 256 bytes
+      const void *src[6] = {h.groups.data(), h.piece_off.data(), h.recs.data(),
+                            h.bops.data(),   h.mems.data(),      order.data()};
+      const size_t len[6] = {h.groups.size() * sizeof(CoverGroup),
+                             h.piece_off.size() * sizeof(int32_t),
+                             h.recs.size() * sizeof(int4),
+                             h.bops.size() * sizeof(uint32_t),
+                             h.mems.size() * sizeof(MemDesc),
+                             order.size() * sizeof(int32_t)};
+      size_t off[7] = {};
+      for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + (len[i] + 255) / 256 * 256;
+      std::vector<char> all(off[6]);
+      for (int i = 0; i < 6; ++i)
+        if (len[i]) memcpy(all.data() + off[i], src[i], len[i]);
+      hipError_t e = hipMalloc(&p.mem, off[6]);
+      if (e != hipSuccess) return hip_fail(e, "lpf_full: plan allocation");
+      e = hipMemcpy(p.mem, all.data(), off[6], hipMemcpyHostToDevice);
+      if (e != hipSuccess) {
+        (void)hipFree(p.mem);
+        return hip_fail(e, "lpf_full: plan upload");
+      }
+      char *m = (char *)p.mem;
+      p.img = CoverImg{(const CoverGroup *)(m + off[0]), (const int32_t *)(m + off[1]),
+                       (const int4 *)(m + off[2]),       (const uint32_t *)(m + off[3]),
+                       (const MemDesc *)(m + off[4]),    W, H, cx, cy, h.sh.R, h.sh.S, h.nct,
+                       h.sh.nwb, h.nsplit, (int)nv, 0};
+      p.order = (int32_t *)(m + off[5]);
+      p.sh = h.sh;
+      p.ngroups = (int)h.groups.size();
+      p.lds_bytes = h.lds_bytes;
+      p.cost = std::move(h.cost);
+      p.ok = true;
+    }
+    plan = &c->cover_plans.emplace(key, std::move(p)).first->second;
+  } catch (const std::exception &) {
+    (void)hipFree(p.mem);
+    return fail(LPF_E_NOMEM, "lpf_full: host memory for the plan");
+  }
+  return LPF_OK;
 }
 
 // Two-point counts plan.  Vector families {dx0, dy, nj}: for each dy, the dx of D_c taken in
@@ -1083,6 +1198,7 @@ lpf_status lpf_ctx_create(int hip_device, lpf_ctx *out) {
   c->dev = hip_device;
   DeviceGuard g(c->dev);
   hipError_t e = prepare_full_kernels(kMaxLds);
+  if (e == hipSuccess) e = prepare_cover_kernels(kMaxLds);
   if (e == hipSuccess) e = prepare_delta_kernels(kDeltaLdsMax);
   if (e == hipSuccess) e = prepare_step_kernels(kDeltaLdsMax);
   if (e == hipSuccess) e = prepare_s2_kernels(kMaxLds);
@@ -1123,7 +1239,8 @@ void lpf_ctx_destroy(lpf_ctx c) {
       (void)hipFree(kv.second.mems);
       (void)hipFree(kv.second.bin_off);
     }
-    release_batch_graphs(c);
+    for (auto &kv : c->cover_plans) (void)hipFree(kv.second.mem);
+    for (auto &kv : c->batch_plans) free_batch_plan(kv.second);
     for (auto &kv : c->delta_plans) {
       (void)hipFree(kv.second.vecs);
       (void)hipFree(kv.second.chunk_off);
@@ -1165,6 +1282,35 @@ lpf_status lpf_pack(lpf_ctx c, const uint8_t *img, int W, int H, uint64_t *bits,
 }
 
 namespace {
+// The counts of one image by the chain walk on rows in device memory, for rows that do not fit
+// in LDS (arguments checked, context locked).
+lpf_status full_from_memory(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int cy,
+                            unsigned phase_mask, int out_layout, uint32_t *counts, hipStream_t s,
+                            bool skip, const uint64_t *sample) {
+  FullPlan *plan = nullptr;
+  lpf_status st = get_full_plan(c, W, H, cx, cy, plan);
+  if (st != LPF_OK) return st;
+  const FullShape &sh = plan->sh;
+  hipError_t e;
+  if ((e = c->ext.ensure((size_t)sh.lds_rows * sh.we * sizeof(uint32_t))) != hipSuccess)
+    return hip_fail(e, "lpf_full: scratch");
+  uint32_t *ext = (uint32_t *)c->ext.p;
+  if ((e = launch_ext(bits, W, H, sh.we, ext, s, sh.lds_rows)) != hipSuccess)
+    return hip_fail(e, "lpf_full: ext");
+  FullImg I = make_img(*plan, ext, counts, W, H, cx, cy, out_layout);
+  if (sample) {
+    if ((e = c->sext.ensure((size_t)H * sh.we * sizeof(uint32_t))) != hipSuccess)
+      return hip_fail(e, "lpf_full_sampled: scratch");
+    if ((e = launch_ext(sample, W, H, sh.we, (uint32_t *)c->sext.p, s)) != hipSuccess)
+      return hip_fail(e, "lpf_full_sampled: ext");
+    I.sample = (const uint32_t *)c->sext.p;
+    I.sample_stride = sh.we;
+  }
+  if ((e = launch_full(I, sh, phase_mask, skip, s)) != hipSuccess)
+    return hip_fail(e, "lpf_full: kernel");
+  return LPF_OK;
+}
+
 lpf_status full_impl(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int cy,
                      unsigned phase_mask, int out_layout, uint32_t *counts, void *stream,
                      bool skip, const uint64_t *sample = nullptr) {
@@ -1181,28 +1327,29 @@ lpf_status full_impl(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int 
   std::lock_guard<std::mutex> lk(c->mu);
   DeviceGuard g(c->dev);
   if (!g.ok) return fail(LPF_E_DEVICE, "lpf_full: cannot select the context's device");
-  FullPlan *plan = nullptr;
-  lpf_status st = get_full_plan(c, W, H, cx, cy, plan);
-  if (st != LPF_OK) return st;
-  const FullShape &sh = plan->sh;
   hipStream_t s = (hipStream_t)stream;
+  FixedShape f;
+  std::string why;
+  if (!fixed_shape(c, W, H, cx, cy, f, why)) return fail(LPF_E_UNSUPPORTED, "lpf_full: " + why);
+  CoverPlan *cp = nullptr;
+  lpf_status st = get_cover_plan(c, W, H, cx, cy, f, cp);
+  if (st != LPF_OK) return st;
+  if (!cp->ok) return full_from_memory(c, bits, W, H, cx, cy, phase_mask, out_layout, counts, s,
+                                       skip, sample);
   hipError_t e;
-  const int ext_rows = sh.glob ? sh.lds_rows : H;
-  if ((e = c->ext.ensure((size_t)ext_rows * sh.we * sizeof(uint32_t))) != hipSuccess)
-    return hip_fail(e, "lpf_full: scratch");
-  uint32_t *ext = (uint32_t *)c->ext.p;
-  if ((e = launch_ext(bits, W, H, sh.we, ext, s, ext_rows)) != hipSuccess)
-    return hip_fail(e, "lpf_full: ext");
-  FullImg I = make_img(*plan, ext, counts, W, H, cx, cy, out_layout);
+  const uint32_t *starts = nullptr;
   if (sample) {
-    if ((e = c->sext.ensure((size_t)H * sh.we * sizeof(uint32_t))) != hipSuccess)
-      return hip_fail(e, "lpf_full_sampled: scratch");
-    if ((e = launch_ext(sample, W, H, sh.we, (uint32_t *)c->sext.p, s)) != hipSuccess)
-      return hip_fail(e, "lpf_full_sampled: ext");
-    I.sample = (const uint32_t *)c->sext.p;
-    I.sample_stride = sh.we;
+    const size_t n = (size_t)2 * H * ((W + 31) / 32) * sizeof(uint32_t);
+    if ((e = c->sext.ensure(n)) != hipSuccess) return hip_fail(e, "lpf_full_sampled: scratch");
+    if ((e = launch_start_sets(sample, W, H, (uint32_t *)c->sext.p, s)) != hipSuccess)
+      return hip_fail(e, "lpf_full_sampled: start pixels");
+    starts = (const uint32_t *)c->sext.p;
   }
-  if ((e = launch_full(I, sh, phase_mask, skip, s)) != hipSuccess) return hip_fail(e, "lpf_full: kernel");
+  CoverImg I = cp->img;
+  I.layout = out_layout;
+  if ((e = launch_cover(I, cp->sh, cp->ngroups, cp->order, cp->lds_bytes, phase_mask, bits, starts,
+                        counts, s)) != hipSuccess)
+    return hip_fail(e, "lpf_full: kernel");
   return LPF_OK;
 }
 }  // namespace
@@ -1232,7 +1379,7 @@ lpf_status lpf_full_noalloc(lpf_ctx c, const uint64_t *bits, int W, int H, int c
   if (!c->noalloc_scratch) return fail(LPF_E_DEVICE, "lpf_full_noalloc: no scratch address");
   FullShape sh{};
   std::string why;
-  if (!choose_shape(c, W, H, cx, cy, sh, why))
+  if (!choose_shape(c, W, H, cx, cy, false, sh, why))
     return fail(LPF_E_UNSUPPORTED, "lpf_full_noalloc: " + why);
   if (full_lds_bytes(sh, sh.wpg) > (size_t)kMaxLds)
     return fail(LPF_E_UNSUPPORTED, "lpf_full_noalloc: tile shape needs more than 160 KiB of LDS");
@@ -2145,6 +2292,82 @@ void lpf_anneal_destroy(lpf_anneal a) {
   delete a;
 }
 
+namespace {
+lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images,
+                            unsigned phase_mask, int out_layout, BatchPlan *&out) {
+  BatchPlan *b = nullptr;
+  try {
+    b = new BatchPlan();
+    b->n_images = n_images;
+    std::vector<CoverImg> imgs(n_images);
+    std::vector<int64_t> bits_off(n_images), counts_off(n_images);
+    std::map<int, std::vector<std::pair<int64_t, int4>>> items;  // per waves of a workgroup
+    std::map<int, size_t> lds;
+    for (int i = 0; i < n_images; ++i) {
+      const lpf_image_desc &d = descs[i];
+      FixedShape f;
+      std::string why;
+      CoverPlan *p = nullptr;
+      lpf_status st = LPF_OK;
+      if (!fixed_shape(c, d.W, d.H, d.cx, d.cy, f, why))
+        st = fail(LPF_E_UNSUPPORTED, "lpf_batch: " + why);
+      if (st == LPF_OK) st = get_cover_plan(c, d.W, d.H, d.cx, d.cy, f, p);
+      if (st != LPF_OK) {
+        free_batch_plan(b);
+        return st;
+      }
+      bits_off[i] = d.bits_off;
+      counts_off[i] = d.counts_off;
+      if (!p->ok) {
+        b->glob.push_back(i);
+        continue;
+      }
+      imgs[i] = p->img;
+      imgs[i].layout = out_layout;
+      b->split = b->split || imgs[i].nsplit > 1;
+      auto &list = items[p->sh.wpg];
+      for (int g = 0; g < p->ngroups; ++g)
+        for (int ph = 0; ph < 2; ++ph)
+          for (int sp = 0; sp < p->img.nsplit; ++sp)
+            if (phase_mask >> ph & 1u)
+              list.push_back({p->cost[g] / p->img.nsplit, make_int4(i, g, ph, sp)});
+      lds[p->sh.wpg] = std::max(lds[p->sh.wpg], p->lds_bytes);
+    }
+    hipError_t e = hipSuccess;
+    auto upload = [&](auto *&dst, const auto &v) {
+      if (e != hipSuccess) return;
+      e = hipMalloc(&dst, sizeof(v[0]) * std::max<size_t>(v.size(), 1));
+      if (e == hipSuccess && !v.empty())
+        e = hipMemcpy(dst, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice);
+    };
+    upload(b->imgs, imgs);
+    upload(b->bits_off, bits_off);
+    upload(b->counts_off, counts_off);
+    for (auto kv = items.rbegin(); kv != items.rend(); ++kv) {  // the largest groups first
+      std::stable_sort(kv->second.begin(), kv->second.end(),
+                       [](const auto &x, const auto &y) { return x.first > y.first; });
+      std::vector<int4> list;
+      for (auto &x : kv->second) list.push_back(x.second);
+      b->launches.emplace_back();
+      BatchPlan::Launch &l = b->launches.back();
+      l.n_items = (int)list.size();
+      l.wpg = kv->first;
+      l.lds_bytes = lds[kv->first];
+      upload(l.items, list);
+    }
+    if (e != hipSuccess) {
+      free_batch_plan(b);
+      return hip_fail(e, "lpf_batch: plan");
+    }
+  } catch (const std::exception &) {
+    free_batch_plan(b);
+    return fail(LPF_E_NOMEM, "lpf_batch: host memory");
+  }
+  out = b;
+  return LPF_OK;
+}
+}  // namespace
+
 lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc *descs,
                      int n_images, unsigned phase_mask, int out_layout, uint32_t *counts_pool,
                      void *stream) {
@@ -2170,135 +2393,43 @@ lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc 
   std::string key;
   {
     char buf[96];
-    snprintf(buf, sizeof buf, "%u|%d|%d|%d|%d|%d|%d|", phase_mask, out_layout, n_images,
-             c->force_R, c->force_S, c->force_wpg, c->force_lds);
+    snprintf(buf, sizeof buf, "%u|%d|%d|%d|%d|%d|%d|%d|", phase_mask, out_layout, n_images,
+             c->force_R, c->force_S, c->force_wpg, c->force_lds, c->tune_count);
     key = buf;
     key.append(reinterpret_cast<const char *>(descs), sizeof(lpf_image_desc) * (size_t)n_images);
   }
-  auto it = c->batch_graphs.find(key);
-  if (it == c->batch_graphs.end() && c->batch_graphs.size() >= kMaxBatchGraphs) {
-    auto lru = c->batch_graphs.begin();
-    for (auto j = c->batch_graphs.begin(); j != c->batch_graphs.end(); ++j)
+  auto it = c->batch_plans.find(key);
+  if (it == c->batch_plans.end() && c->batch_plans.size() >= kMaxBatchPlans) {
+    auto lru = c->batch_plans.begin();
+    for (auto j = c->batch_plans.begin(); j != c->batch_plans.end(); ++j)
       if (j->second->last_use < lru->second->last_use) lru = j;
-    (void)hipDeviceSynchronize();  // its last replay may still run on any stream
-    free_batch_graph(lru->second);
-    c->batch_graphs.erase(lru);
+    (void)hipDeviceSynchronize();  // its last launch may still run on any stream
+    free_batch_plan(lru->second);
+    c->batch_plans.erase(lru);
   }
-  if (it == c->batch_graphs.end()) {
-    // 8 waves per group, or 16 when some image's rows need so much LDS that only one group fits
-    // a CU (four waves per SIMD either way; one launch has one group size); every image's shape
-    // is checked while its plan is built
-    int wpg = 8;
-    std::vector<FullImg> imgs(n_images);
-    std::vector<int64_t> bits_off(n_images), ext_off(n_images), counts_off(n_images);
-    std::vector<std::pair<int64_t, int2>> items;
-    int64_t ext_total = 0;
-    size_t stage_max = 0;
-    bool any_tiled = false;
-    int max_we = 1, max_h = 1;
-    for (int pass = 0; pass < 2; ++pass) {
-    items.clear();
-    ext_total = 0;
-    stage_max = 0;
-    any_tiled = false;
-    max_we = 1;
-    max_h = 1;
-    for (int i = 0; i < n_images; ++i) {
-      const lpf_image_desc &d = descs[i];
-      FullPlan *plan = nullptr;
-      const int saved_wpg = c->force_wpg;
-      c->force_wpg = wpg;
-      lpf_status st = get_full_plan(c, d.W, d.H, d.cx, d.cy, plan);
-      c->force_wpg = saved_wpg;
-      if (st != LPF_OK) return st;
-      const FullShape &sh = plan->sh;
-      ext_off[i] = ext_total;
-      bits_off[i] = d.bits_off;
-      ext_total += (int64_t)(sh.glob ? sh.lds_rows : d.H) * sh.we;
-      imgs[i] = make_img(*plan, nullptr, nullptr, d.W, d.H, d.cx, d.cy, out_layout);
-      counts_off[i] = d.counts_off;
-      if (!sh.glob) stage_max = std::max(stage_max, (size_t)sh.lds_rows * sh.rst);
-      any_tiled = any_tiled || sh.ntiles > 1;
-      max_we = std::max(max_we, sh.we);
-      max_h = std::max(max_h, sh.glob ? sh.lds_rows : d.H);
-      const int64_t rows_work = (int64_t)d.H * sh.S;
-      for (int b = 0; b < sh.nbins; ++b)
-        items.push_back({plan->bin_cost[b] * rows_work * sh.R + (int64_t)sh.lds_rows * sh.we * sh.ntiles,
-                         make_int2(i, b)});
-    }
-    if (pass == 0 && (stage_max * 4 + (size_t)kSlotWords * 4) * 2 > (size_t)kMaxLds) {
-      wpg = 16;
-      continue;
-    }
-    break;
-    }
-    std::stable_sort(items.begin(), items.end(),
-                     [](const std::pair<int64_t, int2> &a, const std::pair<int64_t, int2> &b) {
-                       return a.first > b.first;
-                     });
-    std::vector<int2> item_list(items.size());
-    for (size_t k = 0; k < items.size(); ++k) item_list[k] = items[k].second;
-    const size_t lds_bytes = stage_max * 4 + (size_t)kSlotWords * 4;
-    (void)any_tiled;
-    if (lds_bytes > (size_t)(kMaxLds - kBatchStaticLds))
-      return fail(LPF_E_UNSUPPORTED, "lpf_batch: staging exceeds LDS");
-    BatchGraph *b = new (std::nothrow) BatchGraph();
-    if (!b) return fail(LPF_E_NOMEM, "lpf_batch: host memory");
-    hipError_t e;
-    if ((e = hipMalloc(&b->ext, sizeof(uint32_t) * (size_t)std::max<int64_t>(ext_total, 1))) != hipSuccess ||
-        (e = hipMalloc(&b->imgs, sizeof(FullImg) * n_images)) != hipSuccess ||
-        (e = hipMalloc(&b->args, sizeof(BatchArgs))) != hipSuccess ||
-        (e = hipMalloc(&b->counts_off, sizeof(int64_t) * n_images)) != hipSuccess ||
-        (e = hipMalloc(&b->items, sizeof(int2) * item_list.size())) != hipSuccess ||
-        (e = hipMalloc(&b->bits_off, sizeof(int64_t) * n_images)) != hipSuccess ||
-        (e = hipMalloc(&b->ext_off, sizeof(int64_t) * n_images)) != hipSuccess ||
-        (e = hipMalloc(&b->counter, sizeof(int))) != hipSuccess) {
-      free_batch_graph(b);
-      return hip_fail(e, "lpf_batch: allocation");
-    }
-    for (int i = 0; i < n_images; ++i) imgs[i].E = b->ext + ext_off[i];
-    if ((e = hipMemcpy(b->imgs, imgs.data(), sizeof(FullImg) * n_images, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(b->items, item_list.data(), sizeof(int2) * item_list.size(), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(b->bits_off, bits_off.data(), sizeof(int64_t) * n_images, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(b->ext_off, ext_off.data(), sizeof(int64_t) * n_images, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(b->counts_off, counts_off.data(), sizeof(int64_t) * n_images, hipMemcpyHostToDevice)) != hipSuccess) {
-      free_batch_graph(b);
-      return hip_fail(e, "lpf_batch: upload");
-    }
-    int cus = 256;
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->dev);
-    const int per_cu = std::max<int>(1, std::min<int>(4, (int)(kMaxLds / std::max<size_t>(lds_bytes, 1))));
-    b->n_items = (int)item_list.size();
-    b->n_wg = std::max(1, std::min(b->n_items, cus * per_cu));
-    // capture on a private stream, launch on the caller's
-    hipStream_t cap;
-    if ((e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking)) != hipSuccess) {
-      free_batch_graph(b);
-      return hip_fail(e, "lpf_batch: capture stream");
-    }
-    hipError_t ce = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-    if (ce == hipSuccess) {
-      hipError_t e1 = launch_ext_batch(b->imgs, n_images, max_we, max_h, b->args, b->bits_off,
-                                       b->ext, b->ext_off, cap);
-      hipError_t e2 = launch_batch(b->imgs, b->args, b->counts_off, b->items, b->n_items,
-                                   b->counter, wpg, phase_mask, lds_bytes, (int)stage_max,
-                                   b->n_wg, cap);
-      ce = hipStreamEndCapture(cap, &b->graph);
-      if (ce == hipSuccess && (e1 != hipSuccess || e2 != hipSuccess)) ce = e1 != hipSuccess ? e1 : e2;
-    }
-    if (ce == hipSuccess) ce = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
-    (void)hipStreamDestroy(cap);
-    if (ce != hipSuccess) {
-      free_batch_graph(b);
-      return hip_fail(ce, "lpf_batch: graph capture");
-    }
-    it = c->batch_graphs.emplace(key, b).first;
+  if (it == c->batch_plans.end()) {
+    BatchPlan *b = nullptr;
+    lpf_status st = build_batch_plan(c, descs, n_images, phase_mask, out_layout, b);
+    if (st != LPF_OK) return st;
+    it = c->batch_plans.emplace(key, b).first;
   }
-  it->second->last_use = ++c->batch_clock;
-  hipError_t e = launch_batch_args(it->second->args, bits_pool, counts_pool, s);
-  if (e != hipSuccess) return hip_fail(e, "lpf_batch: buffers");
-  e = hipGraphLaunch(it->second->exec, s);
-  if (e != hipSuccess) return hip_fail(e, "lpf_batch: graph launch");
+  BatchPlan &b = *it->second;
+  b.last_use = ++c->batch_clock;
+  if (b.split) {
+    hipError_t e = launch_cover_zero(b.imgs, b.counts_off, b.n_images, phase_mask, counts_pool, s);
+    if (e != hipSuccess) return hip_fail(e, "lpf_batch: zero");
+  }
+  for (const auto &l : b.launches) {
+    hipError_t e = launch_cover_batch(b.imgs, b.bits_off, b.counts_off, l.items, l.n_items, l.wpg,
+                                      l.lds_bytes, phase_mask, bits_pool, counts_pool, s);
+    if (e != hipSuccess) return hip_fail(e, "lpf_batch: kernel");
+  }
+  for (int i : b.glob) {
+    const lpf_image_desc &d = descs[i];
+    lpf_status st = full_from_memory(c, bits_pool + d.bits_off, d.W, d.H, d.cx, d.cy, phase_mask,
+                                     out_layout, counts_pool + d.counts_off, s, false, nullptr);
+    if (st != LPF_OK) return st;
+  }
   return LPF_OK;
 }
 
@@ -2332,36 +2463,50 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);
   }
-  for (int R : {2, 4, 8, 16}) {
-    if (R > 2 * next_pow2(swd) && R > 2) continue;
-    for (int wpg : {4, 8, 16}) {
-      for (int lds : {64 * 1024, kBigLds}) {
-        if (wpg == 16 && lds != kBigLds) continue;  // 16 waves only at one group per CU
-        c->force_R = R;
-        c->force_S = 0;
-        c->force_wpg = wpg;
-        c->force_lds = lds;
-        float ms_best = 1e30f;
-        bool ok = true;
-        for (int rep = 0; rep < 3 && ok; ++rep) {
-          DeviceGuard g(c->dev);
-          (void)hipEventRecord(e0, s);
-          ok = lpf_full(c, bits, W, H, cx, cy, phase_mask, LPF_OUT_HALF, tmp, stream) == LPF_OK;
-          (void)hipEventRecord(e1, s);
-          if (ok && hipEventSynchronize(e1) == hipSuccess) {
-            float ms = 0;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            if (rep) ms_best = std::min(ms_best, ms);  // first run builds the plan
-          }
-        }
-        if (ok && ms_best < best.ms) {
-          best.R = R;
-          best.wpg = wpg;
-          best.lds = lds;
-          best.ms = ms_best;
-        }
+  auto time = [&](int R, int wpg, int lds) {
+    c->force_R = R;
+    c->force_S = 0;
+    c->force_wpg = wpg;
+    c->force_lds = lds;
+    float ms_best = 1e30f;
+    bool ok = true;
+    for (int rep = 0; rep < 3 && ok; ++rep) {
+      DeviceGuard g(c->dev);
+      (void)hipEventRecord(e0, s);
+      ok = lpf_full(c, bits, W, H, cx, cy, phase_mask, LPF_OUT_HALF, tmp, stream) == LPF_OK;
+      (void)hipEventRecord(e1, s);
+      if (ok && hipEventSynchronize(e1) == hipSuccess) {
+        float ms = 0;
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        if (rep) ms_best = std::min(ms_best, ms);  // first run builds the plan
       }
     }
+    if (!ok || ms_best >= best.ms) return;
+    best.R = R;
+    best.S = 0;
+    best.wpg = wpg;
+    best.lds = lds;
+    best.ms = ms_best;
+    if (R == 0) {  // the automatic plan: the fields it chose
+      auto it = c->cover_plans.find({W, H, cx, cy, 0, 0, 0, 0});
+      if (it == c->cover_plans.end() || !it->second.ok) {
+        best.ms = 1e30;
+        return;
+      }
+      best.R = it->second.sh.R;
+      best.S = it->second.sh.S;
+      best.wpg = it->second.sh.wpg;
+      best.lds = it->second.sh.lds;
+    }
+  };
+  for (int R : {0, 2, 4, 8, 16}) {
+    if (R > 2 * next_pow2(swd) && R > 2) continue;
+    for (int wpg : {0, 4, 8, 16})
+      for (int lds : {0, 80 * 1024, 160 * 1024}) {
+        if ((R == 0) != (wpg == 0) || (R == 0) != (lds == 0)) continue;
+        if (wpg == 16 && lds != 160 * 1024) continue;  // 16 waves only at one group per CU
+        time(R, wpg, lds);
+      }
   }
   c->force_R = saved[0];
   c->force_S = saved[1];
@@ -2377,6 +2522,7 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
   {
     std::lock_guard<std::mutex> lk(c->mu);
     c->tuned[std::make_tuple(W, H, cx, cy)] = best;
+    ++c->tune_count;
   }
   if (best_ms) *best_ms = best.ms;
   return LPF_OK;

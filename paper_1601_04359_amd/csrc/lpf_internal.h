@@ -50,8 +50,6 @@ struct FullShape {
 
 // Count slots of one bin in LDS (two words per member): at most kSlotWords / 2 members per bin.
 constexpr int kSlotWords = 512;
-// LDS the persistent batch kernel keeps for itself (the claimed work item), below the 160 KiB.
-constexpr int kBatchStaticLds = 256;
 
 // One image as seen by the full-evaluation kernels.
 struct FullImg {
@@ -463,20 +461,6 @@ hipError_t launch_full_canon(const FullImg &I, const FullShape &sh, unsigned pha
                              hipStream_t stream);
 size_t full_lds_bytes(const FullShape &sh, int wpg);
 int full_wgs_per_cu(int R, bool skip, int wpg, size_t lds_bytes);
-// The caller's buffers of one lpf_batch call (device struct, set before each replay).
-struct BatchArgs {
-  const uint64_t *pool;
-  uint32_t *counts;
-};
-hipError_t launch_batch(const FullImg *imgs, const BatchArgs *args, const int64_t *counts_off,
-                        const int2 *items, int n_items, int *counter, int wpg,
-                        unsigned phase_mask, size_t lds_bytes, int cnt_off, int n_wg,
-                        hipStream_t stream);
-hipError_t launch_batch_args(BatchArgs *args, const uint64_t *pool, uint32_t *counts,
-                             hipStream_t stream);
-hipError_t launch_ext_batch(const FullImg *imgs, int n_images, int max_we, int max_h,
-                            const BatchArgs *args, const int64_t *bits_off, uint32_t *ext,
-                            const int64_t *ext_off, hipStream_t stream);
 hipError_t prepare_full_kernels(int max_lds_bytes);
 
 // Throughput probes (k_peak.hip): kind 0-3 int32 VALU mixes, 4 LDS reads; nwg workgroups of 256

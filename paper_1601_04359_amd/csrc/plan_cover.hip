@@ -1,0 +1,928 @@
+// Launch plans of the full evaluation (host code): paths covered by shared words.
+//
+// Counting one vector means AND-ing the image, shifted to each pixel of the vector's digitised
+// path.  Two facts make most of these pixels free:
+//  * Paths of neighbouring slopes start alike.  The walked paths of one octant, in the order of
+//    their slopes, form a prefix tree; a product taken at a branch is kept in registers and every
+//    path below the branch goes on from it.  A shorter vector whose path is a prefix of a longer
+//    one (Sec. 3.2) is a node on the way and is counted there.
+//  * An AND may take a pixel twice.  A digitised line of a narrow range of slopes repeats a few
+//    pixel patterns (words) all along, so with the product of a word kept for every pixel of the
+//    staged rows (one mask array in LDS), a step takes the whole word at once, and overlapping
+//    words cover a path exactly: greedily, the step that reaches furthest without passing the
+//    next count.
+// At cutoff 128 both together leave about 2 steps per vector (86 without them, 38 with prefixes
+// shared by whole chains only).
+//
+// A group is a range of slopes of one octant with up to kCoverWords words, walked by one
+// workgroup; a piece is the part of it that one wave walks.  Vectors with dx < 0 are walked on the
+// mirrored image, so every offset is >= 0.
+#include <algorithm>
+#include <atomic>
+#include <climits>
+#include <cmath>
+#include <cstdlib>
+#include <exception>
+#include <thread>
+
+#include "../../include/lpf.h"
+#include "cover.h"
+
+namespace lpf {
+
+namespace {
+
+// A walked path: the first len + 1 pixels of the line of slope m / n (minor over major), and the
+// members counted on it.
+struct Path {
+  int n, m, len, m0, nm;
+  int q(int k) const { return n ? (int)((2ll * k * m + n) / (2ll * n)) : 0; }
+};
+
+struct Octant {
+  bool xm = true, mir = false;
+  std::vector<Path> paths;   // by slope, then length
+  std::vector<MemDesc> mems;
+};
+
+// Canonical index of (dx, dy): [0,cx] x [0,cy] row by row, then [-cx,-1] x [1,cy].
+int64_t index_of(int cx, int cy, int dx, int dy) {
+  if (dx >= 0) return (int64_t)dy * (cx + 1) + dx;
+  return (int64_t)(cx + 1) * (cy + 1) + (int64_t)(dy - 1) * cx + (dx + cx);
+}
+
+// The vectors of one octant as walked paths: longest first, each with the vectors not yet taken
+// whose paths are its prefixes (u = pixel k of the walk, a prefix when u's slope lies in the
+// interval of slopes that digitise to pixels 0..k; see plan_full.hip).  The octant owns the
+// vectors with |dx| >= dy (xm) or |dx| < dy, dx < 0 (mir) or dx >= 0, so that octants are
+// independent.
+void build_octant(int cx, int cy, bool xm, bool mir, Octant &o) {
+  o.xm = xm;
+  o.mir = mir;
+  const int N = xm ? cx : cy, M = xm ? cy : cx;
+  const int mlo = mir ? 1 : 0;
+  auto put = [&](int k, int q) {
+    const int dx = (xm ? k : q) * (mir ? -1 : 1), dy = xm ? q : k;
+    o.mems.push_back(MemDesc{(int32_t)index_of(cx, cy, dx, dy), (int16_t)dx, (int16_t)dy, k});
+  };
+  const bool zero = !mir && (xm ? (cx > 0 || cy == 0) : (cx == 0 && cy > 0));
+  if (zero && N == 0) {  // the 1 x 1 domain: the zero vector alone
+    o.paths.push_back(Path{0, 0, 0, 0, 1});
+    put(0, 0);
+    return;
+  }
+  bool zero_done = !zero;
+  std::vector<char> placed((size_t)(N + 1) * (M + 1), 0);
+  for (int n = N; n >= 1; --n) {
+    const int mhi = std::min(xm ? n : n - 1, M);
+    for (int m = mlo; m <= mhi; ++m) {
+      if (placed[(size_t)n * (M + 1) + m]) continue;
+      Path p{n, m, n, (int)o.mems.size(), 0};
+      if (!zero_done) {
+        put(0, 0);
+        zero_done = true;
+      }
+      // slopes that digitise to the pixels so far: [lp / lq, hp / hq)
+      int64_t lp = -1, lq = 1, hp = (int64_t)1 << 30, hq = 1;
+      int err = n, q = 0;
+      for (int k = 1; k < n; ++k) {
+        err += 2 * m;
+        if (err >= 2 * n) {
+          err -= 2 * n;
+          ++q;
+        }
+        if (q >= mlo && (xm || q < k) && !(q * lq < lp * k) && q * hq < hp * k) {
+          char &t = placed[(size_t)k * (M + 1) + q];
+          if (!t) {
+            t = 1;
+            put(k, q);
+          }
+        }
+        if (lp * 2 * k < (2 * q - 1) * lq) {
+          lp = 2 * q - 1;
+          lq = 2 * k;
+        }
+        if ((2 * q + 1) * hq < hp * 2 * k) {
+          hp = 2 * q + 1;
+          hq = 2 * k;
+        }
+      }
+      put(n, m);
+      p.nm = (int)o.mems.size() - p.m0;
+      // paths with many members (axes, diagonals: one per pixel) are cut into several walks
+      constexpr int kCut = kCoverSlots / 4;
+      for (int j0 = 0; j0 < p.nm; j0 += kCut) {
+        Path c = p;
+        c.m0 = p.m0 + j0;
+        c.nm = std::min(kCut, p.nm - j0);
+        c.len = o.mems[c.m0 + c.nm - 1].l;
+        o.paths.push_back(c);
+      }
+    }
+  }
+  std::sort(o.paths.begin(), o.paths.end(), [](const Path &a, const Path &b) {
+    const int64_t x = (int64_t)a.m * b.n, y = (int64_t)b.m * a.n;
+    return x != y ? x < y : a.len < b.len;
+  });
+}
+
+// Steps of a path along the minor axis, bit k - 1 = q_k - q_{k-1}.
+using Bits = std::vector<uint64_t>;
+void letters(const Path &p, int len, Bits &b) {
+  b.assign((size_t)(len >> 6) + 2, 0);
+  int err = p.n;
+  for (int k = 0; k < len; ++k) {
+    err += 2 * p.m;
+    if (err >= 2 * p.n) {
+      err -= 2 * p.n;
+      b[k >> 6] |= 1ull << (k & 63);
+    }
+  }
+}
+inline uint64_t bits64(const Bits &b, int j) {
+  const int w = j >> 6, s = j & 63;
+  return s ? (b[w] >> s) | (b[w + 1] << (64 - s)) : b[w];
+}
+int common(const Bits &a, const Bits &b, int len) {
+  for (int w = 0; w * 64 < len; ++w) {
+    const uint64_t d = a[w] ^ b[w];
+    if (d) return std::min(len, w * 64 + __builtin_ctzll(d));
+  }
+  return len;
+}
+
+// A word: L steps (L + 1 pixels).
+struct Word {
+  int L = 0;
+  Bits b;
+};
+Word sub_word(const Bits &b, int j, int L) {
+  Word w;
+  w.L = L;
+  w.b.assign((size_t)(L >> 6) + 2, 0);
+  for (int k = 0; k < L; k += 64) {
+    uint64_t v = bits64(b, j + k);
+    if (L - k < 64) v &= (1ull << (L - k)) - 1;
+    w.b[k >> 6] = v;
+  }
+  return w;
+}
+// last[j] = the last pixel <= j where the word starts on the path, -1 when none (j = 0..len).
+void find_word(const Bits &b, int len, const Word &w, std::vector<int> &last) {
+  last.assign(len + 1, -1);
+  int la = -1;
+  const uint64_t m0 = w.L < 64 ? (1ull << w.L) - 1 : ~0ull;
+  for (int j = 0; j <= len; ++j) {
+    if (j + w.L <= len && ((bits64(b, j) ^ w.b[0]) & m0) == 0) {
+      bool ok = true;
+      for (int k = 64; ok && k < w.L; k += 64) {
+        const uint64_t m = w.L - k < 64 ? (1ull << (w.L - k)) - 1 : ~0ull;
+        ok = ((bits64(b, j + k) ^ w.b[k >> 6]) & m) == 0;
+      }
+      if (ok) la = j;
+    }
+    last[j] = la;
+  }
+}
+
+// The furthest step from a path covered below pixel c that does not pass pixel `to`: array (0 the
+// image: one pixel) and the pixel it starts at; returns the last pixel it reaches.
+struct Step {
+  int arr, j;
+};
+int best_step(const std::vector<Word> &words, const std::vector<std::vector<int>> &last, int c,
+              int to, Step &s) {
+  int end = c;
+  s = Step{0, c};
+  for (size_t w = 0; w < words.size(); ++w) {
+    const int at = std::min(c, to - words[w].L);
+    if (at < 0) continue;
+    const int j = last[w][at];
+    if (j >= 0 && j + words[w].L > end) {
+      end = j + words[w].L;
+      s = Step{(int)w + 1, j};
+    }
+  }
+  return end;
+}
+
+struct GroupOut {
+  bool ok = false;
+  CoverGroup g{};
+  size_t lds_dw = 0;
+  std::vector<int32_t> piece_off;  // within recs
+  std::vector<int4> recs;
+  std::vector<uint32_t> bops;
+  std::vector<MemDesc> mems;
+  int64_t cost = 0, steps = 0, counts = 0, bsteps = 0;
+};
+
+// LDS rows of a group: the window of the image that its paths reach from a tile's start pixels.
+// Row y (0 = the tile's first row) is staged from dword xs(y) on; rows are rst dwords apart, so
+// the address of (row, dword) is linear and the window of a steep group, which shifts to the
+// right row by row, is held without the rest of its bounding box.
+struct Geometry {
+  const Octant *o;
+  int SR, maxpy;
+  std::vector<int> lo, hi;  // first and last pixel offset in x at each row offset
+  Geometry(const Octant &oct, const Path &first, const Path &last, int len, int sr) : o(&oct), SR(sr) {
+    maxpy = oct.xm ? last.q(len) : len;
+    lo.assign(maxpy + 1, INT_MAX);
+    hi.assign(maxpy + 1, 0);
+    for (int k = 0; k <= len; ++k) {
+      const int a = first.q(k), b = last.q(k);
+      if (oct.xm) {
+        for (int y = a; y <= b; ++y) {
+          lo[y] = std::min(lo[y], k);
+          hi[y] = std::max(hi[y], k);
+        }
+      } else {
+        lo[k] = a;
+        hi[k] = b;
+      }
+    }
+    // monotone bounds (rows that only some paths reach)
+    for (int y = maxpy - 1; y >= 0; --y) lo[y] = std::min(lo[y], lo[y + 1]);
+    for (int y = 1; y <= maxpy; ++y) hi[y] = std::max(hi[y], hi[y - 1]);
+    slope = 0;
+    if (maxpy > 0) {
+      const double s = oct.xm ? (double)last.n / std::max(last.m, 1) : (double)first.m / first.n;
+      if (s <= 16.0) slope = (int)std::floor(s / 32.0 * 65536.0);
+    }
+  }
+  int slope;
+  void set(int tile, int S, int R, CoverGroup &g) const {
+    g.tile = tile;
+    g.rows = tile + maxpy;
+    g.sh_a = slope;
+    int64_t b = 0;
+    for (int d = 0; d <= maxpy; ++d)
+      b = std::max<int64_t>(b, (int64_t)slope * d - (int64_t)(lo[d] >> 5) * 65536);
+    g.sh_b = (int)b;
+    auto xs = [&](int y) {
+      const int d = std::max(0, y - tile + 1);
+      return std::max(0, (int)(((int64_t)d * g.sh_a - g.sh_b) >> 16));
+    };
+    int wid = 0;
+    for (int y = 0; y < g.rows; ++y)
+      wid = std::max(wid, SR + (hi[std::min(y, maxpy)] >> 5) - xs(y) + 1);
+    g.wid = wid;
+    g.wid_magic = (uint32_t)((((uint64_t)1 << 32) + wid - 1) / wid);
+    g.rows_magic = (uint32_t)((((uint64_t)1 << 32) + g.rows - 1) / g.rows);
+    // lanes of a wave on distinct banks: an odd row stride for one lane per row, else the stride
+    // with the fewest lanes per bank
+    int best = wid, worst = INT_MAX;
+    for (int r = wid; r < wid + 16 && worst > 1; ++r) {
+      int cnt[64] = {}, w = 0;
+      const int rpw = 64 / S;
+      for (int l = 0; l < 64; ++l) w = std::max(w, ++cnt[((l % rpw) * r + (l / rpw) * R) & 63]);
+      if (w < worst) {
+        worst = w;
+        best = r;
+      }
+    }
+    g.rst = best;
+    g.asz = (g.rows - 1) * g.rst + xs(g.rows - 1) + wid;
+  }
+};
+
+// Prefix tree of a piece's paths: the leaves are paths, an inner node the pixels 0..m that the
+// paths a..b-1 share.
+struct Node {
+  int a, b, m;
+  std::vector<int> kids;
+};
+
+class GroupBuilder {
+ public:
+  GroupBuilder(const Octant &o, int a, int b, int H, const CoverShape &sh)
+      : o_(o), a_(a), b_(b), H_(H), sh_(sh) {}
+
+  void build(GroupOut &out) {
+    int len = 0;
+    int nmem = 0;
+    for (int i = a_; i < b_; ++i) {
+      len = std::max(len, o_.paths[i].len);
+      nmem += o_.paths[i].nm;
+    }
+    const int rpw = 64 / sh_.S;
+    const int bands = (H_ + rpw - 1) / rpw;
+    const int SR = sh_.S * sh_.R;
+    Geometry geo(o_, o_.paths[a_], o_.paths[b_ - 1], len, SR);
+    CoverGroup &g = out.g;
+    const int avail = sh_.lds / 4 - nmem - kCoverPad;
+    // as many words as leave room for at least one round of bands, then the largest tile, its
+    // bands spread evenly over the tiles
+    int nw = -1;
+    for (int w = kCoverWords; w >= 1 && nw < 0; --w) {
+      int prev = -1;
+      for (int nt = 1; nt <= bands; ++nt) {
+        int per = (bands + nt - 1) / nt;
+        per = (per + sh_.nwb - 1) / sh_.nwb * sh_.nwb;
+        if (per == prev) continue;
+        prev = per;
+        if ((int64_t)per * rpw > 16384) continue;
+        geo.set(per * rpw, sh_.S, sh_.R, g);
+        if (g.asz < 65536 && (int64_t)(1 + w) * g.asz <= avail && (int64_t)(1 + w) * g.asz < 65536) {
+          nw = w;
+          break;
+        }
+        if (per == sh_.nwb) break;
+      }
+    }
+    if (nw < 0) return;
+    g.ntiles = (H_ + g.tile - 1) / g.tile;
+    g.mirror = o_.mir ? 1 : 0;
+    let_.resize(b_ - a_);
+    for (int i = a_; i < b_; ++i) letters(o_.paths[i], o_.paths[i].len, let_[i - a_]);
+    choose_words(nw, out);
+    g.nw = (int)words_.size();
+    out.lds_dw = (size_t)(1 + g.nw) * g.asz + kCoverPad + nmem;
+    // members: slots in path order
+    for (int i = a_; i < b_; ++i) {
+      const Path &p = o_.paths[i];
+      slot0_.push_back((int)out.mems.size());
+      out.mems.insert(out.mems.end(), o_.mems.begin() + p.m0, o_.mems.begin() + p.m0 + p.nm);
+    }
+    g.nmem = nmem;
+    pieces(out);
+    out.counts = nmem;
+    out.ok = true;
+  }
+
+ private:
+  const Octant &o_;
+  const int a_, b_, H_;
+  const CoverShape sh_;
+  std::vector<Bits> let_;
+  std::vector<int> slot0_;
+  std::vector<Word> words_;
+
+  uint32_t encode(const CoverGroup &g, int arr, int x, int y) const {
+    return (uint32_t)(arr * g.asz + y * g.rst + (x >> 5)) | ((uint32_t)(x & 31) << 16);
+  }
+
+  // The words: greedily, from the beginnings and ends of the middle path, the one that saves most
+  // steps (sampled paths, their last two thirds: what comes before is mostly shared), as long as
+  // it saves more than building its mask costs.
+  void choose_words(int nw, GroupOut &out) {
+    CoverGroup &g = out.g;
+    const int np = b_ - a_;
+    std::vector<int> smp;
+    const int ns = std::min(np, 5);
+    for (int s = 0; s < ns; ++s) smp.push_back((int)((2ll * s + 1) * np / (2 * ns)));
+    int mid = np / 2;
+    for (int i = 0; i < np; ++i)  // the longest path near the middle
+      if (std::abs(i - np / 2) <= np / 4 && o_.paths[a_ + i].len > o_.paths[a_ + mid].len) mid = i;
+    const int ml = o_.paths[a_ + mid].len;
+    std::vector<Word> cand;
+    for (int L = 1; L <= ml; L += std::max(1, L / 4)) {
+      for (int j : {0, ml - L}) {
+        Word w = sub_word(let_[mid], j, L);
+        bool seen = false;
+        for (const Word &c : cand) seen = seen || (c.L == w.L && c.b == w.b);
+        if (!seen) cand.push_back(std::move(w));
+      }
+    }
+    const int nc = (int)cand.size();
+    std::vector<std::vector<std::vector<int>>> last(ns, std::vector<std::vector<int>>(nc));
+    for (int s = 0; s < ns; ++s)
+      for (int c = 0; c < nc; ++c)
+        find_word(let_[smp[s]], o_.paths[a_ + smp[s]].len, cand[c], last[s][c]);
+    std::vector<int> sel;
+    const double scale = (double)np / ns;
+    const double ratio = 1.5 * (double)g.rows * g.wid / ((double)g.tile * sh_.S * sh_.R);
+    auto steps = [&](const std::vector<int> &ws) {
+      int64_t n = 0;
+      for (int s = 0; s < ns; ++s) {
+        const Path &p = o_.paths[a_ + smp[s]];
+        int c = p.len / 3;
+        for (int t = 0; t < p.nm; ++t) {
+          const int l = o_.mems[p.m0 + t].l;
+          while (c <= l) {
+            int end = c;
+            for (int w : ws) {
+              const int at = std::min(c, l - cand[w].L);
+              if (at < 0) continue;
+              const int j = last[s][w][at];
+              if (j >= 0) end = std::max(end, j + cand[w].L);
+            }
+            c = end + 1;
+            ++n;
+          }
+        }
+      }
+      double bc = 0;
+      for (int w : ws) {
+        int sub = 0;
+        for (int v : ws)
+          if (cand[v].L < cand[w].L) sub = std::max(sub, cand[v].L);
+        bc += sub ? (double)cand[w].L / (sub + 1) + 2 : cand[w].L + 1;
+      }
+      return n * scale + bc * ratio;
+    };
+    double cur = steps(sel);
+    for (int r = 0; r < nw; ++r) {
+      int best = -1;
+      for (int c = 0; c < nc; ++c) {
+        std::vector<int> t = sel;
+        t.push_back(c);
+        const double v = steps(t);
+        if (v < cur - 0.5) {
+          cur = v;
+          best = c;
+        }
+      }
+      if (best < 0) break;
+      sel.push_back(best);
+    }
+    // one pass of exchanging each word for a better one
+    for (size_t r = 0; r < sel.size(); ++r) {
+      std::vector<int> t = sel;
+      int best = sel[r];
+      for (int c = 0; c < nc; ++c) {
+        t[r] = c;
+        const double v = steps(t);
+        if (v < cur - 0.5) {
+          cur = v;
+          best = c;
+        }
+      }
+      sel[r] = best;
+    }
+    std::sort(sel.begin(), sel.end(), [&](int x, int y) { return cand[x].L < cand[y].L; });
+    sel.erase(std::unique(sel.begin(), sel.end()), sel.end());
+    for (int w : sel) words_.push_back(cand[w]);
+    // each mask from the image and the shorter masks
+    g.bop[0] = 0;
+    for (size_t w = 0; w < words_.size(); ++w) {
+      const Word &wd = words_[w];
+      std::vector<Word> sub(words_.begin(), words_.begin() + w);
+      std::vector<std::vector<int>> ls(w);
+      for (size_t v = 0; v < w; ++v) find_word(wd.b, wd.L, sub[v], ls[v]);
+      int c = 0;
+      while (c <= wd.L) {
+        Step s;
+        c = best_step(sub, ls, c, wd.L, s) + 1;
+        int q = 0;
+        for (int k = 0; k < s.j; ++k) q += (int)((wd.b[k >> 6] >> (k & 63)) & 1);
+        out.bops.push_back(o_.xm ? encode(g, s.arr, s.j, q) : encode(g, s.arr, q, s.j));
+      }
+      g.bop[w + 1] = (int)out.bops.size();
+    }
+    for (int w = (int)words_.size(); w < kCoverWords; ++w) g.bop[w + 1] = (int)out.bops.size();
+    out.bsteps = (int64_t)out.bops.size();
+  }
+
+  // ---- the walks of one piece ----
+  std::vector<Node> nodes_;
+  std::vector<int> lcp_;
+  std::vector<std::vector<std::pair<int64_t, std::pair<int, bool>>>> memo_;
+  int cur_path_ = -1;
+  std::vector<std::vector<int>> cur_last_;
+
+  int tree(int a, int b) {
+    Node t{a, b, 0, {}};
+    if (b - a == 1) {
+      t.m = o_.paths[a].len;
+    } else {
+      int m = INT_MAX;
+      for (int i = a; i + 1 < b; ++i) m = std::min(m, lcp_[i - a_]);
+      t.m = m;
+      int s = a;
+      for (int i = a; i + 1 < b; ++i)
+        if (lcp_[i - a_] == m) {
+          t.kids.push_back(tree(s, i + 1));
+          s = i + 1;
+        }
+      t.kids.push_back(tree(s, b));
+    }
+    nodes_.push_back(std::move(t));
+    return (int)nodes_.size() - 1;
+  }
+
+  // Least cost, in pixels, of the walks below node v from a product saved at depth s with k saves
+  // left, and whether to save at v's depth.  A save or a restore copies the product: about 6.
+  std::pair<int, bool> best_save(int v, int s, int k) {
+    const int64_t key = (int64_t)(s + 1) * 4 + k;
+    for (auto &e : memo_[v])
+      if (e.first == key) return e.second;
+    std::pair<int, bool> r(0, false);
+    const Node &t = nodes_[v];
+    if (t.kids.empty()) {
+      r.first = t.m - s + 6;
+    } else {
+      for (int u : t.kids) r.first += best_save(u, s, k).first;
+      if (k > 0 && t.m - s >= 6) {
+        int c = t.m - s + 12;
+        for (int u : t.kids) c += best_save(u, t.m, k - 1).first;
+        if (c < r.first) r = std::make_pair(c, true);
+      }
+    }
+    memo_[v].push_back({key, r});
+    return r;
+  }
+
+  void pieces(GroupOut &out) {
+    const int np = b_ - a_;
+    lcp_.assign(np, 0);
+    for (int i = 0; i + 1 < np; ++i)
+      lcp_[i] = common(let_[i], let_[i + 1],
+                       std::min(o_.paths[a_ + i].len, o_.paths[a_ + i + 1].len));
+    const int nsub = sh_.wpg / sh_.nwb;
+    int64_t total = 0;
+    auto cost = [&](int i) { return 4 + 3 * (int64_t)o_.paths[i].nm; };
+    for (int i = a_; i < b_; ++i) total += cost(i);
+    int i = a_;
+    int64_t acc = 0;
+    for (int p = 0; p < nsub; ++p) {
+      out.piece_off.push_back((int32_t)out.recs.size());
+      const int s = i;
+      while (i < b_ && (p + 1 == nsub || (acc + cost(i) / 2) * nsub < total * (p + 1))) acc += cost(i++);
+      if (i == s) continue;
+      nodes_.clear();
+      const int root = tree(s, i);
+      memo_.assign(nodes_.size(), {});
+      in_acc_ = -1;
+      emit(out, root, -1, 0, 0, 2);
+    }
+    out.piece_off.push_back((int32_t)out.recs.size());
+  }
+
+  int in_acc_ = -1;  // level of the saved product that the accumulators hold, -1 none
+
+  const std::vector<std::vector<int>> &last_of(int i) {
+    if (cur_path_ != i) {
+      cur_path_ = i;
+      cur_last_.resize(words_.size());
+      for (size_t w = 0; w < words_.size(); ++w)
+        find_word(let_[i - a_], o_.paths[i].len, words_[w], cur_last_[w]);
+    }
+    return cur_last_;
+  }
+
+  // Records for `steps` on path i; the last one carries the count.
+  void put(GroupOut &out, int i, const std::vector<Step> &steps, int level, int slot) {
+    const Path &p = o_.paths[i];
+    auto code = [&](const Step &s) {
+      const int q = p.q(s.j);
+      return o_.xm ? encode(out.g, s.arr, s.j, q) : encode(out.g, s.arr, q, s.j);
+    };
+    for (size_t t = 0; t < steps.size(); t += 2) {
+      int4 r = make_int4((int)code(steps[t]), 0, 0, 0);
+      if (t + 1 < steps.size()) {
+        r.y = (int)code(steps[t + 1]);
+        r.x |= (int)kRecTwo;
+      }
+      if (!(in_acc_ == level && level > 0)) {
+        if (!started_) r.x |= (level + 1) << kRecRestore;
+      }
+      started_ = true;
+      in_acc_ = -1;
+      if (slot >= 0 && t + 2 >= steps.size()) {
+        r.x |= (int)kRecCount;
+        r.z = slot;
+        counted_.push_back((int)out.recs.size());
+      }
+      out.recs.push_back(r);
+    }
+    out.steps += (int64_t)steps.size();
+    out.cost += 2 * (int64_t)steps.size() + (slot >= 0 ? 2 : 0);
+  }
+  bool started_ = false;
+  std::vector<int> counted_;
+
+  // Walks below node v; products covered below pixel c are saved at `level` (depth s).
+  void emit(GroupOut &out, int v, int s, int c, int level, int k) {
+    const Node &t = nodes_[v];
+    const bool leaf = t.kids.empty();
+    if (!leaf && !(level < 2 && best_save(v, std::max(s, 0), k).second)) {
+      for (int u : t.kids) emit(out, u, s, c, level, k);
+      return;
+    }
+    // counts on the shared pixels s < l <= m of the paths below
+    std::vector<std::pair<int, int>> ends;  // (l, slot)
+    for (int i = t.a; i < t.b; ++i)
+      for (int x = 0; x < o_.paths[i].nm; ++x) {
+        const int l = o_.mems[o_.paths[i].m0 + x].l;
+        if (l > s && l <= t.m) ends.push_back({l, slot0_[i - a_] + x});
+      }
+    std::sort(ends.begin(), ends.end());
+    const auto &last = last_of(t.a);
+    int cv = c;
+    std::vector<Step> st;
+    const size_t rec0 = out.recs.size();
+    started_ = false;
+    std::vector<int> outer;
+    outer.swap(counted_);
+    for (const auto &e : ends) {
+      st.clear();
+      while (cv <= e.first) {
+        Step x;
+        cv = best_step(words_, last, cv, e.first, x) + 1;
+        st.push_back(x);
+      }
+      put(out, t.a, st, level, e.second);
+    }
+    std::vector<int> mine;
+    if (!leaf) {
+      // on towards the branch, while steps are worth it
+      st.clear();
+      for (;;) {
+        if (cv > t.m) break;
+        Step x;
+        const int end = best_step(words_, last, cv, t.m, x);
+        if (end - cv < 3) break;
+        cv = end + 1;
+        st.push_back(x);
+      }
+      if (!st.empty()) put(out, t.a, st, level, -1);
+      mine.swap(counted_);
+      if (out.recs.size() > rec0) {
+        out.recs.back().x |= (level + 1) << kRecSave;
+        in_acc_ = level + 1;
+        for (int u : t.kids) emit(out, u, t.m, cv, level + 1, k - 1);
+      } else {
+        for (int u : t.kids) emit(out, u, s, c, level, k);
+      }
+    } else {
+      mine.swap(counted_);
+    }
+    for (int r : mine) out.recs[r].w = (int)out.recs.size();
+    counted_.swap(outer);
+  }
+};
+
+}  // namespace
+
+void cover_lanes(int W, int H, int *R, int *S) {
+  // words times lanes that a band walks, plus the work per record that does not depend on R
+  // (about four words' worth)
+  const int swd = (W + 31) / 32;
+  int64_t best = INT64_MAX;
+  for (int s = 1; s <= 64; s *= 2)
+    for (int r = 16; r >= 1; --r) {
+      const int nct = (swd + r * s - 1) / (r * s);
+      if (s > 1 && (s / 2) * r >= swd) continue;
+      const int bands = (H + 64 / s - 1) / (64 / s);
+      const int64_t cost = (int64_t)nct * bands * (r + 4);
+      if (cost < best) {
+        best = cost;
+        *R = r;
+        *S = s;
+      }
+    }
+}
+
+bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_want,
+                 CoverHost &out) {
+  out = CoverHost();
+  out.sh = sh;
+  const int swd = (W + 31) / 32;
+  out.nct = (swd + sh.R * sh.S - 1) / (sh.R * sh.S);
+  // the octants, then groups of about equal cost
+  Octant oct[4];
+  const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
+  auto parallel = [&](int n, int threads, auto &&f) {
+    std::atomic<int> next(0);
+    std::atomic<bool> bad(false);
+    auto work = [&]() {
+      try {
+        for (int i; (i = next.fetch_add(1)) < n;) f(i);
+      } catch (...) {
+        bad = true;
+      }
+    };
+    std::vector<std::thread> th;
+    try {
+      for (int t = 1; t < std::min({threads, n, (int)hw}); ++t) th.emplace_back(work);
+    } catch (...) {  // no more threads: the ones that run and this one do the work
+    }
+    work();
+    for (auto &t : th) t.join();
+    if (bad) throw std::bad_alloc();
+  };
+  const int64_t nv = (int64_t)(cx + 1) * (cy + 1) + (int64_t)cx * cy;
+  parallel(4, nv > 3000 ? 4 : 1, [&](int i) { build_octant(cx, cy, i < 2, i & 1, oct[i]); });
+  auto cost = [](const Path &p) { return 4 + 3 * (int64_t)p.nm; };
+  int64_t total = 0;
+  for (auto &o : oct)
+    for (auto &p : o.paths) total += cost(p);
+  struct Range {
+    int o, a, b;
+  };
+  std::vector<Range> ranges;
+  for (int i = 0; i < 4; ++i) {
+    int64_t oc = 0;
+    for (auto &p : oct[i].paths) oc += cost(p);
+    if (oct[i].paths.empty()) continue;
+    const int want = std::max<int>(1, (int)std::llround((double)groups_want * oc / total));
+    int64_t acc = 0;
+    int a = 0, mem = 0, k = 1;
+    const int np = (int)oct[i].paths.size();
+    for (int p = 0; p < np; ++p) {
+      const Path &pt = oct[i].paths[p];
+      if (p > a && (mem + pt.nm > kCoverSlots || (acc + cost(pt) / 2) * want >= oc * k)) {
+        ranges.push_back({i, a, p});
+        a = p;
+        mem = 0;
+        while ((acc + cost(pt) / 2) * want >= oc * k) ++k;
+      }
+      acc += cost(pt);
+      mem += pt.nm;
+    }
+    ranges.push_back({i, a, np});
+  }
+  const int ng = (int)ranges.size();
+  std::vector<GroupOut> go(ng);
+  std::atomic<bool> fits(true);
+  parallel(ng, std::min(8, ng / 4), [&](int i) {
+    if (!fits) return;
+    GroupBuilder b(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
+    b.build(go[i]);
+    if (!go[i].ok) fits = false;
+  });
+  if (!fits) return false;
+  size_t dw = 0;
+  for (auto &x : go) {
+    CoverGroup g = x.g;
+    g.piece0 = (int32_t)out.piece_off.size();
+    g.mem0 = (int32_t)out.mems.size();
+    const int r0 = (int)out.recs.size(), b0 = (int)out.bops.size();
+    for (int &b : g.bop) b += b0;
+    for (int32_t p : x.piece_off) out.piece_off.push_back(p + r0);
+    for (int4 r : x.recs) {
+      r.w += r0;
+      out.recs.push_back(r);
+    }
+    out.bops.insert(out.bops.end(), x.bops.begin(), x.bops.end());
+    out.mems.insert(out.mems.end(), x.mems.begin(), x.mems.end());
+    const int rpw = 64 / sh.S;
+    const int64_t bands = (H + rpw - 1) / rpw;
+    out.cost.push_back((x.cost * bands / sh.nwb + 2 * x.bsteps * g.ntiles * g.rows * g.wid / (sh.R * 64)) * out.nct);
+    out.steps += x.steps;
+    out.counts += x.counts;
+    out.bsteps += x.bsteps;
+    dw = std::max(dw, x.lds_dw);
+    out.groups.push_back(g);
+  }
+  out.recs.push_back(make_int4(0, 0, 0, 0));  // read ahead of the last record
+  out.lds_bytes = dw * 4;
+  return true;
+}
+
+bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, int cus,
+                CoverHost &out) {
+  int R = 0, S = 0;
+  cover_lanes(W, H, &R, &S);
+  if (fR) R = fR;
+  if (fS || fR) {
+    const int swd = (W + 31) / 32;
+    S = 1;
+    while (S < 64 && S * R < swd) S *= 2;
+    if (fS) S = fS;
+  }
+  const int64_t nv = (int64_t)(cx + 1) * (cy + 1) + (int64_t)cx * cy;
+  for (;; R = R / 2) {
+    for (int big = 0; big < 2; ++big) {
+      if (fL && big) break;
+      CoverShape sh;
+      sh.R = R;
+      sh.S = S;
+      sh.lds = fL ? fL : (big ? 160 : 80) * 1024;
+      sh.wpg = fW ? fW : (sh.lds > 80 * 1024 ? 16 : 8);
+      const int bands = (H + 64 / S - 1) / (64 / S);
+      for (int nwb : {2, 1}) {
+        if (nwb > bands || sh.wpg % nwb) continue;
+        sh.nwb = nwb;
+        // Work items (group, phase, tile) for about two per resident workgroup; a group builds its
+        // masks once per tile, so that with many tiles there are fewer, larger groups.
+        const int nsub = sh.wpg / nwb;
+        const int64_t paths = nv / 3 + 1;
+        const int64_t items = (int64_t)cus * (sh.lds > 80 * 1024 ? 2 : 4) / 2;
+        const int nct = ((W + 31) / 32 + R * S - 1) / (R * S);
+        const int rpw = 64 / S;
+        int per = bands;  // bands of a tile, at a guess: the widest rows of a group, three masks
+        while (per > nwb && (int64_t)(per * rpw + cy) * (R * S + 4) * 16 > sh.lds) --per;
+        const int64_t tiles = (int64_t)((bands + per - 1) / per) * nct;
+          int64_t g = std::max<int64_t>(items / tiles, 64);
+        g = std::max<int64_t>(4, std::min<int64_t>(g, paths / (6 * nsub)));
+        if (!build_cover(W, H, cx, cy, sh, (int)g, out)) continue;
+        int most = 1;
+        for (const CoverGroup &x : out.groups) most = std::max(most, x.ntiles * out.nct);
+        out.nsplit = (int)std::min<int64_t>(most, (items + out.groups.size() - 1) / out.groups.size());
+        return true;
+      }
+    }
+    if (fR || R == 1) return false;
+  }
+}
+
+bool run_cover(const CoverHost &p, const uint8_t *img, int W, int H, int phase, int64_t *counts) {
+  const int S = p.sh.S, R = p.sh.R, rpw = 64 / S, SR = S * R;
+  std::vector<uint32_t> lds(p.lds_bytes / 4 + 64);
+  for (const CoverGroup &g : p.groups) {
+    const int64_t top = (int64_t)(1 + g.nw) * g.asz + kCoverPad;
+    if (top + g.nmem > (int64_t)p.lds_bytes / 4) return false;
+    std::vector<int64_t> slot(g.nmem, 0);
+    for (int ct = 0; ct < p.nct; ++ct)
+      for (int rt = 0; rt < g.ntiles; ++rt) {
+        uint32_t junk = 12345u + ct * 7 + rt;
+        for (auto &d : lds) d = junk = junk * 1664525u + 1013904223u;
+        auto cell = [&](int y, int i) {
+          const int d = std::max(0, y - g.tile + 1);
+          return y * g.rst + std::max(0, (int)(((int64_t)d * g.sh_a - g.sh_b) >> 16)) + i;
+        };
+        for (int y = 0; y < g.rows; ++y)
+          for (int i = 0; i < g.wid; ++i) {
+            const int at = cell(y, i), e = at - y * g.rst + ct * SR;
+            uint32_t v = 0;
+            for (int b = 0; b < 32; ++b) {
+              int x = (int)((32ll * e + b) % W);
+              if (g.mirror) x = W - 1 - x;
+              v |= (uint32_t)((img[(size_t)((rt * g.tile + y) % H) * W + x] != 0) == (phase != 0)) << b;
+            }
+            if (at < 0 || at >= g.asz) return false;
+            lds[at] = v;
+          }
+        for (int a = 1; a <= g.nw; ++a)
+          for (int y = 0; y < g.rows; ++y)
+            for (int i = 0; i < g.wid; ++i) {
+              uint32_t v = ~0u;
+              for (int t = g.bop[a - 1]; t < g.bop[a]; ++t) {
+                const int64_t at = cell(y, i) + (int64_t)(p.bops[t] & 0xffff);
+                const int sh = (p.bops[t] >> 16) & 31;
+                if (at + 1 >= top) return false;
+                v &= (uint32_t)((((uint64_t)lds[at + 1] << 32) | lds[at]) >> sh);
+              }
+              lds[(size_t)a * g.asz + cell(y, i)] = v;
+            }
+        const int rows_here = std::min(g.tile, H - rt * g.tile);
+        const int nsub = p.sh.wpg / p.sh.nwb;
+        for (int pc = 0; pc < nsub; ++pc)
+          for (int row = 0; row < g.tile; ++row)
+            for (int strip = 0; strip < S; ++strip) {
+              std::vector<uint32_t> init(R), A(R), sv[2] = {std::vector<uint32_t>(R), std::vector<uint32_t>(R)};
+              for (int i = 0; i < R; ++i) {
+                const int64_t w0 = ct * SR + strip * R + i;
+                for (int b = 0; b < 32; ++b)
+                  if (row < rows_here && 32 * w0 + b < W) init[i] |= 1u << b;
+              }
+              for (int r = p.piece_off[g.piece0 + pc]; r < p.piece_off[g.piece0 + pc + 1]; ++r) {
+                const int4 q = p.recs[r];
+                const int rs = (q.x >> kRecRestore) & 3, sa = (q.x >> kRecSave) & 3;
+                if (rs) A = rs == 1 ? init : sv[rs - 2];
+                for (int t = 0; t < (q.x & (int)kRecTwo ? 2 : 1); ++t) {
+                  const int c = t ? q.y : q.x;
+                  const int64_t at = (int64_t)row * g.rst + strip * R + (c & 0xffff);
+                  const int sh = (c >> 16) & 31;
+                  if (at + R >= top) return false;
+                  for (int i = 0; i < R; ++i)
+                    A[i] &= (uint32_t)((((uint64_t)lds[at + i + 1] << 32) | lds[at + i]) >> sh);
+                }
+                if (sa) sv[sa - 1] = A;
+                if (q.x & (int)kRecCount) {
+                  int64_t n = 0;
+                  for (int i = 0; i < R; ++i) n += __builtin_popcount(A[i]);
+                  if (q.z < 0 || q.z >= g.nmem) return false;
+                  slot[q.z] += n;
+                  if (q.w <= r) return false;
+                  if (n == 0) r = q.w - 1;  // the kernel tests a whole wave's count
+                }
+              }
+            }
+      }
+    for (int t = 0; t < g.nmem; ++t) counts[p.mems[g.mem0 + t].idx] += slot[t];
+  }
+  (void)rpw;
+  return true;
+}
+
+}  // namespace lpf
+
+// Host run of the launch plan of lpf_full (include/lpf.h).
+extern "C" lpf_status lpf_cover_counts(const uint8_t *img, int W, int H, int cx, int cy, int phase,
+                                       int R, int S, int waves, int lds_bytes, uint32_t *counts) {
+  auto pow2 = [](int v, int hi) { return v == 0 || (v >= 1 && v <= hi && (v & (v - 1)) == 0); };
+  if (!img || !counts || W < 1 || H < 1 || W > 4096 || H > 4096 || cx < 0 || cy < 0 || cx >= W ||
+      cy >= H || phase < 0 || phase > 1 || !pow2(R, 16) || !pow2(S, 64) || waves < 0 ||
+      waves > 16 || lds_bytes < 0 || lds_bytes > 160 * 1024)
+    return LPF_E_INVAL;
+  try {
+    lpf::CoverHost p;
+    if (!lpf::plan_cover(W, H, cx, cy, R, S, waves, lds_bytes, 256, p)) return LPF_E_UNSUPPORTED;
+    std::vector<int64_t> n((size_t)lpf_num_vectors(cx, cy), -1);
+    std::vector<int> seen(n.size(), 0);
+    for (const lpf::MemDesc &m : p.mems) {
+      n[m.idx] = 0;
+      ++seen[m.idx];
+    }
+    for (int t : seen)
+      if (t != 1) return LPF_E_INVAL;
+    if (!lpf::run_cover(p, img, W, H, phase, n.data())) return LPF_E_INVAL;
+    for (size_t i = 0; i < n.size(); ++i) counts[i] = (uint32_t)n[i];
+  } catch (const std::exception &) {
+    return LPF_E_NOMEM;
+  }
+  return LPF_OK;
+}
