@@ -13,7 +13,7 @@
 namespace lpf {
 
 // Masks of a group held in LDS beside its image rows, and members (count slots) of a group.
-constexpr int kCoverWords = 3;
+constexpr int kCoverWords = 4;
 constexpr int kCoverSlots = 1024;
 // Dwords behind a group's arrays that a walk or a build may read without using (the second dword
 // of a funnel shift and the words of lanes past the row).
@@ -34,6 +34,7 @@ struct CoverGroup {
   int32_t piece0;        // its pieces' records: piece_off[piece0 + p] .. piece_off[piece0 + p + 1]
   int32_t mem0, nmem;    // its members (count slot = member - mem0)
   int32_t tile, ntiles;  // start rows per tile (whole bands), tiles
+  int32_t nwb;           // waves that share a piece, each over every nwb-th band of a tile
   int32_t rows;          // rows staged: tile + the largest row offset of a path
   int32_t rst, wid;      // dwords between rows, dwords staged per row
   int32_t asz;           // dwords of one array (array 0 the image, 1.. the word masks)
@@ -52,11 +53,11 @@ struct CoverImg {
   const uint32_t *bops;  // offset in dwords | bit shift << 16
   const MemDesc *mems;
   // nsplit workgroups share a group and phase, each over every nsplit-th tile
-  int W, H, cx, cy, R, S, nct, nwb, nsplit, nv, layout;
+  int W, H, cx, cy, R, S, nct, nsplit, nv, layout;
 };
 
-// Shape of a plan: R words per lane, S lanes per row, wpg waves per workgroup of which nwb take
-// the bands of a tile in turn (wpg / nwb pieces per group), LDS bytes per workgroup.
+// Shape of a plan: R words per lane, S lanes per row, wpg waves per workgroup, of which up to nwb
+// share a piece (wpg / nwb pieces per group), LDS bytes per workgroup.
 struct CoverShape {
   int R = 0, S = 0, wpg = 0, nwb = 0, lds = 0;
 };
@@ -71,16 +72,18 @@ struct CoverHost {
   std::vector<int4> recs;
   std::vector<uint32_t> bops;
   std::vector<MemDesc> mems;
-  std::vector<int64_t> cost;  // per group, for the launch order
+  // work items {group, split} of one phase in launch order: most work first (cost), neighbours
+  // in another order than the groups'
+  std::vector<int2> items;
+  std::vector<int64_t> cost;
   int64_t steps = 0, counts = 0, bsteps = 0;
 };
 
 // Lane layout for an image: R in 1..16 and S a power of two.
 void cover_lanes(int W, int H, int *R, int *S);
-// Builds the plan; false when some group's rows do not fit sh.lds.  May throw std::bad_alloc.
-bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_want,
-                 CoverHost &out);
-// The same with the shape chosen here: fR, fS, fW, fL fix a field (0: free).
+// The plan for an image size and cutoff on a device of `cus` compute units; fR, fS, fW, fL fix the
+// shape's R, S, waves and LDS bytes (0: chosen here).  False when the rows do not fit in LDS.  May
+// throw std::bad_alloc.
 bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, int cus,
                 CoverHost &out);
 // Counts of a byte image by running the plan on the host, word for word as the kernel does;
@@ -91,9 +94,9 @@ bool run_cover(const CoverHost &p, const uint8_t *img, int W, int H, int phase, 
 // out[2][H][ceil(W / 32)], plain and mirrored.
 hipError_t launch_start_sets(const uint64_t *sample, int W, int H, uint32_t *out,
                              hipStream_t stream);
-// One workgroup per (group, phase of phase_mask); order: the groups, most work first.  sample:
-// the start pixels of launch_start_sets, or null (every pixel).
-hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, int ngroups, const int32_t *order,
+// One workgroup per item and phase of phase_mask.  sample: the start pixels of
+// launch_start_sets, or null (every pixel).
+hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, const int2 *items, int n_items,
                         size_t lds_bytes, unsigned phase_mask, const uint64_t *bits,
                         const uint32_t *sample, uint32_t *out, hipStream_t stream);
 // Many images: items {image, group, phase, split}, one workgroup each; image i's packed rows at

@@ -23,15 +23,23 @@ namespace lpf {
 
 namespace {
 
-// Bits s .. s + 31 (mod W) of a packed row, 0 <= s < W.  Bits past W in the row's last word are
-// never used.
+// A plan's tables other than the records are read through the constant address space: their
+// wave-uniform reads become scalar loads (plain loads went through the vector memory path).
+#define LPF_CONST __attribute__((address_space(4)))
+template <class T>
+__device__ __forceinline__ const LPF_CONST T *constant(const T *p) {
+  return (const LPF_CONST T *)p;
+}
+
+// The 32 pixels from pixel s on of a packed row, periodic (0 <= s < W).  Bits past W in the row's
+// last word are never used.  Without branches for rows of at least a word.
 __device__ __forceinline__ uint32_t periodic32(const uint32_t *__restrict__ row, int W, int s) {
-  const int q = s >> 5, sh = s & 31;
-  const int n = W - s;  // bits left in the row
-  if (n >= 32) return __builtin_amdgcn_alignbit(sh ? row[q + 1] : 0u, row[q], sh);
   if (W >= 32) {
-    const uint32_t hi = sh + n > 32 ? row[q + 1] : 0u;
-    return (__builtin_amdgcn_alignbit(hi, row[q], sh) & ((1u << n) - 1u)) | (row[0] << n);
+    const int q = s >> 5, n = W - s;  // n: pixels left in the row
+    // (the dword after the row's last pixel: any value, and never read past the packed row)
+    const uint32_t lo = row[q], hi = row[min(q + 1, (W - 1) >> 5)];
+    const uint32_t v = __builtin_amdgcn_alignbit(hi, lo, s & 31);
+    return n < 32 ? (v & ((1u << n) - 1u)) | (row[0] << n) : v;
   }
   uint32_t v = 0;
   for (int b = 0, x = s; b < 32; ++b) {
@@ -41,29 +49,24 @@ __device__ __forceinline__ uint32_t periodic32(const uint32_t *__restrict__ row,
   return v;
 }
 
-// Word e of a row extended periodically; mirror: of the row reversed (bit j is pixel W - 1 - j).
-__device__ __forceinline__ uint32_t ext_word(const uint32_t *__restrict__ row, int W, int e,
-                                             bool mirror) {
+// First pixel of word e of a row extended periodically (bit j of the word is pixel (32 e + j) mod
+// W), or, mirrored, of the 32 pixels that the word holds in reverse (bit j is pixel W - 1 - (32 e
+// + j) mod W).
+__device__ __forceinline__ int word_start(int W, int e, bool mirror) {
   int s = 32 * e;
   if (s >= W) s -= W;
-  if (s >= W) s %= W;  // rows narrower than the window only
-  if (!mirror) return periodic32(row, W, s);
-  // pixels W - 1 - s down to W - 32 - s
-  int t = W - 32 - s;
-  if (t < 0) t += W;
-  if (t < 0) t = (t % W + W) % W;
-  return __builtin_bitreverse32(periodic32(row, W, t));
+  if (s >= W) s %= W;  // windows of more than twice the row only
+  if (mirror) {
+    s = W - 32 - s;
+    if (s < 0) s += W;
+    if (s < 0) s = (s % W + W) % W;
+  }
+  return s;
 }
 
-// Sum over the wave of v, valid in lane 63 (every lane active).
-__device__ __forceinline__ uint32_t wave_sum63(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);   // quad_perm 2,3,0,1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false);  // row_mirror
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
+// Byte address of a word of the workgroup's LDS.
+__device__ __forceinline__ uint32_t lds_address(const uint32_t *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t *)p;
 }
 
 // The start pixels of a lane's words: full words below the row's last one, which keeps the bits
@@ -84,82 +87,207 @@ __device__ __forceinline__ void start_pixels(uint32_t (&A)[R], int w0, int W, bo
   }
 }
 
-// The records [r, r1) for the lane's R words at `base` (its row's first word in array 0).
-template <int R, bool SAMPLE>
-__device__ __forceinline__ void walk(const int4 *__restrict__ recs, int r, int r1,
-                                     const uint32_t *__restrict__ base, int w0, int W, bool row_ok,
-                                     bool full, const uint32_t *__restrict__ srow,
-                                     uint32_t *__restrict__ slots, int lane) {
-  uint32_t A[R], S1[R], S2[R];
-#pragma unroll
-  for (int i = 0; i < R; ++i) A[i] = S1[i] = S2[i] = 0u;
-  int4 rec = recs[r];
-  while (r < r1) {
-    const int4 nxt = recs[r + 1];
-    const uint32_t x = (uint32_t)rec.x;
-    const uint32_t *p0 = base + (x & 0xffffu);
-    uint32_t d0[R + 1];
-#pragma unroll
-    for (int c = 0; c <= R; ++c) d0[c] = p0[c];
-    const int restore = (x >> kRecRestore) & 3;
-    if (restore) {
-      if (restore == 1) {
-        if (full) {
-#pragma unroll
-          for (int i = 0; i < R; ++i) A[i] = 0xffffffffu;
-        } else {
-          start_pixels<R, SAMPLE>(A, w0, W, row_ok, srow);
-        }
-      } else if (restore == 2) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) A[i] = S1[i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < R; ++i) A[i] = S2[i];
-      }
-    }
-    const uint32_t sh0 = (x >> 16) & 31u;
-    if (x & kRecTwo) {
-      const uint32_t y = (uint32_t)rec.y;
-      const uint32_t *p1 = base + (y & 0xffffu);
-      const uint32_t sh1 = (y >> 16) & 31u;
-      uint32_t d1[R + 1];
-#pragma unroll
-      for (int c = 0; c <= R; ++c) d1[c] = p1[c];
-#pragma unroll
-      for (int i = 0; i < R; ++i) {
-        const uint32_t t0 = __builtin_amdgcn_alignbit(d0[i + 1], d0[i], sh0);
-        const uint32_t t1 = __builtin_amdgcn_alignbit(d1[i + 1], d1[i], sh1);
-        A[i] = __builtin_amdgcn_bitop3_b32(A[i], t0, t1, 0x80);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < R; ++i) A[i] &= __builtin_amdgcn_alignbit(d0[i + 1], d0[i], sh0);
-    }
-    const int save = (x >> kRecSave) & 3;
-    if (save == 1) {
-#pragma unroll
-      for (int i = 0; i < R; ++i) S1[i] = A[i];
-    } else if (save == 2) {
-#pragma unroll
-      for (int i = 0; i < R; ++i) S2[i] = A[i];
-    }
-    ++r;
-    if (x & kRecCount) {
-      uint32_t n = 0;
-#pragma unroll
-      for (int i = 0; i < R; ++i) n += __popc(A[i]);
-      n = wave_sum63(n);
-      const uint32_t all = __builtin_amdgcn_readlane(n, 63);
-      if (all == 0u) {
-        r = rec.w;
-        rec = recs[r];
-        continue;
-      }
-      if (lane == 63) atomicAdd(slots + rec.z, n);
-    }
-    rec = nxt;
+// The records [r0, r1) for the lane's R words of one row: the walk of one piece over one band.
+//
+// Written in assembly: the running product and the two saved ones stay in one set of registers
+// each (the compiler copied all R of them wherever a record's branches joined, 16 to 80 moves
+// beside a record's 50 useful operations), and the next record's LDS reads are issued as soon as
+// the current product is formed, so that they return under its popcounts and wave sum.
+//
+// (Records read 16 at a time into a vector register, one batch ahead, and taken out with readlane
+// were 10 % slower than scalar loads one record ahead.)
+//
+//   M  start pixels of the lane's words (what a restore of level 1 gives)
+//   base   LDS byte address of the row's first word in array 0
+//   slots  LDS byte address of the group's count slots
+//
+// Registers: K = 4, 8 or 16 words, from v28 on: M, A (product), S1, S2 (saved), D0 (K + 1 dwords of
+// step 0), T, D1 (step 1), N.  s72..75 the record, s76..79 the next one, s80.. the current record's
+// fields once the next one has moved up; s88, s89: byte offsets of the record after it and of the
+// end.  LDS reads are issued only for records of the piece; records are read up to two past it.  A
+// wave sum of at most 64 lanes x 512 start pixels; all 64 lanes are active throughout.
+#define LPF_WALK_ASM                                                                              \
+  ".set cvA, 28 + %[K]\n"                                                                         \
+  ".set cvS1, cvA + %[K]\n"                                                                       \
+  ".set cvS2, cvS1 + %[K]\n"                                                                      \
+  ".set cvD0, cvS2 + %[K]\n"                                                                      \
+  ".set cvT, cvD0 + %[K] + 1\n"                                                                   \
+  ".set cvD1, cvT + 1\n"                                                                          \
+  ".set cvN, cvD1 + %[K] + 1\n"                                                                   \
+  "s_lshl_b32 s88, %[r0], 4\n"                                                                    \
+  "s_lshl_b32 s89, %[r1], 4\n"                                                                    \
+  "Lcv_load%=:\n" /* record at s88 and the one after it, nothing in flight for them yet */        \
+  "s_add_u32 s90, s88, 16\n"                                                                      \
+  "s_load_dwordx4 s[72:75], %[recs], s88\n"                                                       \
+  "s_load_dwordx4 s[76:79], %[recs], s90\n"                                                       \
+  "s_waitcnt lgkmcnt(0)\n"                                                                        \
+  LPF_WALK_READ("0")                                                                              \
+  "s_waitcnt lgkmcnt(0)\n"                                                                        \
+  "Lcv_top%=:\n" /* the record's dwords are in D0, D1 */                                          \
+  "s_bfe_u32 s84, s72, 0x20016\n"                                                                 \
+  "s_cmp_eq_u32 s84, 0\n"                                                                         \
+  "s_cbranch_scc1 Lcv_and%=\n"                                                                    \
+  "s_cmp_eq_u32 s84, 1\n"                                                                         \
+  "s_cbranch_scc0 Lcv_r2%=\n"                                                                     \
+  LPF_WALK_MOV("cvA", "28")                                                                       \
+  "s_branch Lcv_and%=\n"                                                                          \
+  "Lcv_r2%=:\n"                                                                                   \
+  "s_cmp_eq_u32 s84, 2\n"                                                                         \
+  "s_cbranch_scc0 Lcv_r3%=\n"                                                                     \
+  LPF_WALK_MOV("cvA", "cvS1")                                                                     \
+  "s_branch Lcv_and%=\n"                                                                          \
+  "Lcv_r3%=:\n"                                                                                   \
+  LPF_WALK_MOV("cvA", "cvS2")                                                                     \
+  "Lcv_and%=:\n"                                                                                  \
+  "s_lshr_b32 s85, s72, 16\n" /* a funnel shift takes the low five bits */                        \
+  "s_bitcmp1_b32 s72, 21\n"                                                                       \
+  "s_cbranch_scc0 Lcv_one%=\n"                                                                    \
+  "s_lshr_b32 s86, s73, 16\n"                                                                     \
+  ".set cvi, 0\n"                                                                                 \
+  ".rept %[R]\n"                                                                                  \
+  "v_alignbit_b32 v[cvD0+cvi], v[cvD0+cvi+1], v[cvD0+cvi], s85\n"                                 \
+  "v_alignbit_b32 v[cvD1+cvi], v[cvD1+cvi+1], v[cvD1+cvi], s86\n"                                 \
+  "v_bitop3_b32 v[cvA+cvi], v[cvA+cvi], v[cvD0+cvi], v[cvD1+cvi] bitop3:0x80\n"                   \
+  ".set cvi, cvi+1\n"                                                                             \
+  ".endr\n"                                                                                       \
+  "s_branch Lcv_next%=\n"                                                                         \
+  "Lcv_one%=:\n"                                                                                  \
+  ".set cvi, 0\n"                                                                                 \
+  ".rept %[R]\n"                                                                                  \
+  "v_alignbit_b32 v[cvD0+cvi], v[cvD0+cvi+1], v[cvD0+cvi], s85\n"                                 \
+  "v_and_b32 v[cvA+cvi], v[cvA+cvi], v[cvD0+cvi]\n"                                               \
+  ".set cvi, cvi+1\n"                                                                             \
+  ".endr\n"                                                                                       \
+  "Lcv_next%=:\n" /* the next record moves up; its reads, and the record after it */              \
+  "s_mov_b32 s80, s72\n"                                                                          \
+  "s_mov_b64 s[82:83], s[74:75]\n"                                                                \
+  "s_add_u32 s88, s88, 16\n"                                                                      \
+  "s_cmp_ge_u32 s88, s89\n"                                                                       \
+  "s_cbranch_scc1 Lcv_issued%=\n"                                                                 \
+  "s_mov_b64 s[72:73], s[76:77]\n"                                                                \
+  "s_mov_b64 s[74:75], s[78:79]\n"                                                                \
+  "s_add_u32 s90, s88, 16\n"                                                                      \
+  "s_load_dwordx4 s[76:79], %[recs], s90\n"                                                       \
+  LPF_WALK_READ("1")                                                                              \
+  "Lcv_issued%=:\n"                                                                               \
+  "s_bfe_u32 s84, s80, 0x20018\n"                                                                 \
+  "s_cmp_eq_u32 s84, 0\n"                                                                         \
+  "s_cbranch_scc1 Lcv_count%=\n"                                                                  \
+  "s_cmp_eq_u32 s84, 1\n"                                                                         \
+  "s_cbranch_scc0 Lcv_s2%=\n"                                                                     \
+  LPF_WALK_MOV("cvS1", "cvA")                                                                     \
+  "s_branch Lcv_count%=\n"                                                                        \
+  "Lcv_s2%=:\n"                                                                                   \
+  LPF_WALK_MOV("cvS2", "cvA")                                                                     \
+  "Lcv_count%=:\n"                                                                                \
+  "s_bitcmp1_b32 s80, 26\n"                                                                       \
+  "s_cbranch_scc0 Lcv_wait%=\n"                                                                   \
+  "v_bcnt_u32_b32 v[cvN], v[cvA], 0\n"                                                            \
+  ".set cvi, 1\n"                                                                                 \
+  ".rept %[R]-1\n"                                                                                \
+  "v_bcnt_u32_b32 v[cvN], v[cvA+cvi], v[cvN]\n"                                                   \
+  ".set cvi, cvi+1\n"                                                                             \
+  ".endr\n"                                                                                       \
+  "s_lshl_b32 s82, s82, 2\n"                                                                      \
+  "s_add_u32 s82, s82, %[slots]\n"                                                                \
+  "v_cmp_ne_u32_e32 vcc, 0, v[cvN]\n"                                                             \
+  "s_cbranch_vccz Lcv_zero%=\n"                                                                   \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"         \
+  "s_nop 1\n"                                                                                     \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"         \
+  "s_nop 1\n"                                                                                     \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_half_mirror row_mask:0xf bank_mask:0xf\n"             \
+  "s_nop 1\n"                                                                                     \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_mirror row_mask:0xf bank_mask:0xf\n"                  \
+  "s_nop 1\n"                                                                                     \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_bcast:15 row_mask:0xa bank_mask:0xf\n"                \
+  "s_nop 1\n"                                                                                     \
+  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_bcast:31 row_mask:0xc bank_mask:0xf\n"                \
+  "s_waitcnt lgkmcnt(0)\n" /* the reads, before the add: it need not be waited for */             \
+  "v_mov_b32 v[cvT], s82\n"                                                                       \
+  "s_brev_b64 exec, 1\n" /* lane 63 holds the sum */                                              \
+  "ds_add_u32 v[cvT], v[cvN]\n"                                                                   \
+  "s_mov_b64 exec, -1\n"                                                                          \
+  "s_cmp_lt_u32 s88, s89\n"                                                                       \
+  "s_cbranch_scc1 Lcv_top%=\n"                                                                    \
+  "s_branch Lcv_end%=\n"                                                                          \
+  "Lcv_zero%=:\n" /* nothing that extends this path counts here: on at the jump target */         \
+  "s_waitcnt lgkmcnt(0)\n"                                                                        \
+  "s_lshl_b32 s83, s83, 4\n"                                                                      \
+  "s_cmp_eq_u32 s83, s88\n" /* the record already under way */                                    \
+  "s_mov_b32 s88, s83\n"                                                                          \
+  "s_cbranch_scc1 Lcv_more%=\n"                                                                   \
+  "s_cmp_lt_u32 s88, s89\n"                                                                       \
+  "s_cbranch_scc1 Lcv_load%=\n"                                                                   \
+  "s_branch Lcv_end%=\n"                                                                          \
+  "Lcv_wait%=:\n"                                                                                 \
+  "s_waitcnt lgkmcnt(0)\n"                                                                        \
+  "Lcv_more%=:\n"                                                                                 \
+  "s_cmp_lt_u32 s88, s89\n"                                                                       \
+  "s_cbranch_scc1 Lcv_top%=\n"                                                                    \
+  "Lcv_end%=:\n"                                                                                  \
+  "s_waitcnt lgkmcnt(0)\n"
+// LDS reads of the record in s72, s73 into D0 and, for two steps, D1 (R + 1 dwords each).
+#define LPF_WALK_READ(id)                                                                         \
+  "s_and_b32 s84, s72, 0xffff\n"                                                                  \
+  "v_lshl_add_u32 v[cvT], s84, 2, %[base]\n"                                                      \
+  LPF_WALK_READ1("cvD0")                                                                          \
+  "s_bitcmp1_b32 s72, 21\n"                                                                       \
+  "s_cbranch_scc0 Lcv_read" id "_%=\n"                                                            \
+  "s_and_b32 s84, s73, 0xffff\n"                                                                  \
+  "v_lshl_add_u32 v[cvT], s84, 2, %[base]\n"                                                      \
+  LPF_WALK_READ1("cvD1")                                                                          \
+  "Lcv_read" id "_%=:\n"
+#define LPF_WALK_READ1(d)                                                                         \
+  ".set cvi, 0\n"                                                                                 \
+  ".rept (%[R]+1)/2\n"                                                                            \
+  "ds_read2_b32 v[" d "+cvi:" d "+cvi+1], v[cvT] offset0:cvi offset1:cvi+1\n"                     \
+  ".set cvi, cvi+2\n"                                                                             \
+  ".endr\n"                                                                                       \
+  ".if ((%[R]+1) & 1)\n"                                                                          \
+  "ds_read_b32 v[" d "+%[R]], v[cvT] offset:4*%[R]\n"                                             \
+  ".endif\n"
+#define LPF_WALK_MOV(dst, src)                                                                    \
+  ".set cvi, 0\n"                                                                                 \
+  ".rept %[R]\n"                                                                                  \
+  "v_mov_b32 v[" dst "+cvi], v[" src "+cvi]\n"                                                    \
+  ".set cvi, cvi+1\n"                                                                             \
+  ".endr\n"
+
+typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
+typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Words8 __attribute__((ext_vector_type(8)));
+typedef uint32_t Words16 __attribute__((ext_vector_type(16)));
+
+template <int R>
+__device__ __forceinline__ void walk(const int4 *recs, int r0, int r1, uint32_t base,
+                                     const uint32_t (&st)[R], uint32_t slots) {
+#if __HIP_DEVICE_COMPILE__
+#define LPF_WALK(n, WordsK, m, a, s1, s2, d0, x0, d1, x1)                                         \
+  {                                                                                               \
+    WordsK M = 0u, A, S1, S2, D0, D1;                                                             \
+    Words2 X0, X1;                                                                                \
+    for (int i = 0; i < R; ++i) M[i] = st[i];                                                     \
+    asm volatile(LPF_WALK_ASM                                                                     \
+                 : "=&{" a "}"(A), "=&{" s1 "}"(S1), "=&{" s2 "}"(S2), "=&{" d0 "}"(D0),          \
+                   "=&{" x0 "}"(X0), "=&{" d1 "}"(D1), "=&{" x1 "}"(X1)                           \
+                 : "{" m "}"(M), [K] "i"(n), [R] "i"(R), [recs] "s"(recs), [r0] "s"(r0),          \
+                   [r1] "s"(r1), [base] "v"(base), [slots] "s"(slots)                             \
+                 : "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s82", "s83",   \
+                   "s84", "s85", "s86", "s88", "s89", "s90", "vcc", "scc", "memory");             \
   }
+  if constexpr (R <= 4) {
+    LPF_WALK(4, Words4, "v[28:31]", "v[32:35]", "v[36:39]", "v[40:43]", "v[44:47]", "v[48:49]",
+             "v[50:53]", "v[54:55]")
+  } else if constexpr (R <= 8) {
+    LPF_WALK(8, Words8, "v[28:35]", "v[36:43]", "v[44:51]", "v[52:59]", "v[60:67]", "v[68:69]",
+             "v[70:77]", "v[78:79]")
+  } else {
+    LPF_WALK(16, Words16, "v[28:43]", "v[44:59]", "v[60:75]", "v[76:91]", "v[92:107]",
+             "v[108:109]", "v[110:125]", "v[126:127]")
+  }
+#undef LPF_WALK
+#endif
 }
 
 // Count of vector `idx` = (dx, dy) for phase slot p, in the image's output layout (the GRID
@@ -190,9 +318,11 @@ __device__ __forceinline__ void put_count(const CoverImg &I, uint32_t *__restric
 // One mask of C consecutive dwords per lane and item: item i is chunk i / rows of row i mod rows,
 // so that a wave's lanes read consecutive rows (distinct banks), C + 1 dwords for C funnel
 // shifts.  The last chunk of a row is moved back to end with the row (its overlap is written
-// twice with the same values).
+// twice with the same values).  (Four steps at a time, their reads under way together, with the
+// steps of a mask padded to a multiple of four, were slower: 1 024 x 1 024, cutoff 512: 5.9
+// against 5.6 ms.)
 template <int C>
-__device__ __forceinline__ void build_mask(const CoverGroup &g, const uint32_t *__restrict__ bops,
+__device__ __forceinline__ void build_mask(const LPF_CONST CoverGroup &g, const LPF_CONST uint32_t *bops,
                                            int b0, int b1, uint32_t *__restrict__ lds,
                                            uint32_t *__restrict__ dst) {
   const int chunks = (g.wid + C - 1) / C;
@@ -228,9 +358,10 @@ __device__ __forceinline__ void cover_group(const CoverImg &I, int gi, int phase
                                             const uint32_t *__restrict__ sample,
                                             uint32_t *__restrict__ out,
                                             uint32_t *__restrict__ lds) {
-  const CoverGroup &g = I.groups[gi];
+  const LPF_CONST CoverGroup &g = constant(I.groups)[gi];
+  const LPF_CONST int32_t *piece_off = constant(I.piece_off) + g.piece0;
+  const LPF_CONST uint32_t *bops = constant(I.bops);
   const int ntiles = g.ntiles * I.nct;
-  if (split >= ntiles) return;
   const int tid = threadIdx.x, nt = blockDim.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -244,14 +375,16 @@ __device__ __forceinline__ void cover_group(const CoverImg &I, int gi, int phase
   const uint32_t *rows = reinterpret_cast<const uint32_t *>(bits);
   const uint32_t flip = phase ? 0u : 0xffffffffu;
   const bool mirror = g.mirror != 0;
-  const int piece = wave / I.nwb, bw = wave - piece * I.nwb;
-  const int r0 = I.piece_off[g.piece0 + piece], r1 = I.piece_off[g.piece0 + piece + 1];
+  const int nwb = g.nwb;
+  const int piece = wave / nwb, bw = wave - piece * nwb;
+  const int r0 = piece_off[piece], r1 = piece_off[piece + 1];
   const int cells = g.rows * g.wid;
   for (int tile = split; tile < ntiles; tile += I.nsplit) {
     const int ct = tile / g.ntiles;
     const int e0 = ct * SR;
     const int Y0 = (tile - ct * g.ntiles) * g.tile;
     __syncthreads();  // every wave is done with the previous tile
+    // rows Y0 .. Y0 + rows - 1 (mod H): a word per lane, so that a wave reads along the rows
     for (int i = tid; i < cells; i += nt) {
       const int y = (int)__umulhi((uint32_t)i, g.wid_magic);
       const int d = max(0, y - g.tile + 1);
@@ -259,24 +392,24 @@ __device__ __forceinline__ void cover_group(const CoverImg &I, int gi, int phase
       int r = Y0 + y;
       if (r >= I.H) r -= I.H;
       if (r >= I.H) r %= I.H;
-      lds[y * g.rst + e] = flip ^ ext_word(rows + (size_t)r * wpr, I.W, e0 + e, mirror);
+      const uint32_t v = periodic32(rows + (size_t)r * wpr, I.W, word_start(I.W, e0 + e, mirror));
+      lds[y * g.rst + e] = flip ^ (mirror ? __builtin_bitreverse32(v) : v);
     }
     for (int a = 1; a <= g.nw; ++a) {
       __syncthreads();
-      build_mask<(R >= 7 ? 8 : R + 1)>(g, I.bops, g.bop[a - 1], g.bop[a], lds, lds + a * g.asz);
+      build_mask<(R >= 7 ? 8 : R + 1)>(g, bops, g.bop[a - 1], g.bop[a], lds, lds + a * g.asz);
     }
     __syncthreads();
     const int rows_here = min(g.tile, I.H - Y0);
     if (r0 < r1) {
-      for (int row0 = bw * rpw; row0 < rows_here; row0 += I.nwb * rpw) {
+      for (int row0 = bw * rpw; row0 < rows_here; row0 += nwb * rpw) {
         const int row = row0 + r_in;
-        const int w0 = e0 + strip * R;
         const bool row_ok = row < rows_here;
-        const bool full = !SAMPLE && __all(row_ok && 32 * (w0 + R) <= I.W);
         const uint32_t *srow =
             SAMPLE ? sample + (size_t)((mirror ? I.H : 0) + Y0 + (row_ok ? row : 0)) * swd : nullptr;
-        walk<R, SAMPLE>(I.recs, r0, r1, lds + row * g.rst + strip * R, w0, I.W, row_ok, full, srow,
-                        slots, lane);
+        uint32_t st[R];
+        start_pixels<R, SAMPLE>(st, e0 + strip * R, I.W, row_ok, srow);
+        walk<R>(I.recs, r0, r1, lds_address(lds + row * g.rst + strip * R), st, lds_address(slots));
       }
     }
   }
@@ -319,21 +452,28 @@ __global__ void k_start_sets(const uint32_t *__restrict__ src, int W, int H, int
   const bool mirror = r >= H;
   const uint32_t *row = src + (size_t)(mirror ? r - H : r) * wpr;
   const int left = W - 32 * e;
-  out[i] = ext_word(row, W, e, mirror) & (left >= 32 ? 0xffffffffu : (1u << left) - 1u);
+  uint32_t v = periodic32(row, W, word_start(W, e, mirror));
+  if (mirror) v = __builtin_bitreverse32(v);
+  out[i] = v & (left >= 32 ? 0xffffffffu : (1u << left) - 1u);
 }
 
-// Workgroup b: phase b mod nph, then split, of the group at place b / (nph nsplit) of the order.
+// Workgroups go to the eight XCDs in turn.  The phases of an image differ in work (a zero count
+// ends a walk), so both phases of an item go to the same XCD: eight items of one phase, then the
+// same eight of the other.  (With the phase in the lowest bit, one phase was counted on
+// the even XCDs and the other on the odd ones: 512^2, cutoff 128: 0.27 against 0.15 ms.)
 template <int R, bool SAMPLE>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
-k_cover(CoverImg I, const int32_t *__restrict__ order, unsigned phase_mask,
+k_cover(CoverImg I, const int2 *__restrict__ items, int n_items, unsigned phase_mask,
         const uint64_t *__restrict__ bits, const uint32_t *__restrict__ sample,
         uint32_t *__restrict__ out) {
   extern __shared__ uint32_t lds[];
-  const int both = phase_mask == 3u ? 1 : 0;
-  const int p = blockIdx.x & both, b = blockIdx.x >> both;
-  const int gi = b / I.nsplit;
-  cover_group<R, SAMPLE>(I, order[gi], both ? p : (int)(phase_mask >> 1), p, b - gi * I.nsplit,
-                         bits, sample, out, lds);
+  const bool both = phase_mask == 3u;
+  const int b = blockIdx.x;
+  const int p = both ? (b >> 3) & 1 : 0;
+  const int i = both ? (b >> 4) * 8 + (b & 7) : b;
+  if (i >= n_items) return;
+  const int2 it = items[i];
+  cover_group<R, SAMPLE>(I, it.x, both ? p : (int)(phase_mask >> 1), p, it.y, bits, sample, out, lds);
 }
 
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
@@ -356,7 +496,7 @@ k_cover_batch(const CoverImg *__restrict__ imgs, const int64_t *__restrict__ bit
   }
 }
 
-using CoverKernel = void (*)(CoverImg, const int32_t *, unsigned, const uint64_t *,
+using CoverKernel = void (*)(CoverImg, const int2 *, int, unsigned, const uint64_t *,
                              const uint32_t *, uint32_t *);
 CoverKernel cover_kernel(int R, bool sample) {
   switch (R) {
@@ -371,12 +511,11 @@ CoverKernel cover_kernel(int R, bool sample) {
 
 }  // namespace
 
-hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, int ngroups, const int32_t *order,
+hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, const int2 *items, int n_items,
                         size_t lds_bytes, unsigned phase_mask, const uint64_t *bits,
                         const uint32_t *sample, uint32_t *out, hipStream_t stream) {
   const CoverKernel k = cover_kernel(I.R, sample != nullptr);
-  if (!k || I.R != sh.R || I.S != sh.S || sh.wpg < 1 || sh.wpg > 16 || I.nwb < 1 ||
-      sh.wpg % I.nwb || 64 % I.S)
+  if (!k || I.R != sh.R || I.S != sh.S || sh.wpg < 1 || sh.wpg > 16 || 64 % I.S)
     return hipErrorInvalidValue;
   const int nph = phase_mask == 3u ? 2 : 1;
   if (I.nsplit > 1) {
@@ -387,7 +526,8 @@ hipError_t launch_cover(const CoverImg &I, const CoverShape &sh, int ngroups, co
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k, dim3(ngroups * nph * I.nsplit), dim3(64 * sh.wpg), lds_bytes, stream, I, order,
+  const int blocks = nph == 2 ? (n_items + 7) / 8 * 16 : n_items;
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * sh.wpg), lds_bytes, stream, I, items, n_items,
                      phase_mask, bits, sample, out);
   return hipGetLastError();
 }

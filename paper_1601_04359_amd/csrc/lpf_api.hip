@@ -101,10 +101,10 @@ struct CoverPlan {
   bool ok = false;
   CoverImg img{};
   CoverShape sh{};
-  int ngroups = 0;
   size_t lds_bytes = 0;
-  int32_t *order = nullptr;   // device: groups, most work first
-  std::vector<int64_t> cost;  // host, per group
+  int2 *items = nullptr;  // device: work items of one phase, most work first
+  std::vector<int2> host_items;
+  std::vector<int64_t> cost;  // per item
   void *mem = nullptr;        // one device allocation behind every table
 };
 
@@ -509,19 +509,15 @@ lpf_status get_cover_plan(lpf_ctx c, int W, int H, int cx, int cy, const FixedSh
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->dev);
     if (nv <= kCoverVectors && plan_cover(W, H, cx, cy, f.R, f.S, f.wpg, f.lds, cus, h)) {
-      std::vector<int32_t> order(h.groups.size());
-      for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
-      std::stable_sort(order.begin(), order.end(),
-                       [&](int a, int b) { return h.cost[a] > h.cost[b]; });
       // one allocation, each table at a multiple of 256 bytes
       const void *src[6] = {h.groups.data(), h.piece_off.data(), h.recs.data(),
-                            h.bops.data(),   h.mems.data(),      order.data()};
+                            h.bops.data(),   h.mems.data(),      h.items.data()};
       const size_t len[6] = {h.groups.size() * sizeof(CoverGroup),
                              h.piece_off.size() * sizeof(int32_t),
                              h.recs.size() * sizeof(int4),
                              h.bops.size() * sizeof(uint32_t),
                              h.mems.size() * sizeof(MemDesc),
-                             order.size() * sizeof(int32_t)};
+                             h.items.size() * sizeof(int2)};
       size_t off[7] = {};
       for (int i = 0; i < 6; ++i) off[i + 1] = off[i] + (len[i] + 255) / 256 * 256;
       std::vector<char> all(off[6]);
@@ -538,10 +534,10 @@ lpf_status get_cover_plan(lpf_ctx c, int W, int H, int cx, int cy, const FixedSh
       p.img = CoverImg{(const CoverGroup *)(m + off[0]), (const int32_t *)(m + off[1]),
                        (const int4 *)(m + off[2]),       (const uint32_t *)(m + off[3]),
                        (const MemDesc *)(m + off[4]),    W, H, cx, cy, h.sh.R, h.sh.S, h.nct,
-                       h.sh.nwb, h.nsplit, (int)nv, 0};
-      p.order = (int32_t *)(m + off[5]);
+                       h.nsplit, (int)nv, 0};
+      p.items = (int2 *)(m + off[5]);
+      p.host_items = std::move(h.items);
       p.sh = h.sh;
-      p.ngroups = (int)h.groups.size();
       p.lds_bytes = h.lds_bytes;
       p.cost = std::move(h.cost);
       p.ok = true;
@@ -1347,7 +1343,7 @@ lpf_status full_impl(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int 
   }
   CoverImg I = cp->img;
   I.layout = out_layout;
-  if ((e = launch_cover(I, cp->sh, cp->ngroups, cp->order, cp->lds_bytes, phase_mask, bits, starts,
+  if ((e = launch_cover(I, cp->sh, cp->items, (int)cp->host_items.size(), cp->lds_bytes, phase_mask, bits, starts,
                         counts, s)) != hipSuccess)
     return hip_fail(e, "lpf_full: kernel");
   return LPF_OK;
@@ -2326,11 +2322,10 @@ lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images
       imgs[i].layout = out_layout;
       b->split = b->split || imgs[i].nsplit > 1;
       auto &list = items[p->sh.wpg];
-      for (int g = 0; g < p->ngroups; ++g)
+      for (size_t k = 0; k < p->host_items.size(); ++k)
         for (int ph = 0; ph < 2; ++ph)
-          for (int sp = 0; sp < p->img.nsplit; ++sp)
-            if (phase_mask >> ph & 1u)
-              list.push_back({p->cost[g] / p->img.nsplit, make_int4(i, g, ph, sp)});
+          if (phase_mask >> ph & 1u)
+            list.push_back({p->cost[k], make_int4(i, p->host_items[k].x, ph, p->host_items[k].y)});
       lds[p->sh.wpg] = std::max(lds[p->sh.wpg], p->lds_bytes);
     }
     hipError_t e = hipSuccess;
@@ -2346,8 +2341,14 @@ lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images
     for (auto kv = items.rbegin(); kv != items.rend(); ++kv) {  // the largest groups first
       std::stable_sort(kv->second.begin(), kv->second.end(),
                        [](const auto &x, const auto &y) { return x.first > y.first; });
+      // Workgroups go to the eight XCDs in turn: items of about equal cost change places (48 at
+      // a time, a fixed pattern coprime to 8), so that no XCD gets one phase or one split only.
       std::vector<int4> list;
-      for (auto &x : kv->second) list.push_back(x.second);
+      const size_t n = kv->second.size();
+      for (size_t i = 0; i < n; ++i) {
+        const size_t w = i / 48 * 48;
+        list.push_back(kv->second[n - w < 48 ? i : w + (i - w) * 29 % 48].second);
+      }
       b->launches.emplace_back();
       BatchPlan::Launch &l = b->launches.back();
       l.n_items = (int)list.size();

@@ -167,22 +167,31 @@ Word sub_word(const Bits &b, int j, int L) {
   }
   return w;
 }
-// last[j] = the last pixel <= j where the word starts on the path, -1 when none (j = 0..len).
-void find_word(const Bits &b, int len, const Word &w, std::vector<int> &last) {
-  last.assign(len + 1, -1);
+// last[j] = the last pixel in [from, j] where the word starts on the path, -1 when none, for
+// j = from .. len.
+void find_word(const Bits &b, int from, int len, const Word &w, int16_t *last) {
+  const uint64_t m0 = w.L < 64 ? (1ull << w.L) - 1 : ~0ull, w0 = w.b[0] & m0;
+  const int top = len - w.L;
   int la = -1;
-  const uint64_t m0 = w.L < 64 ? (1ull << w.L) - 1 : ~0ull;
-  for (int j = 0; j <= len; ++j) {
-    if (j + w.L <= len && ((bits64(b, j) ^ w.b[0]) & m0) == 0) {
-      bool ok = true;
-      for (int k = 64; ok && k < w.L; k += 64) {
-        const uint64_t m = w.L - k < 64 ? (1ull << (w.L - k)) - 1 : ~0ull;
-        ok = ((bits64(b, j + k) ^ w.b[k >> 6]) & m) == 0;
+  int j = from;
+  while (j <= top) {
+    // the 64 steps from pixel j on, and how many pixels they serve whole
+    const uint64_t lo = bits64(b, j), hi = j + 64 <= len ? bits64(b, j + 64) : 0;
+    const int n = std::min(64, top - j + 1);
+    for (int k = 0; k < n; ++k, ++j) {
+      const uint64_t v = k ? (lo >> k) | (hi << (64 - k)) : lo;
+      if (((v & m0) ^ w0) == 0) {
+        bool ok = true;
+        for (int t = 64; ok && t < w.L; t += 64) {
+          const uint64_t m = w.L - t < 64 ? (1ull << (w.L - t)) - 1 : ~0ull;
+          ok = ((bits64(b, j + t) ^ w.b[t >> 6]) & m) == 0;
+        }
+        if (ok) la = j;
       }
-      if (ok) la = j;
+      last[j] = (int16_t)la;
     }
-    last[j] = la;
   }
+  for (; j <= len; ++j) last[j] = (int16_t)la;
 }
 
 // The furthest step from a path covered below pixel c that does not pass pixel `to`: array (0 the
@@ -190,8 +199,8 @@ void find_word(const Bits &b, int len, const Word &w, std::vector<int> &last) {
 struct Step {
   int arr, j;
 };
-int best_step(const std::vector<Word> &words, const std::vector<std::vector<int>> &last, int c,
-              int to, Step &s) {
+int best_step(const std::vector<Word> &words, const std::vector<std::vector<int16_t>> &last,
+              int c, int to, Step &s) {
   int end = c;
   s = Step{0, c};
   for (size_t w = 0; w < words.size(); ++w) {
@@ -207,7 +216,6 @@ int best_step(const std::vector<Word> &words, const std::vector<std::vector<int>
 }
 
 struct GroupOut {
-  bool ok = false;
   CoverGroup g{};
   size_t lds_dw = 0;
   std::vector<int32_t> piece_off;  // within recs
@@ -298,44 +306,72 @@ class GroupBuilder {
   GroupBuilder(const Octant &o, int a, int b, int H, const CoverShape &sh)
       : o_(o), a_(a), b_(b), H_(H), sh_(sh) {}
 
-  void build(GroupOut &out) {
-    int len = 0;
-    int nmem = 0;
+  // Tile and LDS layout of the group; false when its rows do not fit.
+  bool fit(GroupOut &out) {
+    int len = 0, nmem = 0;
     for (int i = a_; i < b_; ++i) {
       len = std::max(len, o_.paths[i].len);
       nmem += o_.paths[i].nm;
     }
     const int rpw = 64 / sh_.S;
     const int bands = (H_ + rpw - 1) / rpw;
-    const int SR = sh_.S * sh_.R;
-    Geometry geo(o_, o_.paths[a_], o_.paths[b_ - 1], len, SR);
+    Geometry geo(o_, o_.paths[a_], o_.paths[b_ - 1], len, sh_.S * sh_.R);
     CoverGroup &g = out.g;
+    g.nmem = nmem;
     const int avail = sh_.lds / 4 - nmem - kCoverPad;
-    // as many words as leave room for at least one round of bands, then the largest tile, its
-    // bands spread evenly over the tiles
-    int nw = -1;
-    for (int w = kCoverWords; w >= 1 && nw < 0; --w) {
-      int prev = -1;
-      for (int nt = 1; nt <= bands; ++nt) {
-        int per = (bands + nt - 1) / nt;
-        per = (per + sh_.nwb - 1) / sh_.nwb * sh_.nwb;
-        if (per == prev) continue;
-        prev = per;
-        if ((int64_t)per * rpw > 16384) continue;
-        geo.set(per * rpw, sh_.S, sh_.R, g);
-        if (g.asz < 65536 && (int64_t)(1 + w) * g.asz <= avail && (int64_t)(1 + w) * g.asz < 65536) {
-          nw = w;
-          break;
+    // Words, waves per chain and tile by estimated work: steps per member by the number of words
+    // (measured means over the groups of cutoffs 128 to 512; longer paths take more), a count per
+    // member, and the masks' steps over the staged rows.
+    const double len_f = std::min(2.0, std::max(0.5, len / 256.0));
+    static const double kSteps[] = {20, 8, 4.6, 3.4, 3.0};
+    double best = 1e300;
+    CoverGroup pick = g;
+    for (int nwb = sh_.nwb; nwb >= 1; nwb /= 2) {
+      if (nwb > bands) continue;
+      // sixteen pieces share too little (1 024 x 1 024, cutoff 512: 6.9 against 5.6 ms)
+      if (nwb == 1 && sh_.wpg > 8 && best < 1e300) continue;
+      for (int w = kCoverWords; w >= 1; --w) {
+        int prev = -1;
+        for (int nt = 1; nt <= bands; ++nt) {
+          int per = (bands + nt - 1) / nt;
+          per = (per + nwb - 1) / nwb * nwb;
+          if (per == prev) continue;
+          prev = per;
+          // (rows alone beyond the budget: no need for the exact window)
+          if ((int64_t)per * rpw <= 16384 &&
+              (int64_t)(1 + w) * (per * rpw + geo.maxpy) * sh_.S * sh_.R <= avail) {
+            CoverGroup t = g;
+            geo.set(per * rpw, sh_.S, sh_.R, t);
+            if ((int64_t)(1 + w) * t.asz <= std::min(avail, 65535)) {
+              const double SR = sh_.S * sh_.R;
+              const double walk = nmem * (kSteps[w] * len_f * (1.5 * sh_.R + 6) + sh_.R + 12) *
+                                  (1.0 + 0.04 * (sh_.wpg / nwb - 1));
+              const double build = (6 + 5 * w) * 2.5 * sh_.R * t.rows * t.wid / (t.tile * SR);
+              if (walk + build < best) {
+                best = walk + build;
+                pick = t;
+                pick.nwb = nwb;
+                nw_ = w;
+              }
+              break;
+            }
+          }
+          if (per == nwb) break;
         }
-        if (per == sh_.nwb) break;
       }
     }
-    if (nw < 0) return;
+    g = pick;
+    return best < 1e300;
+  }
+
+  void build(GroupOut &out) {
+    CoverGroup &g = out.g;
+    const int nmem = g.nmem;
     g.ntiles = (H_ + g.tile - 1) / g.tile;
     g.mirror = o_.mir ? 1 : 0;
     let_.resize(b_ - a_);
     for (int i = a_; i < b_; ++i) letters(o_.paths[i], o_.paths[i].len, let_[i - a_]);
-    choose_words(nw, out);
+    choose_words(nw_, out);
     g.nw = (int)words_.size();
     out.lds_dw = (size_t)(1 + g.nw) * g.asz + kCoverPad + nmem;
     // members: slots in path order
@@ -344,16 +380,15 @@ class GroupBuilder {
       slot0_.push_back((int)out.mems.size());
       out.mems.insert(out.mems.end(), o_.mems.begin() + p.m0, o_.mems.begin() + p.m0 + p.nm);
     }
-    g.nmem = nmem;
     pieces(out);
     out.counts = nmem;
-    out.ok = true;
   }
 
  private:
   const Octant &o_;
   const int a_, b_, H_;
   const CoverShape sh_;
+  int nw_ = 0;
   std::vector<Bits> let_;
   std::vector<int> slot0_;
   std::vector<Word> words_;
@@ -376,7 +411,7 @@ class GroupBuilder {
       if (std::abs(i - np / 2) <= np / 4 && o_.paths[a_ + i].len > o_.paths[a_ + mid].len) mid = i;
     const int ml = o_.paths[a_ + mid].len;
     std::vector<Word> cand;
-    for (int L = 1; L <= ml; L += std::max(1, L / 4)) {
+    for (int L = 1; L <= ml; L += std::max(1, L / 3)) {
       for (int j : {0, ml - L}) {
         Word w = sub_word(let_[mid], j, L);
         bool seen = false;
@@ -385,71 +420,78 @@ class GroupBuilder {
       }
     }
     const int nc = (int)cand.size();
-    std::vector<std::vector<std::vector<int>>> last(ns, std::vector<std::vector<int>>(nc));
-    for (int s = 0; s < ns; ++s)
+    // occurrences of every candidate on every sample
+    std::vector<std::vector<int16_t>> last(ns);
+    std::vector<int> width(ns);
+    for (int s = 0; s < ns; ++s) {
+      const int len = o_.paths[a_ + smp[s]].len;
+      width[s] = len + 1;
+      last[s].resize((size_t)nc * width[s]);
       for (int c = 0; c < nc; ++c)
-        find_word(let_[smp[s]], o_.paths[a_ + smp[s]].len, cand[c], last[s][c]);
-    std::vector<int> sel;
+        find_word(let_[smp[s]], 0, len, cand[c], &last[s][(size_t)c * width[s]]);
+    }
     const double scale = (double)np / ns;
     const double ratio = 1.5 * (double)g.rows * g.wid / ((double)g.tile * sh_.S * sh_.R);
-    auto steps = [&](const std::vector<int> &ws) {
+    std::vector<int> sel;
+    // cost of the words sel[0..k), given up once it passes `most`
+    auto steps = [&](const int *ws, int k, double most) {
+      double bc = 0;
+      for (int x = 0; x < k; ++x) {
+        int sub = 0;
+        const int L = cand[ws[x]].L;
+        for (int y = 0; y < k; ++y)
+          if (cand[ws[y]].L < L) sub = std::max(sub, cand[ws[y]].L);
+        bc += sub ? (double)L / (sub + 1) + 2 : L + 1;
+      }
+      bc *= ratio;
       int64_t n = 0;
-      for (int s = 0; s < ns; ++s) {
+      for (int s = 0; s < ns && n * scale + bc < most; ++s) {
         const Path &p = o_.paths[a_ + smp[s]];
+        const int16_t *la = last[s].data();
         int c = p.len / 3;
         for (int t = 0; t < p.nm; ++t) {
           const int l = o_.mems[p.m0 + t].l;
           while (c <= l) {
             int end = c;
-            for (int w : ws) {
-              const int at = std::min(c, l - cand[w].L);
+            for (int x = 0; x < k; ++x) {
+              const int L = cand[ws[x]].L, at = std::min(c, l - L);
               if (at < 0) continue;
-              const int j = last[s][w][at];
-              if (j >= 0) end = std::max(end, j + cand[w].L);
+              const int j = la[(size_t)ws[x] * width[s] + at];
+              if (j >= 0) end = std::max(end, j + L);
             }
             c = end + 1;
             ++n;
           }
         }
       }
-      double bc = 0;
-      for (int w : ws) {
-        int sub = 0;
-        for (int v : ws)
-          if (cand[v].L < cand[w].L) sub = std::max(sub, cand[v].L);
-        bc += sub ? (double)cand[w].L / (sub + 1) + 2 : cand[w].L + 1;
-      }
-      return n * scale + bc * ratio;
+      return n * scale + bc;
     };
-    double cur = steps(sel);
-    for (int r = 0; r < nw; ++r) {
+    int ws[kCoverWords] = {};
+    double cur = steps(ws, 0, 1e300);
+    auto better = [&](int at, int k) {  // the best candidate for word `at` of k; -1 when none helps
       int best = -1;
       for (int c = 0; c < nc; ++c) {
-        std::vector<int> t = sel;
-        t.push_back(c);
-        const double v = steps(t);
+        ws[at] = c;
+        const double v = steps(ws, k, cur - 0.5);
         if (v < cur - 0.5) {
           cur = v;
           best = c;
         }
       }
+      return best;
+    };
+    int k = 0;
+    while (k < nw) {
+      const int best = better(k, k + 1);
       if (best < 0) break;
-      sel.push_back(best);
+      ws[k++] = best;
     }
-    // one pass of exchanging each word for a better one
-    for (size_t r = 0; r < sel.size(); ++r) {
-      std::vector<int> t = sel;
-      int best = sel[r];
-      for (int c = 0; c < nc; ++c) {
-        t[r] = c;
-        const double v = steps(t);
-        if (v < cur - 0.5) {
-          cur = v;
-          best = c;
-        }
-      }
-      sel[r] = best;
+    // the first word was chosen alone: once more, given the others
+    if (k > 1) {
+      const int old = ws[0], best = better(0, k);
+      ws[0] = best < 0 ? old : best;
     }
+    sel.assign(ws, ws + k);
     std::sort(sel.begin(), sel.end(), [&](int x, int y) { return cand[x].L < cand[y].L; });
     sel.erase(std::unique(sel.begin(), sel.end()), sel.end());
     for (int w : sel) words_.push_back(cand[w]);
@@ -458,8 +500,8 @@ class GroupBuilder {
     for (size_t w = 0; w < words_.size(); ++w) {
       const Word &wd = words_[w];
       std::vector<Word> sub(words_.begin(), words_.begin() + w);
-      std::vector<std::vector<int>> ls(w);
-      for (size_t v = 0; v < w; ++v) find_word(wd.b, wd.L, sub[v], ls[v]);
+      std::vector<std::vector<int16_t>> ls(w, std::vector<int16_t>(wd.L + 1));
+      for (size_t v = 0; v < w; ++v) find_word(wd.b, 0, wd.L, sub[v], ls[v].data());
       int c = 0;
       while (c <= wd.L) {
         Step s;
@@ -478,8 +520,7 @@ class GroupBuilder {
   std::vector<Node> nodes_;
   std::vector<int> lcp_;
   std::vector<std::vector<std::pair<int64_t, std::pair<int, bool>>>> memo_;
-  int cur_path_ = -1;
-  std::vector<std::vector<int>> cur_last_;
+  std::vector<std::vector<int16_t>> cur_last_;
 
   int tree(int a, int b) {
     Node t{a, b, 0, {}};
@@ -523,40 +564,57 @@ class GroupBuilder {
     return r;
   }
 
+  // The pieces: about equal work for each wave.  The work of a path shows only once its records
+  // are there (what it shares with its neighbours is walked once), so the group is cut by members
+  // first and cut again by the work that each path's records took.
   void pieces(GroupOut &out) {
     const int np = b_ - a_;
     lcp_.assign(np, 0);
     for (int i = 0; i + 1 < np; ++i)
       lcp_[i] = common(let_[i], let_[i + 1],
                        std::min(o_.paths[a_ + i].len, o_.paths[a_ + i + 1].len));
-    const int nsub = sh_.wpg / sh_.nwb;
-    int64_t total = 0;
-    auto cost = [&](int i) { return 4 + 3 * (int64_t)o_.paths[i].nm; };
-    for (int i = a_; i < b_; ++i) total += cost(i);
-    int i = a_;
-    int64_t acc = 0;
-    for (int p = 0; p < nsub; ++p) {
+    const int nsub = sh_.wpg / out.g.nwb;
+    work_.resize(np);
+    for (int i = 0; i < np; ++i) work_[i] = 4 + 3 * o_.paths[a_ + i].nm;
+    for (int pass = 0; pass < (nsub > 1 ? 2 : 1); ++pass) {
+      const std::vector<int> w = work_;
+      int64_t total = 0;
+      for (int x : w) total += x;
+      std::fill(work_.begin(), work_.end(), 0);
+      out.recs.clear();
+      out.piece_off.clear();
+      out.steps = 0;
+      int i = 0;
+      int64_t acc = 0;
+      for (int p = 0; p < nsub; ++p) {
+        out.piece_off.push_back((int32_t)out.recs.size());
+        const int s = i;
+        while (i < np && (p + 1 == nsub || (acc + w[i] / 2) * nsub < total * (p + 1))) acc += w[i++];
+        if (i == s) continue;
+        nodes_.clear();
+        const int root = tree(a_ + s, a_ + i);
+        memo_.assign(nodes_.size(), {});
+        in_acc_ = -1;
+        emit(out, root, -1, 0, 0, 2);
+      }
       out.piece_off.push_back((int32_t)out.recs.size());
-      const int s = i;
-      while (i < b_ && (p + 1 == nsub || (acc + cost(i) / 2) * nsub < total * (p + 1))) acc += cost(i++);
-      if (i == s) continue;
-      nodes_.clear();
-      const int root = tree(s, i);
-      memo_.assign(nodes_.size(), {});
-      in_acc_ = -1;
-      emit(out, root, -1, 0, 0, 2);
     }
-    out.piece_off.push_back((int32_t)out.recs.size());
+    out.cost = 0;
+    for (int x : work_) out.cost += x;
   }
+  std::vector<int> work_;  // vector instructions of each path's records
 
   int in_acc_ = -1;  // level of the saved product that the accumulators hold, -1 none
 
-  const std::vector<std::vector<int>> &last_of(int i) {
-    if (cur_path_ != i) {
-      cur_path_ = i;
-      cur_last_.resize(words_.size());
-      for (size_t w = 0; w < words_.size(); ++w)
-        find_word(let_[i - a_], o_.paths[i].len, words_[w], cur_last_[w]);
+  // Occurrences of the words on path i for a walk that has covered the pixels below c: an
+  // occurrence that ends before c is of no use.
+  const std::vector<std::vector<int16_t>> &last_of(int i, int c) {
+    const int len = o_.paths[i].len;
+    cur_last_.resize(words_.size());
+    for (size_t w = 0; w < words_.size(); ++w) {
+      if ((int)cur_last_[w].size() <= len) cur_last_[w].resize(len + 1);
+      const int from = std::max(0, c - words_[w].L);
+      if (from <= len) find_word(let_[i - a_], from, len, words_[w], cur_last_[w].data());
     }
     return cur_last_;
   }
@@ -587,7 +645,7 @@ class GroupBuilder {
       out.recs.push_back(r);
     }
     out.steps += (int64_t)steps.size();
-    out.cost += 2 * (int64_t)steps.size() + (slot >= 0 ? 2 : 0);
+    work_[i - a_] += (int)(steps.size() * (3 * sh_.R / 2 + 6)) + (slot >= 0 ? sh_.R + 12 : 0);
   }
   bool started_ = false;
   std::vector<int> counted_;
@@ -608,7 +666,7 @@ class GroupBuilder {
         if (l > s && l <= t.m) ends.push_back({l, slot0_[i - a_] + x});
       }
     std::sort(ends.begin(), ends.end());
-    const auto &last = last_of(t.a);
+    const auto &last = last_of(t.a, c);
     int cv = c;
     std::vector<Step> st;
     const size_t rec0 = out.recs.size();
@@ -674,36 +732,39 @@ void cover_lanes(int W, int H, int *R, int *S) {
     }
 }
 
-bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_want,
-                 CoverHost &out) {
+namespace {
+
+// f(0), ..., f(n - 1) on up to `threads` threads (this one among them).
+template <class F>
+void parallel(int n, int threads, F &&f) {
+  std::atomic<int> next(0);
+  std::atomic<bool> bad(false);
+  auto work = [&]() {
+    try {
+      for (int i; (i = next.fetch_add(1)) < n;) f(i);
+    } catch (...) {
+      bad = true;
+    }
+  };
+  const int hw = std::max(1, (int)std::thread::hardware_concurrency());
+  std::vector<std::thread> th;
+  try {
+    for (int t = 1; t < std::min({threads, n, hw}); ++t) th.emplace_back(work);
+  } catch (...) {  // no more threads: the ones that run and this one do the work
+  }
+  work();
+  for (auto &t : th) t.join();
+  if (bad) throw std::bad_alloc();
+}
+
+// The plan for given octants and shape; false when some group's rows do not fit sh.lds.
+bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape &sh,
+                 int groups_want, CoverHost &out, std::vector<int64_t> &tile_cost) {
   out = CoverHost();
   out.sh = sh;
   const int swd = (W + 31) / 32;
   out.nct = (swd + sh.R * sh.S - 1) / (sh.R * sh.S);
-  // the octants, then groups of about equal cost
-  Octant oct[4];
-  const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-  auto parallel = [&](int n, int threads, auto &&f) {
-    std::atomic<int> next(0);
-    std::atomic<bool> bad(false);
-    auto work = [&]() {
-      try {
-        for (int i; (i = next.fetch_add(1)) < n;) f(i);
-      } catch (...) {
-        bad = true;
-      }
-    };
-    std::vector<std::thread> th;
-    try {
-      for (int t = 1; t < std::min({threads, n, (int)hw}); ++t) th.emplace_back(work);
-    } catch (...) {  // no more threads: the ones that run and this one do the work
-    }
-    work();
-    for (auto &t : th) t.join();
-    if (bad) throw std::bad_alloc();
-  };
-  const int64_t nv = (int64_t)(cx + 1) * (cy + 1) + (int64_t)cx * cy;
-  parallel(4, nv > 3000 ? 4 : 1, [&](int i) { build_octant(cx, cy, i < 2, i & 1, oct[i]); });
+  // groups of about equal cost
   auto cost = [](const Path &p) { return 4 + 3 * (int64_t)p.nm; };
   int64_t total = 0;
   for (auto &o : oct)
@@ -716,7 +777,12 @@ bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_
     int64_t oc = 0;
     for (auto &p : oct[i].paths) oc += cost(p);
     if (oct[i].paths.empty()) continue;
-    const int want = std::max<int>(1, (int)std::llround((double)groups_want * oc / total));
+    // (groups full of members would leave remnants between them)
+    int64_t om = 0;
+    for (auto &p : oct[i].paths) om += p.nm;
+    const int want = (int)std::max<int64_t>(
+        std::max<int64_t>(1, std::llround((double)groups_want * oc / total)),
+        (om * 5 / 4 + kCoverSlots - 1) / kCoverSlots);
     int64_t acc = 0;
     int a = 0, mem = 0, k = 1;
     const int np = (int)oct[i].paths.size();
@@ -735,15 +801,15 @@ bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_
   }
   const int ng = (int)ranges.size();
   std::vector<GroupOut> go(ng);
-  std::atomic<bool> fits(true);
-  parallel(ng, std::min(8, ng / 4), [&](int i) {
-    if (!fits) return;
-    GroupBuilder b(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
-    b.build(go[i]);
-    if (!go[i].ok) fits = false;
-  });
-  if (!fits) return false;
+  std::vector<GroupBuilder> gb;
+  gb.reserve(ng);
+  for (int i = 0; i < ng; ++i) {
+    gb.emplace_back(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
+    if (!gb[i].fit(go[i])) return false;
+  }
+  parallel(ng, std::min(8, ng / 4), [&](int i) { gb[i].build(go[i]); });
   size_t dw = 0;
+  tile_cost.clear();
   for (auto &x : go) {
     CoverGroup g = x.g;
     g.piece0 = (int32_t)out.piece_off.size();
@@ -757,19 +823,22 @@ bool build_cover(int W, int H, int cx, int cy, const CoverShape &sh, int groups_
     }
     out.bops.insert(out.bops.end(), x.bops.begin(), x.bops.end());
     out.mems.insert(out.mems.end(), x.mems.begin(), x.mems.end());
-    const int rpw = 64 / sh.S;
-    const int64_t bands = (H + rpw - 1) / rpw;
-    out.cost.push_back((x.cost * bands / sh.nwb + 2 * x.bsteps * g.ntiles * g.rows * g.wid / (sh.R * 64)) * out.nct);
+    // vector instructions of a tile: its masks (8 dwords a lane, about 40 instructions a step with
+    // the waits between them), its rows, the walks of its bands
+    const int bands = g.tile / (64 / sh.S);
+    tile_cost.push_back(x.cost * bands + (x.bsteps * 5 + 60) * g.rows * g.wid / 64);
     out.steps += x.steps;
     out.counts += x.counts;
     out.bsteps += x.bsteps;
     dw = std::max(dw, x.lds_dw);
     out.groups.push_back(g);
   }
-  out.recs.push_back(make_int4(0, 0, 0, 0));  // read ahead of the last record
+  out.recs.resize(out.recs.size() + 48, make_int4(0, 0, 0, 0));  // read ahead of the last record
   out.lds_bytes = dw * 4;
   return true;
 }
+
+}  // namespace
 
 bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, int cus,
                 CoverHost &out) {
@@ -783,6 +852,8 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
     if (fS) S = fS;
   }
   const int64_t nv = (int64_t)(cx + 1) * (cy + 1) + (int64_t)cx * cy;
+  std::vector<Octant> oct(4);
+  parallel(4, nv > 3000 ? 4 : 1, [&](int i) { build_octant(cx, cy, i < 2, i & 1, oct[i]); });
   for (;; R = R / 2) {
     for (int big = 0; big < 2; ++big) {
       if (fL && big) break;
@@ -791,28 +862,46 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
       sh.S = S;
       sh.lds = fL ? fL : (big ? 160 : 80) * 1024;
       sh.wpg = fW ? fW : (sh.lds > 80 * 1024 ? 16 : 8);
-      const int bands = (H + 64 / S - 1) / (64 / S);
-      for (int nwb : {2, 1}) {
-        if (nwb > bands || sh.wpg % nwb) continue;
-        sh.nwb = nwb;
-        // Work items (group, phase, tile) for about two per resident workgroup; a group builds its
-        // masks once per tile, so that with many tiles there are fewer, larger groups.
-        const int nsub = sh.wpg / nwb;
-        const int64_t paths = nv / 3 + 1;
-        const int64_t items = (int64_t)cus * (sh.lds > 80 * 1024 ? 2 : 4) / 2;
-        const int nct = ((W + 31) / 32 + R * S - 1) / (R * S);
-        const int rpw = 64 / S;
-        int per = bands;  // bands of a tile, at a guess: the widest rows of a group, three masks
-        while (per > nwb && (int64_t)(per * rpw + cy) * (R * S + 4) * 16 > sh.lds) --per;
-        const int64_t tiles = (int64_t)((bands + per - 1) / per) * nct;
-          int64_t g = std::max<int64_t>(items / tiles, 64);
-        g = std::max<int64_t>(4, std::min<int64_t>(g, paths / (6 * nsub)));
-        if (!build_cover(W, H, cx, cy, sh, (int)g, out)) continue;
-        int most = 1;
-        for (const CoverGroup &x : out.groups) most = std::max(most, x.ntiles * out.nct);
-        out.nsplit = (int)std::min<int64_t>(most, (items + out.groups.size() - 1) / out.groups.size());
-        return true;
+      sh.nwb = sh.wpg % 2 ? 1 : 2;
+      // Groups: one item (group, phase, tile) per resident workgroup and phase, at least 64 groups
+      // (512 x 512, cutoff 128, one tile per item: 64 groups 0.20 ms, 128 0.144, 160 0.141, 256
+      // 0.167: fewer groups have wider slopes and poorer words, more build more masks), fewer
+      // when a piece would get less than about three paths (128 x 128, cutoff 32: 12.3 against
+      // 13.5 us with six).
+      const int nsub = sh.wpg / sh.nwb;
+      const int64_t paths = nv / 3 + 1;
+      const int64_t slots = (int64_t)cus * (sh.lds > 80 * 1024 ? 1 : 2);
+      const int nct = ((W + 31) / 32 + R * S - 1) / (R * S);
+      const int rpw = 64 / S;
+      const int bands = (H + rpw - 1) / rpw;
+      int per = bands;  // bands of a tile, at a guess: the widest rows of a group, three masks
+      while (per > 2 && (int64_t)(per * rpw + cy) * (R * S + 4) * 16 > sh.lds) --per;
+      const int64_t tiles = (int64_t)((bands + per - 1) / per) * nct;
+      int64_t g = std::max<int64_t>(slots / tiles, 64);
+      g = std::max<int64_t>(4, std::min<int64_t>(g, paths / (3 * nsub)));
+      std::vector<int64_t> tile_cost;
+      if (!build_cover(oct, W, H, sh, (int)g, out, tile_cost)) continue;
+      int64_t most = 1;
+      for (const CoverGroup &x : out.groups) most = std::max<int64_t>(most, x.ntiles * out.nct);
+      // up to eight items per CU and phase, so that the last ones are short (1 024 x 1 024, cutoff
+      // 512: 5.6 ms against 6.1 with two)
+      const int64_t items = 8 * (int64_t)cus;
+      const int64_t want = std::min(most, std::max<int64_t>(1, items / (int64_t)out.groups.size()));
+      const int64_t each = (most + want - 1) / want;
+      out.nsplit = (int)((most + each - 1) / each);
+      std::vector<std::pair<int64_t, int2>> list;
+      for (int x = 0; x < (int)out.groups.size(); ++x) {
+        const int tiles_x = out.groups[x].ntiles * out.nct;
+        for (int t = 0; t < std::min(out.nsplit, tiles_x); ++t)
+          list.push_back({tile_cost[x] * ((tiles_x - t + out.nsplit - 1) / out.nsplit), make_int2(x, t)});
       }
+      std::stable_sort(list.begin(), list.end(),
+                       [](const auto &a, const auto &b) { return a.first > b.first; });
+      for (auto &x : list) {
+        out.items.push_back(x.second);
+        out.cost.push_back(x.first);
+      }
+      return true;
     }
     if (fR || R == 1) return false;
   }
@@ -858,7 +947,7 @@ bool run_cover(const CoverHost &p, const uint8_t *img, int W, int H, int phase, 
               lds[(size_t)a * g.asz + cell(y, i)] = v;
             }
         const int rows_here = std::min(g.tile, H - rt * g.tile);
-        const int nsub = p.sh.wpg / p.sh.nwb;
+        const int nsub = p.sh.wpg / g.nwb;
         for (int pc = 0; pc < nsub; ++pc)
           for (int row = 0; row < g.tile; ++row)
             for (int strip = 0; strip < S; ++strip) {
