@@ -167,31 +167,30 @@ Word sub_word(const Bits &b, int j, int L) {
   }
   return w;
 }
-// last[j] = the last pixel in [from, j] where the word starts on the path, -1 when none, for
-// j = from .. len.
-void find_word(const Bits &b, int from, int len, const Word &w, int16_t *last) {
-  const uint64_t m0 = w.L < 64 ? (1ull << w.L) - 1 : ~0ull, w0 = w.b[0] & m0;
-  const int top = len - w.L;
-  int la = -1;
-  int j = from;
-  while (j <= top) {
-    // the 64 steps from pixel j on, and how many pixels they serve whole
-    const uint64_t lo = bits64(b, j), hi = j + 64 <= len ? bits64(b, j + 64) : 0;
-    const int n = std::min(64, top - j + 1);
-    for (int k = 0; k < n; ++k, ++j) {
-      const uint64_t v = k ? (lo >> k) | (hi << (64 - k)) : lo;
-      if (((v & m0) ^ w0) == 0) {
-        bool ok = true;
-        for (int t = 64; ok && t < w.L; t += 64) {
-          const uint64_t m = w.L - t < 64 ? (1ull << (w.L - t)) - 1 : ~0ull;
-          ok = ((bits64(b, j + t) ^ w.b[t >> 6]) & m) == 0;
-        }
-        if (ok) la = j;
+// Where a word starts on a path: bit j of occ (words of 64 pixels, occ_words(len) of them).
+inline int occ_words(int len) { return (len >> 6) + 1; }
+void find_word(const Bits &b, int len, const Word &w, uint64_t *occ) {
+  const int top = len - w.L;  // the last pixel where the word fits
+  for (int x = 0; x < occ_words(len); ++x) {
+    uint64_t o = 0;
+    if (64 * x <= top) {
+      o = top - 64 * x >= 63 ? ~0ull : (2ull << (top - 64 * x)) - 1;
+      // (64 x + t <= len, so the reads end in the path's spare word)
+      for (int t = 0; t < w.L && o; ++t) {
+        const uint64_t l = bits64(b, 64 * x + t);
+        o &= (w.b[t >> 6] >> (t & 63)) & 1 ? l : ~l;
       }
-      last[j] = (int16_t)la;
     }
+    occ[x] = o;
   }
-  for (; j <= len; ++j) last[j] = (int16_t)la;
+}
+// The last start at pixel <= at, -1 when there is none from pixel `from` on (or before).
+inline int last_start(const uint64_t *occ, int at, int from) {
+  int w = at >> 6;
+  uint64_t x = occ[w] & (~0ull >> (63 - (at & 63)));
+  const int w0 = std::max(from, 0) >> 6;
+  while (!x && w > w0) x = occ[--w];
+  return x ? 64 * w + 63 - __builtin_clzll(x) : -1;
 }
 
 // The furthest step from a path covered below pixel c that does not pass pixel `to`: array (0 the
@@ -199,17 +198,17 @@ void find_word(const Bits &b, int from, int len, const Word &w, int16_t *last) {
 struct Step {
   int arr, j;
 };
-int best_step(const std::vector<Word> &words, const std::vector<std::vector<int16_t>> &last,
-              int c, int to, Step &s) {
+// (occ: the words' starts, `width` words each).
+int best_step(const Word *words, int nw, const uint64_t *occ, int width, int c, int to, Step &s) {
   int end = c;
   s = Step{0, c};
-  for (size_t w = 0; w < words.size(); ++w) {
-    const int at = std::min(c, to - words[w].L);
+  for (int w = 0; w < nw; ++w) {
+    const int L = words[w].L, at = std::min(c, to - L);
     if (at < 0) continue;
-    const int j = last[w][at];
-    if (j >= 0 && j + words[w].L > end) {
-      end = j + words[w].L;
-      s = Step{(int)w + 1, j};
+    const int j = last_start(occ + (size_t)w * width, at, end - L + 1);
+    if (j >= 0 && j + L > end) {
+      end = j + L;
+      s = Step{w + 1, j};
     }
   }
   return end;
@@ -404,14 +403,15 @@ class GroupBuilder {
     CoverGroup &g = out.g;
     const int np = b_ - a_;
     std::vector<int> smp;
-    const int ns = std::min(np, 5);
+    const bool quick = np < 40;  // small groups: their plans are most of a first call
+    const int ns = std::min(np, quick ? 3 : 5);
     for (int s = 0; s < ns; ++s) smp.push_back((int)((2ll * s + 1) * np / (2 * ns)));
     int mid = np / 2;
     for (int i = 0; i < np; ++i)  // the longest path near the middle
       if (std::abs(i - np / 2) <= np / 4 && o_.paths[a_ + i].len > o_.paths[a_ + mid].len) mid = i;
     const int ml = o_.paths[a_ + mid].len;
     std::vector<Word> cand;
-    for (int L = 1; L <= ml; L += std::max(1, L / 3)) {
+    for (int L = 1; L <= ml; L += std::max(1, quick ? L / 2 : L / 3)) {
       for (int j : {0, ml - L}) {
         Word w = sub_word(let_[mid], j, L);
         bool seen = false;
@@ -420,15 +420,15 @@ class GroupBuilder {
       }
     }
     const int nc = (int)cand.size();
-    // occurrences of every candidate on every sample
-    std::vector<std::vector<int16_t>> last(ns);
+    // starts of every candidate on every sample
+    std::vector<std::vector<uint64_t>> occ(ns);
     std::vector<int> width(ns);
     for (int s = 0; s < ns; ++s) {
       const int len = o_.paths[a_ + smp[s]].len;
-      width[s] = len + 1;
-      last[s].resize((size_t)nc * width[s]);
+      width[s] = occ_words(len);
+      occ[s].resize((size_t)nc * width[s]);
       for (int c = 0; c < nc; ++c)
-        find_word(let_[smp[s]], 0, len, cand[c], &last[s][(size_t)c * width[s]]);
+        find_word(let_[smp[s]], len, cand[c], &occ[s][(size_t)c * width[s]]);
     }
     const double scale = (double)np / ns;
     const double ratio = 1.5 * (double)g.rows * g.wid / ((double)g.tile * sh_.S * sh_.R);
@@ -447,7 +447,7 @@ class GroupBuilder {
       int64_t n = 0;
       for (int s = 0; s < ns && n * scale + bc < most; ++s) {
         const Path &p = o_.paths[a_ + smp[s]];
-        const int16_t *la = last[s].data();
+        const uint64_t *oc = occ[s].data();
         int c = p.len / 3;
         for (int t = 0; t < p.nm; ++t) {
           const int l = o_.mems[p.m0 + t].l;
@@ -456,7 +456,7 @@ class GroupBuilder {
             for (int x = 0; x < k; ++x) {
               const int L = cand[ws[x]].L, at = std::min(c, l - L);
               if (at < 0) continue;
-              const int j = la[(size_t)ws[x] * width[s] + at];
+              const int j = last_start(oc + (size_t)ws[x] * width[s], at, end - L + 1);
               if (j >= 0) end = std::max(end, j + L);
             }
             c = end + 1;
@@ -487,7 +487,7 @@ class GroupBuilder {
       ws[k++] = best;
     }
     // the first word was chosen alone: once more, given the others
-    if (k > 1) {
+    if (k > 1 && !quick) {
       const int old = ws[0], best = better(0, k);
       ws[0] = best < 0 ? old : best;
     }
@@ -499,13 +499,13 @@ class GroupBuilder {
     g.bop[0] = 0;
     for (size_t w = 0; w < words_.size(); ++w) {
       const Word &wd = words_[w];
-      std::vector<Word> sub(words_.begin(), words_.begin() + w);
-      std::vector<std::vector<int16_t>> ls(w, std::vector<int16_t>(wd.L + 1));
-      for (size_t v = 0; v < w; ++v) find_word(wd.b, 0, wd.L, sub[v], ls[v].data());
+      const int wd_words = occ_words(wd.L);
+      std::vector<uint64_t> oc(w * wd_words);
+      for (size_t v = 0; v < w; ++v) find_word(wd.b, wd.L, words_[v], &oc[v * wd_words]);
       int c = 0;
       while (c <= wd.L) {
         Step s;
-        c = best_step(sub, ls, c, wd.L, s) + 1;
+        c = best_step(words_.data(), (int)w, oc.data(), wd_words, c, wd.L, s) + 1;
         int q = 0;
         for (int k = 0; k < s.j; ++k) q += (int)((wd.b[k >> 6] >> (k & 63)) & 1);
         out.bops.push_back(o_.xm ? encode(g, s.arr, s.j, q) : encode(g, s.arr, q, s.j));
@@ -520,7 +520,7 @@ class GroupBuilder {
   std::vector<Node> nodes_;
   std::vector<int> lcp_;
   std::vector<std::vector<std::pair<int64_t, std::pair<int, bool>>>> memo_;
-  std::vector<std::vector<int16_t>> cur_last_;
+  std::vector<std::vector<uint64_t>> occ_;  // per path: the words' starts
 
   int tree(int a, int b) {
     Node t{a, b, 0, {}};
@@ -566,13 +566,21 @@ class GroupBuilder {
 
   // The pieces: about equal work for each wave.  The work of a path shows only once its records
   // are there (what it shares with its neighbours is walked once), so the group is cut by members
-  // first and cut again by the work that each path's records took.
+  // first and cut again by the work that each path's records took (slowest against mean piece at
+  // cutoff 512: 1.5 and 1.13; an estimate from the unshared lengths gave 1.5 as well).
   void pieces(GroupOut &out) {
     const int np = b_ - a_;
     lcp_.assign(np, 0);
     for (int i = 0; i + 1 < np; ++i)
       lcp_[i] = common(let_[i], let_[i + 1],
                        std::min(o_.paths[a_ + i].len, o_.paths[a_ + i + 1].len));
+    occ_.resize(np);
+    for (int i = 0; i < np; ++i) {
+      const int len = o_.paths[a_ + i].len, width = occ_words(len);
+      occ_[i].resize(words_.size() * width);
+      for (size_t w = 0; w < words_.size(); ++w)
+        find_word(let_[i], len, words_[w], &occ_[i][w * width]);
+    }
     const int nsub = sh_.wpg / out.g.nwb;
     work_.resize(np);
     for (int i = 0; i < np; ++i) work_[i] = 4 + 3 * o_.paths[a_ + i].nm;
@@ -605,19 +613,6 @@ class GroupBuilder {
   std::vector<int> work_;  // vector instructions of each path's records
 
   int in_acc_ = -1;  // level of the saved product that the accumulators hold, -1 none
-
-  // Occurrences of the words on path i for a walk that has covered the pixels below c: an
-  // occurrence that ends before c is of no use.
-  const std::vector<std::vector<int16_t>> &last_of(int i, int c) {
-    const int len = o_.paths[i].len;
-    cur_last_.resize(words_.size());
-    for (size_t w = 0; w < words_.size(); ++w) {
-      if ((int)cur_last_[w].size() <= len) cur_last_[w].resize(len + 1);
-      const int from = std::max(0, c - words_[w].L);
-      if (from <= len) find_word(let_[i - a_], from, len, words_[w], cur_last_[w].data());
-    }
-    return cur_last_;
-  }
 
   // Records for `steps` on path i; the last one carries the count.
   void put(GroupOut &out, int i, const std::vector<Step> &steps, int level, int slot) {
@@ -666,7 +661,8 @@ class GroupBuilder {
         if (l > s && l <= t.m) ends.push_back({l, slot0_[i - a_] + x});
       }
     std::sort(ends.begin(), ends.end());
-    const auto &last = last_of(t.a, c);
+    const uint64_t *occ = occ_[t.a - a_].data();
+    const int width = occ_words(o_.paths[t.a].len), nw = (int)words_.size();
     int cv = c;
     std::vector<Step> st;
     const size_t rec0 = out.recs.size();
@@ -677,7 +673,7 @@ class GroupBuilder {
       st.clear();
       while (cv <= e.first) {
         Step x;
-        cv = best_step(words_, last, cv, e.first, x) + 1;
+        cv = best_step(words_.data(), nw, occ, width, cv, e.first, x) + 1;
         st.push_back(x);
       }
       put(out, t.a, st, level, e.second);
@@ -689,7 +685,7 @@ class GroupBuilder {
       for (;;) {
         if (cv > t.m) break;
         Step x;
-        const int end = best_step(words_, last, cv, t.m, x);
+        const int end = best_step(words_.data(), nw, occ, width, cv, t.m, x);
         if (end - cv < 3) break;
         cv = end + 1;
         st.push_back(x);
@@ -803,12 +799,17 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
   std::vector<GroupOut> go(ng);
   std::vector<GroupBuilder> gb;
   gb.reserve(ng);
-  for (int i = 0; i < ng; ++i) {
-    gb.emplace_back(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
-    if (!gb[i].fit(go[i])) return false;
-  }
-  parallel(ng, std::min(8, ng / 4), [&](int i) { gb[i].build(go[i]); });
-  size_t dw = 0;
+  for (int i = 0; i < ng; ++i) gb.emplace_back(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
+  std::atomic<bool> fits(true);
+  const int threads = std::min(16, ng / 4);
+  parallel(ng, threads, [&](int i) {
+    if (fits && !gb[i].fit(go[i])) fits = false;
+  });
+  if (!fits) return false;
+  parallel(ng, threads, [&](int i) { gb[i].build(go[i]); });
+  size_t nrec = 64, dw = 0;
+  for (auto &x : go) nrec += x.recs.size();
+  out.recs.reserve(nrec);
   tile_cost.clear();
   for (auto &x : go) {
     CoverGroup g = x.g;
@@ -817,10 +818,8 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
     const int r0 = (int)out.recs.size(), b0 = (int)out.bops.size();
     for (int &b : g.bop) b += b0;
     for (int32_t p : x.piece_off) out.piece_off.push_back(p + r0);
-    for (int4 r : x.recs) {
-      r.w += r0;
-      out.recs.push_back(r);
-    }
+    out.recs.insert(out.recs.end(), x.recs.begin(), x.recs.end());
+    for (size_t r = r0; r < out.recs.size(); ++r) out.recs[r].w += r0;
     out.bops.insert(out.bops.end(), x.bops.begin(), x.bops.end());
     out.mems.insert(out.mems.end(), x.mems.begin(), x.mems.end());
     // vector instructions of a tile: its masks (8 dwords a lane, about 40 instructions a step with
