@@ -2558,7 +2558,7 @@ lpf_status lpf_cnn_create(lpf_ctx c, int W, int H, int max_batch, int max_sample
   n->max_samples = max_samples;
   DeviceGuard g(c->dev);
   const int64_t np = (int64_t)W * H * max_batch;
-  const int64_t cb = cnn_conv_blocks(np), hb = (np + 255) / 256;
+  const int64_t cb = cnn_weight_blocks(), hb = cnn_head_blocks();
   hipError_t e = hipSuccess;
   auto get = [&](void **p, size_t bytes) {
     if (e != hipSuccess) return;
@@ -2580,7 +2580,7 @@ lpf_status lpf_cnn_create(lpf_ctx c, int W, int H, int max_batch, int max_sample
   get((void **)&B.dZ2, 2 * 16 * (size_t)np);
   get((void **)&B.dZ3, 2 * 16 * (size_t)np);
   get((void **)&B.S, 4 * (size_t)np);
-  get((void **)&B.r, 4 * (size_t)max_samples);
+  get((void **)&B.lpart, 8 * (((size_t)max_samples + 255) / 256));
   get((void **)&B.dS, 8 * (size_t)np);
   get((void **)&B.part1, 4 * (size_t)cb * (9 * 256 + 16));
   get((void **)&B.part2, 4 * (size_t)cb * (9 * 256 + 16));

@@ -431,7 +431,8 @@ struct CnnBufs {
   uint16_t *Wf, *Wt;                             // bf16 [3][9][16][16] forward / transposed
   float *W4bf;                                   // head weights rounded to bf16
   uint16_t *X0, *A1, *A2, *A3, *dZ1, *dZ2, *dZ3;  // channels-last activations and gradients
-  float *S, *r;                                  // scores, residuals
+  float *S;                                      // scores
+  double *lpart;                                 // sums of r^2 per 256 samples
   int64_t *dS;                                   // score gradient, 2^-40 fixed point
   float *part1, *part2, *part3, *part_h;         // per-block gradient partials
   float *slices;                                 // [64][kCnnParams] partial sums of the partials
@@ -446,7 +447,9 @@ hipError_t cnn_grad(const CnnBufs &B, const uint64_t *bits, int W, int H, int ba
 hipError_t cnn_pack(const CnnBufs &B, hipStream_t s);
 hipError_t cnn_adam(const CnnBufs &B, const float *grad, float lr, float b1, float b2, float eps,
                     float c1, float c2, hipStream_t s);
-int cnn_conv_blocks(int64_t npix);
+// Workgroups that write partials, at most.
+int cnn_weight_blocks();
+int cnn_head_blocks();
 
 // Kernel launchers (defined in k_full.hip).  All enqueue on `stream` and return the HIP status.
 hipError_t launch_pack(const uint8_t *img, int W, int H, uint64_t *bits, hipStream_t stream);
