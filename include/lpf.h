@@ -161,6 +161,14 @@ lpf_status lpf_plan_check(int cx, int cy, int64_t nb_want, int64_t *out);
 lpf_status lpf_cover_counts(const uint8_t *img, int W, int H, int cx, int cy, int phase, int R,
                             int S, int waves, int lds_bytes, uint32_t *counts);
 
+/* Host run of lpf_delta_swap's launch plan (diagnostic, no device): the change of every count
+ * under the interchange of pixels a (phase 1) and b (phase 0) of a byte image img[H][W], evaluated
+ * by the plan's tables with every access checked.  delta: int32[2][|D_c|], phase 0 first.
+ * Errors: LPF_E_INVAL (arguments, or a check failed), LPF_E_UNSUPPORTED (cutoffs above 126),
+ * LPF_E_NOMEM. */
+lpf_status lpf_swap_plan_delta(const uint8_t *img, int W, int H, int cx, int cy, int a, int b,
+                               int32_t *delta);
+
 /* Throughput probe (diagnostic; not part of the method): one launch of nwg workgroups of 256
  * threads whose lanes each run 8 independent dependency chains for `iters` iterations of
  *   kind 0: two funnel shifts (v_alignbit_b32), a 3-input AND (v_bitop3_b32) and a 3-input OR
@@ -181,8 +189,9 @@ lpf_status lpf_peak_probe(lpf_ctx ctx, int kind, int64_t iters, int nwg, uint32_
  * written in full) with delta[s][p][i] = L_p(I')(v_i) - L_p(I)(v_i), canonical vector order.
  * An interchange of two pixels of the same phase, a == b, or an index outside [0, W*H) gives an
  * all-zero row (indices live on the device and are not checked on the host).  Only the
- * translations whose segment covers a or b are recounted: by offset rows (for cutoffs up to 255,
- * a per-cutoff table of at most 256 MB built on the first call) or by runs of start columns
+ * translations whose segment covers a or b are recounted: from shared segments (cutoffs up to 126;
+ * per-cutoff tables of at most 256 MB built on the first call, and scratch of at most 64 MB), by
+ * offset rows (cutoffs up to 255, a table of at most 256 MB likewise) or by runs of start columns
  * (any cutoff; see lpf_set_delta_method).  Same requirements on W, H, cx, cy, phase_mask as
  * lpf_full; 0 <= n <= 2^24.  Errors: LPF_E_INVAL, LPF_E_NOMEM, LPF_E_DEVICE. */
 lpf_status lpf_delta_swap(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
@@ -190,7 +199,9 @@ lpf_status lpf_delta_swap(lpf_ctx ctx, const uint64_t *bits, int W, int H, int c
                           void *stream);
 
 /* How later lpf_delta_swap calls on ctx recount (the results are identical):
- * LPF_SWAP_AUTO: offset rows -- for a fixed difference d between a path index and a placement
+ * LPF_SWAP_AUTO: shared segments -- the window around a changed pixel as words of 32 candidates,
+ *   placements as ANDs of segments of 8 pixels that neighbouring directions share -- up to cutoff
+ *   126; above it offset rows -- for a fixed difference d between a path index and a placement
  *   index, the pixels of all placements of a vector lie on one image row (column) at two
  *   neighbouring offsets, so one 32-bit window gives the pixel word of up to 32 placements --
  *   when the cutoff's table fits, else runs;

@@ -59,6 +59,7 @@ _sig("lpf_full_noalloc", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _i32, _P, _
 _sig("lpf_chain_stats", _i32, _i32, _i32, _P)
 _sig("lpf_plan_check", _i32, _i32, _i32, _i64, _P)
 _sig("lpf_cover_counts", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _P)
+_sig("lpf_swap_plan_delta", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _P)
 _sig("lpf_peak_probe", _i32, _P, _i32, _i64, _i32, _P, ctypes.POINTER(ctypes.c_double), _P)
 _sig("lpf_set_full_shape", _i32, _P, _i32, _i32, _i32, _i32)
 _sig("lpf_delta_swap", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _P, _i32, _P, _P)
@@ -246,6 +247,18 @@ def lpf_cover_counts(img: np.ndarray, cx: int, cy: int, phase: int, R: int = 0, 
                                out.ctypes.data)
     if st != LPF_OK:
         raise LpfError(st, f"lpf_cover_counts({W}, {H}, {cx}, {cy})")
+    return out
+
+
+def lpf_swap_plan_delta(img: np.ndarray, cx: int, cy: int, a: int, b: int) -> np.ndarray:
+    """Host run of lpf_delta_swap's launch plan (no device) for one interchange: int32 [2][|D_c|],
+    phase 0 first; raises LpfError when a check fails."""
+    img = np.ascontiguousarray(img, np.uint8)
+    H, W = img.shape
+    out = np.zeros((2, lpf_num_vectors(cx, cy)), np.int32)
+    st = _lib.lpf_swap_plan_delta(img.ctypes.data, W, H, cx, cy, a, b, out.ctypes.data)
+    if st != LPF_OK:
+        raise LpfError(st, f"lpf_swap_plan_delta({W}, {H}, {cx}, {cy}, {a}, {b})")
     return out
 
 

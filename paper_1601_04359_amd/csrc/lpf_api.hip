@@ -15,6 +15,7 @@
 
 #include "../../include/lpf.h"
 #include "cover.h"
+#include "swap.h"
 #include "lpf_internal.h"
 
 using namespace lpf;
@@ -133,6 +134,13 @@ struct DiagPlan {
   bool ok = false;
 };
 
+// Tables of the interchange delta by shared segments (plan_swap.hip), in one allocation.
+struct SwapPlan {
+  void *mem = nullptr;
+  SwapLaunch L{};  // the tables' addresses and sizes
+  bool ok = false;
+};
+
 // Launch plan of the two-point counts (k_s2.hip).
 struct S2Plan {
   int4 *fams = nullptr;      // device: vector families {dx0, dy, members}, sorted by dy
@@ -203,6 +211,7 @@ struct lpf_ctx_s {
   std::map<std::pair<int, int>, ChainSet> chain_sets;  // chains per cutoff (host)
   std::map<std::tuple<int, int, int, int, int>, DeltaPlan> delta_plans;
   std::map<std::tuple<int, int, int>, DiagPlan> diag_plans;  // (cx, cy, chunks)
+  std::map<std::pair<int, int>, SwapPlan> swap_plans;        // (cx, cy)
   std::map<std::tuple<int, int, int, int>, TunedShape> tuned;   // autotuner results
   std::map<std::tuple<int, int, int, int>, S2Plan> s2_plans;
   // 3-D vectors per cutoff, longest first, and the start of each one's voxel-table entries
@@ -837,6 +846,56 @@ lpf_status get_diag_plan(lpf_ctx c, int cx, int cy, int nchunks_req, DiagPlan *&
   return LPF_OK;
 }
 
+constexpr size_t kSwapTableMax = (size_t)256 << 20;  // bytes of placement entries per plan
+
+lpf_status get_swap_plan(lpf_ctx c, int cx, int cy, SwapPlan *&plan) {
+  const std::pair<int, int> key(cx, cy);
+  auto it = c->swap_plans.find(key);
+  if (it != c->swap_plans.end()) {
+    plan = &it->second;
+    return LPF_OK;
+  }
+  SwapPlan p;
+  try {
+    SwapHost h;
+    if (plan_swap(cx, cy, kSwapTableMax, h)) {
+      const void *src[7] = {h.sectors.data(), h.tiles.data(), h.idx.data(), h.rank.data(),
+                            h.pix.data(),     h.segs.data(),  h.ents.data()};
+      const size_t len[7] = {h.sectors.size() * sizeof(SwapSector), h.tiles.size() * sizeof(SwapTile),
+                             h.idx.size() * 4, h.rank.size() * 4, h.pix.size() * 4,
+                             h.segs.size() * 4, h.ents.size() * 4};
+      size_t off[8] = {};
+      for (int i = 0; i < 7; ++i) off[i + 1] = off[i] + (len[i] + 255) / 256 * 256;
+      std::vector<char> all(off[7]);
+      for (int i = 0; i < 7; ++i)
+        if (len[i]) memcpy(all.data() + off[i], src[i], len[i]);
+      hipError_t e = hipMalloc(&p.mem, off[7]);
+      if (e != hipSuccess) return hip_fail(e, "lpf_delta_swap: plan allocation");
+      e = hipMemcpy(p.mem, all.data(), off[7], hipMemcpyHostToDevice);
+      if (e != hipSuccess) {
+        (void)hipFree(p.mem);
+        return hip_fail(e, "lpf_delta_swap: plan upload");
+      }
+      char *m = (char *)p.mem;
+      p.L.sectors = (const SwapSector *)(m + off[0]);
+      p.L.tiles = (const SwapTile *)(m + off[1]);
+      p.L.idx = (const int32_t *)(m + off[2]);
+      p.L.rank = (const int32_t *)(m + off[3]);
+      p.L.pix = (const uint32_t *)(m + off[4]);
+      p.L.segs = (const uint32_t *)(m + off[5]);
+      p.L.ents = (const uint32_t *)(m + off[6]);
+      p.L.nsectors = (int)h.sectors.size();
+      p.L.slots = h.slots;
+      p.ok = true;
+    }
+    plan = &c->swap_plans.emplace(key, p).first->second;
+  } catch (const std::exception &) {
+    (void)hipFree(p.mem);
+    return fail(LPF_E_NOMEM, "lpf_delta_swap: host memory for the plan");
+  }
+  return LPF_OK;
+}
+
 // Number of vector chunks for K candidates: enough workgroups to fill the device.
 int delta_chunks(int K) {
   const int groups = (K + 255) / 256;
@@ -1242,6 +1301,7 @@ void lpf_ctx_destroy(lpf_ctx c) {
       (void)hipFree(kv.second.chunk_off);
       (void)hipFree(kv.second.runs);
     }
+    for (auto &kv : c->swap_plans) (void)hipFree(kv.second.mem);
     for (auto &kv : c->diag_plans) {
       (void)hipFree(kv.second.groups);
       (void)hipFree(kv.second.rows);
@@ -1482,6 +1542,28 @@ lpf_status lpf_delta_swap(lpf_ctx c, const uint64_t *bits, int W, int H, int cx,
   if (!g.ok) return fail(LPF_E_DEVICE, "lpf_delta_swap: cannot select the context's device");
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
+  if (!c->force_run_delta) {
+    SwapPlan *sp = nullptr;
+    if ((st = get_swap_plan(c, cx, cy, sp)) != LPF_OK) return st;
+    if (sp->ok) {
+      const size_t need = swap_near_bytes(cx, cy, phase_mask) * swap_batch(cx, cy, phase_mask, n);
+      if ((e = c->ext3.ensure(need)) != hipSuccess) return hip_fail(e, "lpf_delta_swap: scratch");
+      SwapLaunch L = sp->L;
+      L.bits = bits;
+      L.W = W;
+      L.H = H;
+      L.cx = cx;
+      L.cy = cy;
+      L.cand = reinterpret_cast<const int2 *>(swaps);
+      L.K = n;
+      L.near = (uint2 *)c->ext3.p;
+      L.phase_mask = phase_mask;
+      L.nv = (int)lpf_num_vectors(cx, cy);
+      L.delta_out = delta;
+      if ((e = launch_swap(L, s)) != hipSuccess) return hip_fail(e, "lpf_delta_swap: kernel");
+      return LPF_OK;
+    }
+  }
   // offset rows where their table fits (cutoffs up to 255), else the run-based kernel
   DiagPlan *dp = nullptr;
   if (!c->force_run_delta) {

@@ -18,15 +18,14 @@
 // workgroup; a piece is the part of it that one wave walks.  Vectors with dx < 0 are walked on the
 // mirrored image, so every offset is >= 0.
 #include <algorithm>
-#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <exception>
-#include <thread>
 
 #include "../../include/lpf.h"
 #include "cover.h"
+#include "parallel.h"
 
 namespace lpf {
 
@@ -729,29 +728,6 @@ void cover_lanes(int W, int H, int *R, int *S) {
 }
 
 namespace {
-
-// f(0), ..., f(n - 1) on up to `threads` threads (this one among them).
-template <class F>
-void parallel(int n, int threads, F &&f) {
-  std::atomic<int> next(0);
-  std::atomic<bool> bad(false);
-  auto work = [&]() {
-    try {
-      for (int i; (i = next.fetch_add(1)) < n;) f(i);
-    } catch (...) {
-      bad = true;
-    }
-  };
-  const int hw = std::max(1, (int)std::thread::hardware_concurrency());
-  std::vector<std::thread> th;
-  try {
-    for (int t = 1; t < std::min({threads, n, hw}); ++t) th.emplace_back(work);
-  } catch (...) {  // no more threads: the ones that run and this one do the work
-  }
-  work();
-  for (auto &t : th) t.join();
-  if (bad) throw std::bad_alloc();
-}
 
 // The plan for given octants and shape; false when some group's rows do not fit sh.lds.
 bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape &sh,
