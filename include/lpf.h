@@ -169,6 +169,13 @@ lpf_status lpf_cover_counts(const uint8_t *img, int W, int H, int cx, int cy, in
 lpf_status lpf_swap_plan_delta(const uint8_t *img, int W, int H, int cx, int cy, int a, int b,
                                int32_t *delta);
 
+/* Host run of lpf_full3d's launch plan (diagnostic, no device): the counts of one phase of a byte
+ * volume vol[D][H][W] (nonzero = phase 1) by the plan's records, every access checked.
+ * Errors: LPF_E_INVAL (arguments, or a check failed), LPF_E_UNSUPPORTED (no such plan: a cutoff
+ * above 24, rows longer than 512 voxels, or a slab that does not fit in LDS), LPF_E_NOMEM. */
+lpf_status lpf_cover3_counts(const uint8_t *vol, int W, int H, int D, int cx, int cy, int cz,
+                             int phase, uint32_t *counts);
+
 /* Throughput probe (diagnostic; not part of the method): one launch of nwg workgroups of 256
  * threads whose lanes each run 8 independent dependency chains for `iters` iterations of
  *   kind 0: two funnel shifts (v_alignbit_b32), a 3-input AND (v_bitop3_b32) and a 3-input OR
@@ -228,7 +235,8 @@ lpf_status lpf_vectors3(int cx, int cy, int cz, int16_t *dxdydz);
  * sums over the D xy-cuts of their 2-D functions (lpf_full), the ensemble average of Sec. 6.3 times
  * D*W*H.  Requires 1 <= W, H, D <= 65535, W*H*D < 2^32, 0 <= cx <= W-1, 0 <= cy <= H-1,
  * 0 <= cz <= D-1, cutoffs <= 32767, phase_mask in {1,2,3}.  The first call for a cutoff and a
- * volume shape allocates the vector list and the segments' voxel table in the context (device
+ * volume shape allocates the launch plan (prefix trees of the segments; for cutoffs above 24 and
+ * volumes without such a plan the vector list and the segments' voxel table) in the context (device
  * memory kept until lpf_destroy; later calls only read them), so a call to be captured in a
  * graph follows one made outside the capture.
  * Errors: LPF_E_INVAL, LPF_E_UNSUPPORTED (W > 32768, too many vectors), LPF_E_NOMEM,

@@ -59,6 +59,7 @@ _sig("lpf_full_noalloc", _i32, _P, _P, _i32, _i32, _i32, _i32, _u32, _i32, _P, _
 _sig("lpf_chain_stats", _i32, _i32, _i32, _P)
 _sig("lpf_plan_check", _i32, _i32, _i32, _i64, _P)
 _sig("lpf_cover_counts", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _P)
+_sig("lpf_cover3_counts", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _P)
 _sig("lpf_swap_plan_delta", _i32, _P, _i32, _i32, _i32, _i32, _i32, _i32, _P)
 _sig("lpf_peak_probe", _i32, _P, _i32, _i64, _i32, _P, ctypes.POINTER(ctypes.c_double), _P)
 _sig("lpf_set_full_shape", _i32, _P, _i32, _i32, _i32, _i32)
@@ -247,6 +248,18 @@ def lpf_cover_counts(img: np.ndarray, cx: int, cy: int, phase: int, R: int = 0, 
                                out.ctypes.data)
     if st != LPF_OK:
         raise LpfError(st, f"lpf_cover_counts({W}, {H}, {cx}, {cy})")
+    return out
+
+
+def lpf_cover3_counts(vol: np.ndarray, cx: int, cy: int, cz: int, phase: int) -> np.ndarray:
+    """Host run of lpf_full3d's launch plan (no device): counts of one phase of a byte volume
+    [D][H][W]; raises LpfError when a check fails or the volume has no such plan."""
+    vol = np.ascontiguousarray(vol, np.uint8)
+    D, H, W = vol.shape
+    out = np.zeros(lpf_num_vectors3(cx, cy, cz), np.uint32)
+    st = _lib.lpf_cover3_counts(vol.ctypes.data, W, H, D, cx, cy, cz, phase, out.ctypes.data)
+    if st != LPF_OK:
+        raise LpfError(st, f"lpf_cover3_counts({W}, {H}, {D}, {cx}, {cy}, {cz})")
     return out
 
 

@@ -18,6 +18,8 @@
 // A count of zero over the wave's rows ends everything that extends that path there (the paper's
 // enhanced evaluation, Sec. 3.2): the walk goes on at the record's jump target.
 #include "cover.h"
+#include "row_dev.h"
+#include "walk_dev.h"
 
 namespace lpf {
 
@@ -29,44 +31,6 @@ namespace {
 template <class T>
 __device__ __forceinline__ const LPF_CONST T *constant(const T *p) {
   return (const LPF_CONST T *)p;
-}
-
-// The 32 pixels from pixel s on of a packed row, periodic (0 <= s < W).  Bits past W in the row's
-// last word are never used.  Without branches for rows of at least a word.
-__device__ __forceinline__ uint32_t periodic32(const uint32_t *__restrict__ row, int W, int s) {
-  if (W >= 32) {
-    const int q = s >> 5, n = W - s;  // n: pixels left in the row
-    // (the dword after the row's last pixel: any value, and never read past the packed row)
-    const uint32_t lo = row[q], hi = row[min(q + 1, (W - 1) >> 5)];
-    const uint32_t v = __builtin_amdgcn_alignbit(hi, lo, s & 31);
-    return n < 32 ? (v & ((1u << n) - 1u)) | (row[0] << n) : v;
-  }
-  uint32_t v = 0;
-  for (int b = 0, x = s; b < 32; ++b) {
-    v |= ((row[0] >> x) & 1u) << b;
-    x = x + 1 == W ? 0 : x + 1;
-  }
-  return v;
-}
-
-// First pixel of word e of a row extended periodically (bit j of the word is pixel (32 e + j) mod
-// W), or, mirrored, of the 32 pixels that the word holds in reverse (bit j is pixel W - 1 - (32 e
-// + j) mod W).
-__device__ __forceinline__ int word_start(int W, int e, bool mirror) {
-  int s = 32 * e;
-  if (s >= W) s -= W;
-  if (s >= W) s %= W;  // windows of more than twice the row only
-  if (mirror) {
-    s = W - 32 - s;
-    if (s < 0) s += W;
-    if (s < 0) s = (s % W + W) % W;
-  }
-  return s;
-}
-
-// Byte address of a word of the workgroup's LDS.
-__device__ __forceinline__ uint32_t lds_address(const uint32_t *p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t *)p;
 }
 
 // The start pixels of a lane's words: full words below the row's last one, which keeps the bits
@@ -87,173 +51,8 @@ __device__ __forceinline__ void start_pixels(uint32_t (&A)[R], int w0, int W, bo
   }
 }
 
-// The records [r0, r1) for the lane's R words of one row: the walk of one piece over one band.
-//
-// Written in assembly: the running product and the two saved ones stay in one set of registers
-// each (the compiler copied all R of them wherever a record's branches joined, 16 to 80 moves
-// beside a record's 50 useful operations), and the next record's LDS reads are issued as soon as
-// the current product is formed, so that they return under its popcounts and wave sum.
-//
-// (Records read 16 at a time into a vector register, one batch ahead, and taken out with readlane
-// were 10 % slower than scalar loads one record ahead.)
-//
-//   M  start pixels of the lane's words (what a restore of level 1 gives)
-//   base   LDS byte address of the row's first word in array 0
-//   slots  LDS byte address of the group's count slots
-//
-// Registers: K = 4, 8 or 16 words, from v28 on: M, A (product), S1, S2 (saved), D0 (K + 1 dwords of
-// step 0), T, D1 (step 1), N.  s72..75 the record, s76..79 the next one, s80.. the current record's
-// fields once the next one has moved up; s88, s89: byte offsets of the record after it and of the
-// end.  LDS reads are issued only for records of the piece; records are read up to two past it.  A
-// wave sum of at most 64 lanes x 512 start pixels; all 64 lanes are active throughout.
-#define LPF_WALK_ASM                                                                              \
-  ".set cvA, 28 + %[K]\n"                                                                         \
-  ".set cvS1, cvA + %[K]\n"                                                                       \
-  ".set cvS2, cvS1 + %[K]\n"                                                                      \
-  ".set cvD0, cvS2 + %[K]\n"                                                                      \
-  ".set cvT, cvD0 + %[K] + 1\n"                                                                   \
-  ".set cvD1, cvT + 1\n"                                                                          \
-  ".set cvN, cvD1 + %[K] + 1\n"                                                                   \
-  "s_lshl_b32 s88, %[r0], 4\n"                                                                    \
-  "s_lshl_b32 s89, %[r1], 4\n"                                                                    \
-  "Lcv_load%=:\n" /* record at s88 and the one after it, nothing in flight for them yet */        \
-  "s_add_u32 s90, s88, 16\n"                                                                      \
-  "s_load_dwordx4 s[72:75], %[recs], s88\n"                                                       \
-  "s_load_dwordx4 s[76:79], %[recs], s90\n"                                                       \
-  "s_waitcnt lgkmcnt(0)\n"                                                                        \
-  LPF_WALK_READ("0")                                                                              \
-  "s_waitcnt lgkmcnt(0)\n"                                                                        \
-  "Lcv_top%=:\n" /* the record's dwords are in D0, D1 */                                          \
-  "s_bfe_u32 s84, s72, 0x20016\n"                                                                 \
-  "s_cmp_eq_u32 s84, 0\n"                                                                         \
-  "s_cbranch_scc1 Lcv_and%=\n"                                                                    \
-  "s_cmp_eq_u32 s84, 1\n"                                                                         \
-  "s_cbranch_scc0 Lcv_r2%=\n"                                                                     \
-  LPF_WALK_MOV("cvA", "28")                                                                       \
-  "s_branch Lcv_and%=\n"                                                                          \
-  "Lcv_r2%=:\n"                                                                                   \
-  "s_cmp_eq_u32 s84, 2\n"                                                                         \
-  "s_cbranch_scc0 Lcv_r3%=\n"                                                                     \
-  LPF_WALK_MOV("cvA", "cvS1")                                                                     \
-  "s_branch Lcv_and%=\n"                                                                          \
-  "Lcv_r3%=:\n"                                                                                   \
-  LPF_WALK_MOV("cvA", "cvS2")                                                                     \
-  "Lcv_and%=:\n"                                                                                  \
-  "s_lshr_b32 s85, s72, 16\n" /* a funnel shift takes the low five bits */                        \
-  "s_bitcmp1_b32 s72, 21\n"                                                                       \
-  "s_cbranch_scc0 Lcv_one%=\n"                                                                    \
-  "s_lshr_b32 s86, s73, 16\n"                                                                     \
-  ".set cvi, 0\n"                                                                                 \
-  ".rept %[R]\n"                                                                                  \
-  "v_alignbit_b32 v[cvD0+cvi], v[cvD0+cvi+1], v[cvD0+cvi], s85\n"                                 \
-  "v_alignbit_b32 v[cvD1+cvi], v[cvD1+cvi+1], v[cvD1+cvi], s86\n"                                 \
-  "v_bitop3_b32 v[cvA+cvi], v[cvA+cvi], v[cvD0+cvi], v[cvD1+cvi] bitop3:0x80\n"                   \
-  ".set cvi, cvi+1\n"                                                                             \
-  ".endr\n"                                                                                       \
-  "s_branch Lcv_next%=\n"                                                                         \
-  "Lcv_one%=:\n"                                                                                  \
-  ".set cvi, 0\n"                                                                                 \
-  ".rept %[R]\n"                                                                                  \
-  "v_alignbit_b32 v[cvD0+cvi], v[cvD0+cvi+1], v[cvD0+cvi], s85\n"                                 \
-  "v_and_b32 v[cvA+cvi], v[cvA+cvi], v[cvD0+cvi]\n"                                               \
-  ".set cvi, cvi+1\n"                                                                             \
-  ".endr\n"                                                                                       \
-  "Lcv_next%=:\n" /* the next record moves up; its reads, and the record after it */              \
-  "s_mov_b32 s80, s72\n"                                                                          \
-  "s_mov_b64 s[82:83], s[74:75]\n"                                                                \
-  "s_add_u32 s88, s88, 16\n"                                                                      \
-  "s_cmp_ge_u32 s88, s89\n"                                                                       \
-  "s_cbranch_scc1 Lcv_issued%=\n"                                                                 \
-  "s_mov_b64 s[72:73], s[76:77]\n"                                                                \
-  "s_mov_b64 s[74:75], s[78:79]\n"                                                                \
-  "s_add_u32 s90, s88, 16\n"                                                                      \
-  "s_load_dwordx4 s[76:79], %[recs], s90\n"                                                       \
-  LPF_WALK_READ("1")                                                                              \
-  "Lcv_issued%=:\n"                                                                               \
-  "s_bfe_u32 s84, s80, 0x20018\n"                                                                 \
-  "s_cmp_eq_u32 s84, 0\n"                                                                         \
-  "s_cbranch_scc1 Lcv_count%=\n"                                                                  \
-  "s_cmp_eq_u32 s84, 1\n"                                                                         \
-  "s_cbranch_scc0 Lcv_s2%=\n"                                                                     \
-  LPF_WALK_MOV("cvS1", "cvA")                                                                     \
-  "s_branch Lcv_count%=\n"                                                                        \
-  "Lcv_s2%=:\n"                                                                                   \
-  LPF_WALK_MOV("cvS2", "cvA")                                                                     \
-  "Lcv_count%=:\n"                                                                                \
-  "s_bitcmp1_b32 s80, 26\n"                                                                       \
-  "s_cbranch_scc0 Lcv_wait%=\n"                                                                   \
-  "v_bcnt_u32_b32 v[cvN], v[cvA], 0\n"                                                            \
-  ".set cvi, 1\n"                                                                                 \
-  ".rept %[R]-1\n"                                                                                \
-  "v_bcnt_u32_b32 v[cvN], v[cvA+cvi], v[cvN]\n"                                                   \
-  ".set cvi, cvi+1\n"                                                                             \
-  ".endr\n"                                                                                       \
-  "s_lshl_b32 s82, s82, 2\n"                                                                      \
-  "s_add_u32 s82, s82, %[slots]\n"                                                                \
-  "v_cmp_ne_u32_e32 vcc, 0, v[cvN]\n"                                                             \
-  "s_cbranch_vccz Lcv_zero%=\n"                                                                   \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"         \
-  "s_nop 1\n"                                                                                     \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"         \
-  "s_nop 1\n"                                                                                     \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_half_mirror row_mask:0xf bank_mask:0xf\n"             \
-  "s_nop 1\n"                                                                                     \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_mirror row_mask:0xf bank_mask:0xf\n"                  \
-  "s_nop 1\n"                                                                                     \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_bcast:15 row_mask:0xa bank_mask:0xf\n"                \
-  "s_nop 1\n"                                                                                     \
-  "v_add_u32_dpp v[cvN], v[cvN], v[cvN] row_bcast:31 row_mask:0xc bank_mask:0xf\n"                \
-  "s_waitcnt lgkmcnt(0)\n" /* the reads, before the add: it need not be waited for */             \
-  "v_mov_b32 v[cvT], s82\n"                                                                       \
-  "s_brev_b64 exec, 1\n" /* lane 63 holds the sum */                                              \
-  "ds_add_u32 v[cvT], v[cvN]\n"                                                                   \
-  "s_mov_b64 exec, -1\n"                                                                          \
-  "s_cmp_lt_u32 s88, s89\n"                                                                       \
-  "s_cbranch_scc1 Lcv_top%=\n"                                                                    \
-  "s_branch Lcv_end%=\n"                                                                          \
-  "Lcv_zero%=:\n" /* nothing that extends this path counts here: on at the jump target */         \
-  "s_waitcnt lgkmcnt(0)\n"                                                                        \
-  "s_lshl_b32 s83, s83, 4\n"                                                                      \
-  "s_cmp_eq_u32 s83, s88\n" /* the record already under way */                                    \
-  "s_mov_b32 s88, s83\n"                                                                          \
-  "s_cbranch_scc1 Lcv_more%=\n"                                                                   \
-  "s_cmp_lt_u32 s88, s89\n"                                                                       \
-  "s_cbranch_scc1 Lcv_load%=\n"                                                                   \
-  "s_branch Lcv_end%=\n"                                                                          \
-  "Lcv_wait%=:\n"                                                                                 \
-  "s_waitcnt lgkmcnt(0)\n"                                                                        \
-  "Lcv_more%=:\n"                                                                                 \
-  "s_cmp_lt_u32 s88, s89\n"                                                                       \
-  "s_cbranch_scc1 Lcv_top%=\n"                                                                    \
-  "Lcv_end%=:\n"                                                                                  \
-  "s_waitcnt lgkmcnt(0)\n"
-// LDS reads of the record in s72, s73 into D0 and, for two steps, D1 (R + 1 dwords each).
-#define LPF_WALK_READ(id)                                                                         \
-  "s_and_b32 s84, s72, 0xffff\n"                                                                  \
-  "v_lshl_add_u32 v[cvT], s84, 2, %[base]\n"                                                      \
-  LPF_WALK_READ1("cvD0")                                                                          \
-  "s_bitcmp1_b32 s72, 21\n"                                                                       \
-  "s_cbranch_scc0 Lcv_read" id "_%=\n"                                                            \
-  "s_and_b32 s84, s73, 0xffff\n"                                                                  \
-  "v_lshl_add_u32 v[cvT], s84, 2, %[base]\n"                                                      \
-  LPF_WALK_READ1("cvD1")                                                                          \
-  "Lcv_read" id "_%=:\n"
-#define LPF_WALK_READ1(d)                                                                         \
-  ".set cvi, 0\n"                                                                                 \
-  ".rept (%[R]+1)/2\n"                                                                            \
-  "ds_read2_b32 v[" d "+cvi:" d "+cvi+1], v[cvT] offset0:cvi offset1:cvi+1\n"                     \
-  ".set cvi, cvi+2\n"                                                                             \
-  ".endr\n"                                                                                       \
-  ".if ((%[R]+1) & 1)\n"                                                                          \
-  "ds_read_b32 v[" d "+%[R]], v[cvT] offset:4*%[R]\n"                                             \
-  ".endif\n"
-#define LPF_WALK_MOV(dst, src)                                                                    \
-  ".set cvi, 0\n"                                                                                 \
-  ".rept %[R]\n"                                                                                  \
-  "v_mov_b32 v[" dst "+cvi], v[" src "+cvi]\n"                                                    \
-  ".set cvi, cvi+1\n"                                                                             \
-  ".endr\n"
-
+// The records [r0, r1) for the lane's R words of one row (walk_dev.h): the walk of one piece over
+// one band.
 typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
 typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
 typedef uint32_t Words8 __attribute__((ext_vector_type(8)));
@@ -271,8 +70,9 @@ __device__ __forceinline__ void walk(const int4 *recs, int r0, int r1, uint32_t 
     asm volatile(LPF_WALK_ASM                                                                     \
                  : "=&{" a "}"(A), "=&{" s1 "}"(S1), "=&{" s2 "}"(S2), "=&{" d0 "}"(D0),          \
                    "=&{" x0 "}"(X0), "=&{" d1 "}"(D1), "=&{" x1 "}"(X1)                           \
-                 : "{" m "}"(M), [K] "i"(n), [R] "i"(R), [recs] "s"(recs), [r0] "s"(r0),          \
-                   [r1] "s"(r1), [base] "v"(base), [slots] "s"(slots)                             \
+                 : "{" m "}"(M), "{v24}"(base), [K] "i"(n), [KD] "i"(n + 1), [R] "i"(R),        \
+                   [Q] "i"(1), [P] "i"(R), [PD] "i"(R + 1), [MV] "i"(R), [recs] "s"(recs), [r0] "s"(r0), [r1] "s"(r1),          \
+                   [slots] "s"(slots)                                                             \
                  : "s72", "s73", "s74", "s75", "s76", "s77", "s78", "s79", "s80", "s82", "s83",   \
                    "s84", "s85", "s86", "s88", "s89", "s90", "vcc", "scc", "memory");             \
   }

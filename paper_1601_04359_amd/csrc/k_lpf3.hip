@@ -1,5 +1,7 @@
 // Lineal path function of a periodic 3-D volume (the extension of Sec. 2; with cz = 0 it is the
-// sum over the xy-cuts of their 2-D functions, the ensemble of cuts of Sec. 6.3).
+// sum over the xy-cuts of their 2-D functions, the ensemble of cuts of Sec. 6.3), for the volumes
+// that have no prefix-tree plan (k_cover3.hip): cutoffs above 24, rows of more than 512 voxels,
+// slabs that do not fit in LDS.
 //
 // Same bit-parallel product as the 2-D kernel: 32 start voxels of one x-row share a word; for a
 // segment voxel (px, py, pz) a lane forms t = bits [32w + px, 32w + px + 32) of row

@@ -15,6 +15,7 @@
 
 #include "../../include/lpf.h"
 #include "cover.h"
+#include "cover3.h"
 #include "swap.h"
 #include "lpf_internal.h"
 
@@ -134,6 +135,13 @@ struct DiagPlan {
   bool ok = false;
 };
 
+// Prefix-tree plan of the volume evaluation (plan_cover3.hip), its tables in one allocation.
+struct Cover3Plan {
+  void *mem = nullptr;
+  Cover3Launch L{};
+  bool ok = false;
+};
+
 // Tables of the interchange delta by shared segments (plan_swap.hip), in one allocation.
 struct SwapPlan {
   void *mem = nullptr;
@@ -223,6 +231,7 @@ struct lpf_ctx_s {
     std::map<std::pair<int, int>, int2 *> walk;
   };
   std::map<std::tuple<int, int, int>, Vec3> vec3;
+  std::map<std::array<int, 6>, Cover3Plan> cover3_plans;  // (W, H, D, cx, cy, cz)
   std::map<std::string, struct BatchPlan *> batch_plans;
   uint64_t batch_clock = 0;  // use counter of the cached batch plans
   DevBuf ext, ext3, s2ext, s2acc, sext, rank_buf;
@@ -846,6 +855,60 @@ lpf_status get_diag_plan(lpf_ctx c, int cx, int cy, int nchunks_req, DiagPlan *&
   return LPF_OK;
 }
 
+// The prefix-tree plan of a volume; plan->ok is false when none fits.
+lpf_status get_cover3_plan(lpf_ctx c, int W, int H, int D, int cx, int cy, int cz,
+                           Cover3Plan *&plan) {
+  const std::array<int, 6> key = {W, H, D, cx, cy, cz};
+  auto it = c->cover3_plans.find(key);
+  if (it != c->cover3_plans.end()) {
+    plan = &it->second;
+    return LPF_OK;
+  }
+  Cover3Plan p;
+  try {
+    Cover3Host h;
+    const int64_t nv = lpf_num_vectors3(cx, cy, cz);
+    if (std::max(cx, std::max(cy, cz)) <= kCover3Cut) {
+      std::vector<int16_t> v((size_t)nv * 3);
+      lpf_vectors3(cx, cy, cz, v.data());
+      int cus = 256;
+      (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->dev);
+      p.ok = plan_cover3(W, H, D, cx, cy, cz, v.data(), nv, kMaxLds, cus, h);
+    }
+    if (p.ok) {
+      const void *src[4] = {h.groups.data(), h.piece_off.data(), h.recs.data(), h.mems.data()};
+      const size_t len[4] = {h.groups.size() * sizeof(Cover3Group),
+                             h.piece_off.size() * sizeof(int32_t), h.recs.size() * sizeof(int4),
+                             h.mems.size() * sizeof(int32_t)};
+      size_t off[5] = {};
+      for (int i = 0; i < 4; ++i) off[i + 1] = off[i] + (len[i] + 255) / 256 * 256;
+      std::vector<char> all(off[4]);
+      for (int i = 0; i < 4; ++i) memcpy(all.data() + off[i], src[i], len[i]);
+      hipError_t e = hipMalloc(&p.mem, off[4]);
+      if (e != hipSuccess) return hip_fail(e, "lpf_full3d: plan allocation");
+      e = hipMemcpy(p.mem, all.data(), off[4], hipMemcpyHostToDevice);
+      if (e != hipSuccess) {
+        (void)hipFree(p.mem);
+        return hip_fail(e, "lpf_full3d: plan upload");
+      }
+      char *m = (char *)p.mem;
+      p.L.sh = h.sh;
+      p.L.groups = (const Cover3Group *)(m + off[0]);
+      p.L.piece_off = (const int32_t *)(m + off[1]);
+      p.L.recs = (const int4 *)(m + off[2]);
+      p.L.mems = (const int32_t *)(m + off[3]);
+      p.L.ngroups = (int)h.groups.size();
+      p.L.lds_bytes = h.lds_bytes;
+      p.L.nv = (int)nv;
+    }
+    plan = &c->cover3_plans.emplace(key, p).first->second;
+  } catch (const std::exception &) {
+    (void)hipFree(p.mem);
+    return fail(LPF_E_NOMEM, "lpf_full3d: host memory for the plan");
+  }
+  return LPF_OK;
+}
+
 constexpr size_t kSwapTableMax = (size_t)256 << 20;  // bytes of placement entries per plan
 
 lpf_status get_swap_plan(lpf_ctx c, int cx, int cy, SwapPlan *&plan) {
@@ -1254,6 +1317,7 @@ lpf_status lpf_ctx_create(int hip_device, lpf_ctx *out) {
   DeviceGuard g(c->dev);
   hipError_t e = prepare_full_kernels(kMaxLds);
   if (e == hipSuccess) e = prepare_cover_kernels(kMaxLds);
+  if (e == hipSuccess) e = prepare_cover3_kernels(kMaxLds);
   if (e == hipSuccess) e = prepare_delta_kernels(kDeltaLdsMax);
   if (e == hipSuccess) e = prepare_step_kernels(kDeltaLdsMax);
   if (e == hipSuccess) e = prepare_s2_kernels(kMaxLds);
@@ -1301,6 +1365,7 @@ void lpf_ctx_destroy(lpf_ctx c) {
       (void)hipFree(kv.second.chunk_off);
       (void)hipFree(kv.second.runs);
     }
+    for (auto &kv : c->cover3_plans) (void)hipFree(kv.second.mem);
     for (auto &kv : c->swap_plans) (void)hipFree(kv.second.mem);
     for (auto &kv : c->diag_plans) {
       (void)hipFree(kv.second.groups);
@@ -1679,6 +1744,18 @@ lpf_status lpf_full3d(lpf_ctx c, const uint64_t *bits, int W, int H, int D, int 
   DeviceGuard g(c->dev);
   if (!g.ok) return fail(LPF_E_DEVICE, "lpf_full3d: cannot select the context's device");
   hipError_t e;
+  Cover3Plan *cp = nullptr;
+  const lpf_status st = get_cover3_plan(c, W, H, D, cx, cy, cz, cp);
+  if (st != LPF_OK) return st;
+  if (cp->ok) {
+    Cover3Launch L = cp->L;
+    L.bits = bits;
+    L.phase_mask = phase_mask;
+    L.counts = counts;
+    if ((e = launch_cover3(L, (hipStream_t)stream)) != hipSuccess)
+      return hip_fail(e, "lpf_full3d: kernel");
+    return LPF_OK;
+  }
   lpf_ctx_s::Vec3 *v3p = nullptr;
   auto key = std::make_tuple(cx, cy, cz);
   auto it = c->vec3.find(key);
