@@ -5,11 +5,10 @@ U[5, 20] px, volume fraction 0.3, seed 1602), all vectors with |dx|, |dy| <= 128
 bit-packed input already resident in device memory.  One step = one lpf_full call.
 
 Prints ONE JSON line.  `value` = path placements per second (|D_c| * W * H * phases / t).
-`roofline` reports the dominant kernel (k_lpf_full) against the integer-VALU peak (theoretical,
-and measured on the box by lpf_peak_probe), with the op count the kernel issues per launch:
-(N/32)(2 walk + 4 |D_c|), walk = pixels of the chains it walks (lpf_chain_stats): per walked pixel
-and 32 start pixels one funnel shift and half of a 3-input AND and of a 3-input OR, per vector
-two masks and two popcounts.  `cpu_baseline` times the CPU oracle on a bounded sample of the same
+`roofline` reports the dominant kernel (k_cover) against the integer-VALU peak (theoretical, and
+measured by lpf_peak_probe), with the operations that no method of this kind can do without: per
+vector, phase and 32 start pixels the AND that extends a shorter path's product and the popcount,
+2 P (N/32) |D_c| (a walk per vector takes (N/32)(3 M_c + 2 |D_c|), 65 times as many at cutoff 128).  `cpu_baseline` times the CPU oracle on a bounded sample of the same
 workload (median of 5, all host threads and one), and `parity` compares those oracle counts with
 the GPU's.  `anneal` and `learned` are the metric's second half: time to a fixed LPF error of the
 128^2 reconstruction, and learned against uniform proposals on the 256^2 cell.
@@ -29,26 +28,20 @@ if ROOT not in sys.path:
 # MI355X: 256 CUs x 64 int32 lanes per clock x 2.4 GHz (4 SIMD16 per CU, 1 op/lane/clk)
 P_INT_TOPS = 256 * 64 * 2.4e9 / 1e12
 
-# HBM bytes per k_lpf_full launch from rocprofv3 FETCH_SIZE and WRITE_SIZE runs (scaled by the
-# same counters on a 256 MiB copy), profiles/k_lpf_full_512_c128.md.  Valid only for the kernel
-# source and tile-shape choice the counters were taken on; reported as null once either changes.
-MEASURED_TRAFFIC = {"src_sha256_16": "64c08c8f7b640d17", "bytes": int((2 * 833.438 + 1351.59) * 1024)}
+# HBM bytes per k_cover launch from rocprofv3 FETCH_SIZE and WRITE_SIZE runs (scaled by the same
+# counters on a 256 MiB copy), profiles/k_cover_512_c128.md.  Valid only for the kernel and plan
+# that the counters were taken on; reported as null once either changes.
+MEASURED_TRAFFIC = {"src_sha256_16": "f2a88821fe1a3f5e", "bytes": int((2 * 5295 + 4397) * 1024)}
 
 
 def source_hash() -> str:
-    """Hash of the kernel source, the plan builder, and the host functions that pick the tile
-    shape and the bins."""
+    """Hash of the kernel source and of the planner that picks the tile shape and the groups."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_1601_04359_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("k_full.hip", "plan_full.hip"):
+    for name in ("k_cover.hip", "walk_dev.h", "row_dev.h", "cover.h", "plan_cover.hip"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
-    with open(os.path.join(csrc, "lpf_api.hip"), "rb") as f:
-        api = f.read()
-    for fn in (b"bool choose_shape(", b"lpf_status get_full_plan("):
-        i = api.index(fn)
-        h.update(api[i:api.index(b"\n}\n", i)])
     return h.hexdigest()[:16]
 
 
@@ -116,15 +109,13 @@ def measure_peaks(ctx, stream, nwg=4096, iters=20000, reps=3) -> dict:
     return out
 
 
-def chain_ops(W: int, H: int, cx: int, cy: int) -> dict:
-    """Ops k_lpf_full issues per launch, (N/32)(2 walk + 4 |D_c|), and the per-vector walk's
-    count (N/32)(3 M_c + 2 |D_c|) of the same counts, for comparison."""
-    from paper_1601_04359_amd import _abi
-    st = _abi.lpf_chain_stats(cx, cy)
+def count_ops(W: int, H: int, cx: int, cy: int, nph: int = 2) -> dict:
+    """Least ops of a full evaluation (an AND and a popcount per vector, phase and 32 start pixels)
+    and the count of a walk per vector, (N/32)(3 M_c + 2 |D_c|), for comparison."""
+    nv = (cx + 1) * (cy + 1) + cx * cy
     words = W * H / 32.0
-    return {"chains": st["chains"], "walk": st["walk"], "path_pixels": st["path_pixels"],
-            "ops_model": words * (2 * st["walk"] + 4 * st["vectors"]),
-            "ops_per_vector_walk": words * (3 * st["path_pixels"] + 2 * st["vectors"])}
+    return {"ops_model": words * 2 * nph * nv,
+            "ops_per_vector_walk": words * (3 * path_pixels(cx, cy) + 2 * nv)}
 
 
 def ops_alg(W: int, H: int, cx: int, cy: int, nph: int) -> float:
@@ -323,10 +314,10 @@ def delta_bench(ctx, stream, steps: int) -> dict:
                 "speedup_vs_runs": round(res["runs"] / t, 2),
                 "candidates_per_s": round(K / t, 1),
                 "pixel_tests_per_s_T": round(rate / 1e12, 3),
-                "roofline": {"bound": "alu", "achieved": round(rate / 32 / 1e12, 3),
-                             "peak": round(P_INT_TOPS, 3), "unit": "Tops/s (32 pixel tests per op)",
-                             "frac": round(rate / 32 / 1e12 / P_INT_TOPS, 4),
-                             "kernel": "k_delta_diag (+k_dframe in the event window)"},
+                "roofline": {"bound": "hbm", "achieved": round(4e-12 * K * nph * nv / t, 3),
+                             "peak": 8.0, "unit": "TB/s (the changes written)",
+                             "frac": round(4e-12 * K * nph * nv / t / 8.0, 4),
+                             "kernel": "k_swap (+k_swap_near in the event window)"},
                 "outputs_equal_runs": bool(torch.equal(outs["rows"], outs["runs"])),
                 "config": f"{W}x{W} cell, cutoff {c}, phase mask {mask}, 4096 interchanges, one call"}
 
@@ -859,17 +850,6 @@ def mc_bench(args) -> dict:
             "error_vs_n": curves, "reconstruction": recon}
 
 
-def path_pixels3(cx: int, cy: int, cz: int) -> int:
-    """Sum of n + 1 over the canonical 3-D vectors (the 3-D segment has n + 1 voxels)."""
-    n2 = path_pixels(cx, cy)
-    tot = 0
-    for dz in range(1, cz + 1):
-        for dy in range(-cy, cy + 1):
-            for dx in range(-cx, cx + 1):
-                tot += max(abs(dx), abs(dy), dz) + 1
-    return n2 + tot
-
-
 def volume_bench(args) -> dict:
     """3-D extension: a 100^3 periodic level-cut Gaussian volume (phi 0.5, correlation 2 voxels,
     seed 1608; the morphology of the trabecular-bone specimen of Sec. 5), both phases:
@@ -905,7 +885,7 @@ def volume_bench(args) -> dict:
     N = vol.size
     out3 = torch.empty((2, 17969), dtype=torch.int32, device=dev)
     t3 = timed(lambda: ctx.full3d(bits, 100, 100, 100, 16, 16, 16, 3, out=out3), max(3, args.steps))
-    ops3 = (N / 32) * (3 * path_pixels3(16, 16, 16) + 2 * 17969) * 1.0
+    ops3 = (N / 32) * 4 * 17969  # an AND and a popcount per vector, phase and 32 start voxels
     oute = torch.empty((2, 19801), dtype=torch.int32, device=dev)
     te = timed(lambda: ctx.full3d(bits, 100, 100, 100, 99, 99, 0, 3, out=oute), max(3, args.steps))
     cuts = [ctx.pack(dv[z].contiguous()) for z in range(100)]
@@ -915,7 +895,7 @@ def volume_bench(args) -> dict:
         for b in cuts:
             ctx.full(b, 100, 100, 99, 99, 3, out=outc)
     tc = timed(per_cut, 3)
-    opse = (N / 32) * (3 * path_pixels(99, 99) + 2 * 19801)
+    opse = (N / 32) * 4 * 19801
     # reconstruction of a 50 x 50 cell from the ensemble descriptor of the cuts
     side, c = 50, 24
     target = ctx.full3d(bits, 100, 100, 100, c, c, 0, 3)
@@ -945,7 +925,7 @@ def volume_bench(args) -> dict:
                                    "axis, both phases"},
             "roofline": {"bound": "alu", "achieved": round(ach, 3), "peak": round(P_INT_TOPS, 3),
                          "unit": "Tops/s", "frac": round(ach / P_INT_TOPS, 4),
-                         "kernel": "k_lpf3 (+k_ext inside the event window)",
+                         "kernel": "k_cover3 (+k_cover3_zero inside the event window)",
                          "ops_alg_per_launch": ops3},
             "ensemble_of_cuts": {"vectors": 19801, "lpf_full3d_ms": round(te * 1e3, 3),
                                  "per_cut_lpf_full_ms": round(tc * 1e3, 3),
@@ -958,8 +938,7 @@ def volume_bench(args) -> dict:
 
 def batch_bench(args) -> dict:
     """Uneven batch: 256 Boolean disk images, side ~ U{64,128,256,512,1024}, phi ~ U[0.2,0.6],
-    r ~ U[3,15], cutoff side/2, both phases; one step = one lpf_batch call (persistent launch,
-    replayed hipGraph)."""
+    r ~ U[3,15], cutoff side/2, both phases; one step = one lpf_batch call."""
     import numpy as np
     import torch
     import workloads as wl
@@ -1003,7 +982,7 @@ def batch_bench(args) -> dict:
             ev[i][0].record(stream)
             _abi.lpf_batch(ctx.handle, pool, descs, 3, 0, counts, stream)
             ev[i][1].record(stream)
-            # a launch takes about 20 s: wait for it (microseconds against the launch) to report
+            # a launch takes about half a second: wait for it (microseconds against it) to report
             ev[i][1].synchronize()
             print(f"  batch: step {i + 1}/{args.steps} done", file=sys.stderr, flush=True)
         stream.synchronize()
@@ -1018,7 +997,7 @@ def batch_bench(args) -> dict:
         nv = (c + 1) * (c + 1) + c * c
         placements += nv * b.side * b.side * 2
         if c not in cops:
-            cops[c] = chain_ops(b.side, b.side, c, c)
+            cops[c] = count_ops(b.side, b.side, c, c)
         ops += cops[c]["ops_model"]
         ops_vec += ops_alg(b.side, b.side, c, c, 2)
     achieved = ops / kern_s / 1e12
@@ -1033,15 +1012,15 @@ def batch_bench(args) -> dict:
         "dtype": "u32", "data": "synthetic",
         "config": {"workload": "batched full LPF, 256 Boolean disk images, side U{64..1024}, "
                                "phi U[0.2,0.6], r U[3,15], cutoff side/2, both phases, one "
-                               "persistent launch (hipGraph replay)",
+                               "launch",
                    "images_per_side": {str(s): sides.count(s) for s in sorted(set(sides))},
                    "tuned_shapes_R_wpg_lds": {str(k): v for k, v in sorted(tuned.items())},
                    "tune_s": round(t_tune, 2), "setup_s": round(t_setup, 2)},
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": round(P_INT_TOPS, 3),
                      "unit": "Tops/s", "frac": round(achieved / P_INT_TOPS, 4), "traffic": None,
-                     "kernel": "k_lpf_batch (+k_ext_batch in the event window)",
-                     "model": "int32 lane-ops issued per launch = sum over images of "
-                              "(N/32)(2 walk + 4 |D_c|), walk = pixels over the cutoff's chains",
+                     "kernel": "k_cover_batch (+k_cover_zero_batch in the event window)",
+                     "model": "least int32 lane-ops per launch = sum over images of 2 P (N/32) |D_c|: an "
+                              "AND and a popcount per vector, phase and 32 start pixels",
                      "event_ms_mean": round(kern_s * 1e3, 3), "ops_per_launch": ops,
                      "ops_per_vector_walk": ops_vec,
                      "per_vector_walk_equivalent_tops": round(ops_vec / kern_s / 1e12, 3)},
@@ -1215,7 +1194,7 @@ def main() -> int:
     placements = nv * W * H * nph
     value = placements / (wall / args.steps) / 1e9
     kern_s = float(np.median(step_ms)) / 1e3
-    co = chain_ops(W, H, cx, cy)
+    co = count_ops(W, H, cx, cy)
     achieved = co["ops_model"] / kern_s / 1e12
     line = {
         "metric": "LPF path-placements/s",
@@ -1236,9 +1215,9 @@ def main() -> int:
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": round(P_INT_TOPS, 3),
                      "unit": "Tops/s", "frac": round(achieved / P_INT_TOPS, 4),
                      "traffic": measured_traffic(),
-                     "kernel": "k_lpf_full (+k_ext inside the event window)",
-                     "model": "int32 lane-ops issued per launch = (N/32)(2 walk + 4 |D_c|), "
-                              f"walk = {co['walk']} pixels over {co['chains']} chains",
+                     "kernel": "k_cover (+k_cover_zero inside the event window)",
+                     "model": "least int32 lane-ops per launch = 2 P (N/32) |D_c|: an AND and a popcount "
+                              "per vector, phase and 32 start pixels",
                      "ops_per_launch": co["ops_model"],
                      "peak_theoretical": round(P_INT_TOPS, 3),
                      "peak_measured": peaks["valu_mix_tops"],
@@ -1254,8 +1233,8 @@ def main() -> int:
                      "placements_per_s_G": round(placements / (enh_ms / 1e3) / 1e9, 3),
                      "speedup_vs_standard": round(kern_s * 1e3 / enh_ms, 3),
                      "counts_equal_standard": enh_equal,
-                     "note": "a chain's walk stops for a band once a member has no occurrence "
-                             "there (Sec. 3.2 enhanced evaluation); not used for the roofline"},
+                     "note": "the walk of lpf_full itself stops once a count is zero (Sec. 3.2 "
+                             "enhanced evaluation)"},
     }
     s2_ops = s2_ops_alg(W, H, cx, cy)
     s2_ach = s2_ops / (s2_ms / 1e3) / 1e12

@@ -91,9 +91,11 @@ lpf_status lpf_pack(lpf_ctx ctx, const uint8_t *img, int W, int H, uint64_t *bit
  * vector of D_c and every phase of phase_mask, exact uint32 counts in `out_layout`.
  * bits: packed image as above (read only).  counts: see "Output layouts" (written in full).
  * Requires 1 <= W, H <= 65535, 0 <= cx <= W-1, 0 <= cy <= H-1, phase_mask in {1,2,3}.
- * Rows are staged in LDS with their periodic halo; when a row tile and its cy halo rows do not
- * fit (e.g. the whole domain, cx = W - 1, cy = H - 1, of a 1024 x 1024 image), the rows are read
- * from a periodically extended copy of the image in device memory instead (same counts).
+ * Rows are staged in LDS with their periodic halo; images whose rows do not fit, and domains of
+ * more than 2^22 vectors, are read from a periodically extended copy in device memory instead
+ * (same counts).  The first call for an image size and cutoff builds its launch plan on the host
+ * and keeps it in the context, so a call to be captured in a graph follows one made outside the
+ * capture.
  * Errors: LPF_E_INVAL (arguments), LPF_E_UNSUPPORTED (a cutoff above 32767, the int16 range of
  * the vectors, or W > 32768), LPF_E_NOMEM / LPF_E_DEVICE (HIP).  The same cutoff limit applies to
  * every entry point below. */
@@ -101,10 +103,11 @@ lpf_status lpf_full(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int
                     unsigned phase_mask, int out_layout, uint32_t *counts, void *stream);
 
 /* The paper's "enhanced" evaluation (Sec. 3.2: segments whose shorter overlapping segments
- * already have no occurrence are not walked to the end), done exactly per wavefront: every 16
- * segment pixels a wavefront stops walking the segment once none of its start pixels can still
- * count for a requested phase.  Same arguments, same counts as lpf_full, bit for bit; the time
- * saved depends on the image.  Errors as lpf_full. */
+ * already have no occurrence are not walked to the end), done exactly per wavefront: a count of
+ * zero over its start pixels ends the walk of everything that extends that segment.  lpf_full
+ * does the same, except where it reads rows from device memory: there only this call skips.  Same
+ * arguments, same counts as lpf_full, bit for bit; the time saved depends on the image.  Errors
+ * as lpf_full. */
 lpf_status lpf_full_enhanced(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
                              unsigned phase_mask, int out_layout, uint32_t *counts,
                              void *stream);
@@ -133,7 +136,7 @@ lpf_status lpf_full_sampled(lpf_ctx ctx, const uint64_t *bits, int W, int H, int
 lpf_status lpf_full_noalloc(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
                             unsigned phase_mask, int out_layout, uint32_t *counts, void *stream);
 
-/* Statistics of the chains lpf_full walks for cutoff (cx, cy) (host only; no device, no
+/* Statistics of the chains that lpf_full walks when it reads rows from device memory, for cutoff (cx, cy) (host only; no device, no
  * context).  A chain is one walked vector v and every vector u of D_c whose digitised path is,
  * up to a translation, pixels 0..n_u of v's path (a "shorter overlapping segment" of v, Sec.
  * 3.2); one walk gives the counts of all of them.  out (host, 4 int64): |D_c|, number of chains,
@@ -142,7 +145,7 @@ lpf_status lpf_full_noalloc(lpf_ctx ctx, const uint64_t *bits, int W, int H, int
  * out or a cutoff outside [0, 32767], LPF_E_UNSUPPORTED above 2^26 vectors; sets no message. */
 lpf_status lpf_chain_stats(int cx, int cy, int64_t *out);
 
-/* Host check of the launch plan lpf_full builds for cutoff (cx, cy) with nb_want workgroup bins
+/* Host check of the launch plan of those chains for cutoff (cx, cy) with nb_want workgroup bins
  * requested (host only; no device, no context): every vector of D_c is counted exactly once,
  * each as pixel l of a walked path whose first l + 1 pixels are its own path (checked by the
  * digitisation rule), members of a piece in increasing l, at most 256 members per bin.  out
@@ -273,23 +276,20 @@ typedef struct {
   int64_t counts_off;
 } lpf_image_desc;
 
-/* lpf_full for many images of any sizes in ONE persistent launch: workgroups draw work items
- * (image, bin of vector chains) from a device counter, longest first, until the list is empty.
- * descs (host): n_images (<= 65535) descriptors; every image follows lpf_full's rules.  The
- * first call for a set of (descriptors, phases, layout) builds launch plans and captures the
- * launch sequence in a hipGraph owned by the context; later calls with the same set replay it,
- * with any bits_pool and counts_pool (their addresses are written on `stream` before each
- * replay).  The context keeps the 16 most recently used graphs (releasing one waits for the
- * device).  Calls on one context must not overlap (the graph's scratch is shared).  Shapes tuned
- * by lpf_autotune_full for an image size are used.  Errors: LPF_E_INVAL (a descriptor, naming
- * its index), LPF_E_UNSUPPORTED, LPF_E_NOMEM, LPF_E_DEVICE. */
+/* lpf_full for many images of any sizes in one launch over the work items of all of them (a group
+ * of an image's directions, a phase, a share of its rows), longest first; images whose rows do not
+ * fit in LDS follow one by one.  descs (host): n_images (<= 65535) descriptors; every image follows
+ * lpf_full's rules.  The first call for a set of (descriptors, phases, layout) builds launch plans
+ * and the item list; the context keeps the 16 most recently used sets (releasing one waits for
+ * the device).  bits_pool and counts_pool may differ from call to call.  Calls on one context
+ * must not overlap.  Shapes tuned by lpf_autotune_full for an image size are used.  Errors:
+ * LPF_E_INVAL (a descriptor, naming its index), LPF_E_UNSUPPORTED, LPF_E_NOMEM, LPF_E_DEVICE. */
 lpf_status lpf_batch(lpf_ctx ctx, const uint64_t *bits_pool, const lpf_image_desc *descs,
                      int n_images, unsigned phase_mask, int out_layout, uint32_t *counts_pool,
                      void *stream);
 
-/* Autotuner for lpf_full: times the tile shapes R in {2,4,8,16}, waves per group in {4,8} (and
- * 16 with the 160 KiB budget, one group per CU) and staging budgets {64 KiB, 160 KiB} on the
- * given image (several runs each, stream-ordered and
+/* Autotuner for lpf_full: times the automatic plan and tile shapes R in {2,4,8,16} by waves per
+ * workgroup and staging budget on the given image (several runs each, stream-ordered and
  * synchronised here) and records the fastest for images of this W, H, cx, cy in the context;
  * lpf_full and lpf_batch then use it.  *best_ms (host, may be NULL) receives its time.  This
  * replaces the paper's fixed occupancy rule, eq. (block).  Errors: as lpf_full. */
@@ -502,7 +502,7 @@ void lpf_cnn_destroy(lpf_cnn net);
 
 /* Tile-shape override for lpf_full (and the kernels that share its launch plans); used by the
  * autotuner.  R = 32-pixel words per lane (1,2,4,8,16), S = lanes per image row (power of two,
- * <= 64), waves_per_group (1..16; automatic: 8, or 16 when the rows need the 160 KiB budget),
+ * <= 64), waves_per_group (1..16; automatic: 8, or 16 with a staging budget above 80 KiB),
  * lds_bytes = staging budget per workgroup (<= 160 KiB; a
  * budget too small for one row tile and its halo selects rows read from device memory).
  * 0 in any field restores the automatic choice for that field.  This replaces the paper's
