@@ -61,7 +61,8 @@ __device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane) {
   return v;
 }
 
-constexpr int kNearRows = 2;   // window rows of a wave
+// Window rows of a wave: 512 candidates at cutoff 48 take 27, 29 and 35 us with 1, 2 and 4.
+constexpr int kNearRows = 1;
 constexpr int kNearWords = 4;  // words of a row in flight
 
 }  // namespace
@@ -279,8 +280,9 @@ k_swap(const uint2 *__restrict__ near, int npos, const SwapSector *__restrict__ 
   const uint2 *in = near + ((size_t)g * nph + p) * npos;
   const int npix = s.npix;
   if (threadIdx.x == 0) slot[0] = make_uint2(0, 0);
-  // kBatch loads in flight (past the end: the last entry again)
-  constexpr int kBatch = 4, kThreads = 64 * kSwapWaves;
+  // kBatch loads in flight, twice as many of segments (past the end: the last entry again; with
+  // twice as many of both 2048 candidates at cutoff 32 take 34.5 us against 33.3)
+  constexpr int kBatch = 2, kThreads = 64 * kSwapWaves;
   for (int i0 = threadIdx.x; i0 < npix; i0 += kThreads * kBatch) {
     uint32_t at[kBatch];
 #pragma unroll
