@@ -255,7 +255,9 @@ lpf_status lpf_full3d(lpf_ctx ctx, const uint64_t *bits, int W, int H, int D, in
  * that of v).  The paper evaluates S2 through the FFT over all W x H shifts; here the pairs are
  * counted directly, 32 start pixels per AND and popcount (cx = W-1, cy = H-1 covers every
  * shift).  Phase 0 follows from phase 1 by eq. (S2add) in counts: C_0(v) = W H - 2 N_1 + C_1(v).
- * bits, counts, W, H, cx, cy, phase_mask, out_layout: as lpf_full.
+ * bits, counts, W, H, cx, cy, phase_mask, out_layout: as lpf_full.  Calls take turns with two
+ * accumulators of the context (each clears the other's), so a captured call must not be replayed
+ * with other calls in between or twice in a row.
  * Errors: LPF_E_INVAL (arguments), LPF_E_NOMEM / LPF_E_DEVICE (HIP). */
 lpf_status lpf_s2(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
                   unsigned phase_mask, int out_layout, uint32_t *counts, void *stream);
