@@ -39,11 +39,47 @@ struct CoverGroup {
   int32_t rst, wid;      // dwords between rows, dwords staged per row
   int32_t asz;           // dwords of one array (array 0 the image, 1.. the word masks)
   int32_t sh_a, sh_b;    // first dword staged of row y: max(0, ((y - tile + 1) sh_a - sh_b) >> 16)
-  uint32_t wid_magic, rows_magic;  // ceil(2^32 / wid), ceil(2^32 / rows)
+  uint32_t wid_magic, rows_magic;  // ceil(2^32 / wid), ceil(2^32 / rows); wid and rows are >= 2
   int32_t nw;            // word masks
   int32_t bop[kCoverWords + 1];  // build steps of mask a: bops[bop[a - 1]] .. bops[bop[a]]
   int32_t mirror;        // x reversed (vectors with dx < 0)
 };
+
+// Index arithmetic of a group's LDS rows, for the kernel and for the planner's host run of it (G: a
+// CoverGroup in whatever address space).
+//
+// i / n for i < 2^16 times n's rounding error below 2^32, magic = ceil(2^32 / n), n >= 2.
+__host__ __device__ __forceinline__ int cover_div(int i, uint32_t magic) {
+  return (int)(((uint64_t)(uint32_t)i * magic) >> 32);
+}
+// First dword staged of row y.
+template <class G>
+__host__ __device__ __forceinline__ int cover_first(const G &g, int y) {
+  const int d = y - g.tile + 1 > 0 ? y - g.tile + 1 : 0;
+  const int e = (d * g.sh_a - g.sh_b) >> 16;
+  return e > 0 ? e : 0;
+}
+// Staged cell i of rows * wid: row y, dword e of the row.
+template <class G>
+__host__ __device__ __forceinline__ void cover_cell(const G &g, int i, int &y, int &e) {
+  y = cover_div(i, g.wid_magic);
+  e = cover_first(g, y) + i - y * g.wid;
+}
+// Item i of a mask's build, C dwords each: chunk i / rows of row i mod rows; the last chunk of a row
+// is moved back to end with the row.  Returns the first dword's place in its array.
+template <int C>
+__host__ __device__ __forceinline__ int cover_mask_items(int wid, int rows) {
+  return (wid + C - 1) / C * rows;
+}
+template <int C, class G>
+__host__ __device__ __forceinline__ int cover_mask_item(const G &g, int i) {
+  const int ch = cover_div(i, g.rows_magic);
+  const int y = i - ch * g.rows;
+  const int e = ch * C < g.wid - C ? ch * C : g.wid - C;
+  return y * g.rst + cover_first(g, y) + e;
+}
+// Dwords per item for R words per lane.
+constexpr int cover_mask_words(int R) { return R >= 7 ? 8 : R + 1; }
 
 // One image's plan as the kernel reads it.
 struct CoverImg {

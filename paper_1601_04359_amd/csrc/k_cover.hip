@@ -125,13 +125,9 @@ template <int C>
 __device__ __forceinline__ void build_mask(const LPF_CONST CoverGroup &g, const LPF_CONST uint32_t *bops,
                                            int b0, int b1, uint32_t *__restrict__ lds,
                                            uint32_t *__restrict__ dst) {
-  const int chunks = (g.wid + C - 1) / C;
-  const int items = chunks * g.rows;
+  const int items = cover_mask_items<C>(g.wid, g.rows);
   for (int i = threadIdx.x; i < items; i += blockDim.x) {
-    const int ch = (int)__umulhi((uint32_t)i, g.rows_magic);
-    const int y = i - ch * g.rows;
-    const int d = max(0, y - g.tile + 1);
-    const int at = y * g.rst + max(0, (d * g.sh_a - g.sh_b) >> 16) + min(ch * C, g.wid - C);
+    const int at = cover_mask_item<C>(g, i);
     uint32_t v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) v[c] = 0xffffffffu;
@@ -143,7 +139,7 @@ __device__ __forceinline__ void build_mask(const LPF_CONST CoverGroup &g, const 
 #pragma unroll
       for (int c = 0; c <= C; ++c) t[c] = q[c];
 #pragma unroll
-      for (int c = 0; c < C; ++c) v[c] &= __builtin_amdgcn_alignbit(t[c + 1], t[c], sh);
+      for (int c = 0; c < C; ++c) v[c] &= funnel(t[c + 1], t[c], (int)sh);
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) dst[at + c] = v[c];
@@ -186,18 +182,17 @@ __device__ __forceinline__ void cover_group(const CoverImg &I, int gi, int phase
     __syncthreads();  // every wave is done with the previous tile
     // rows Y0 .. Y0 + rows - 1 (mod H): a word per lane, so that a wave reads along the rows
     for (int i = tid; i < cells; i += nt) {
-      const int y = (int)__umulhi((uint32_t)i, g.wid_magic);
-      const int d = max(0, y - g.tile + 1);
-      const int e = max(0, (d * g.sh_a - g.sh_b) >> 16) + i - y * g.wid;
+      int y, e;
+      cover_cell(g, i, y, e);
       int r = Y0 + y;
       if (r >= I.H) r -= I.H;
       if (r >= I.H) r %= I.H;
       const uint32_t v = periodic32(rows + (size_t)r * wpr, I.W, word_start(I.W, e0 + e, mirror));
-      lds[y * g.rst + e] = flip ^ (mirror ? __builtin_bitreverse32(v) : v);
+      lds[y * g.rst + e] = flip ^ (mirror ? bit_reverse(v) : v);
     }
     for (int a = 1; a <= g.nw; ++a) {
       __syncthreads();
-      build_mask<(R >= 7 ? 8 : R + 1)>(g, bops, g.bop[a - 1], g.bop[a], lds, lds + a * g.asz);
+      build_mask<cover_mask_words(R)>(g, bops, g.bop[a - 1], g.bop[a], lds, lds + a * g.asz);
     }
     __syncthreads();
     const int rows_here = min(g.tile, I.H - Y0);
@@ -253,7 +248,7 @@ __global__ void k_start_sets(const uint32_t *__restrict__ src, int W, int H, int
   const uint32_t *row = src + (size_t)(mirror ? r - H : r) * wpr;
   const int left = W - 32 * e;
   uint32_t v = periodic32(row, W, word_start(W, e, mirror));
-  if (mirror) v = __builtin_bitreverse32(v);
+  if (mirror) v = bit_reverse(v);
   out[i] = v & (left >= 32 ? 0xffffffffu : (1u << left) - 1u);
 }
 

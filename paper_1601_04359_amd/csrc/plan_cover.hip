@@ -26,6 +26,7 @@
 #include "../../include/lpf.h"
 #include "cover.h"
 #include "parallel.h"
+#include "row_dev.h"
 
 namespace lpf {
 
@@ -259,7 +260,7 @@ struct Geometry {
   int slope;
   void set(int tile, int S, int R, CoverGroup &g) const {
     g.tile = tile;
-    g.rows = tile + maxpy;
+    g.rows = std::max(2, tile + maxpy);  // one row, H = 1: rows_magic would not fit 32 bits
     g.sh_a = slope;
     int64_t b = 0;
     for (int d = 0; d <= maxpy; ++d)
@@ -882,8 +883,56 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
   }
 }
 
+namespace {
+
+// A byte image as packed rows, the bits past W of each row set (they are not part of the image).
+std::vector<uint32_t> packed_rows(const uint8_t *img, int W, int H, int wpr) {
+  std::vector<uint32_t> rows((size_t)H * wpr, 0);
+  for (int y = 0; y < H; ++y)
+    for (int x = 0; x < 32 * wpr; ++x)
+      if (x >= W || img[(size_t)y * W + x])
+        rows[(size_t)y * wpr + (x >> 5)] |= 1u << (x & 31);
+  return rows;
+}
+
+// The masks of a group as the kernel builds them, C dwords per item; false when an access leaves
+// its array.
+template <int C>
+bool run_masks(const CoverHost &p, const CoverGroup &g, int64_t top, std::vector<uint32_t> &lds) {
+  const int items = cover_mask_items<C>(g.wid, g.rows);
+  for (int a = 1; a <= g.nw; ++a)
+    for (int i = 0; i < items; ++i) {
+      const int at = cover_mask_item<C>(g, i);
+      if (at < 0 || at + C > g.asz) return false;
+      uint32_t v[C];
+      std::fill(v, v + C, ~0u);
+      for (int b = g.bop[a - 1]; b < g.bop[a]; ++b) {
+        const int64_t q = at + (int64_t)(p.bops[b] & 0xffff);
+        if (q + C >= top) return false;
+        for (int c = 0; c < C; ++c) v[c] &= funnel(lds[q + c + 1], lds[q + c], (p.bops[b] >> 16) & 31);
+      }
+      for (int c = 0; c < C; ++c) lds[(size_t)a * g.asz + at + c] = v[c];
+    }
+  return true;
+}
+bool run_masks(int C, const CoverHost &p, const CoverGroup &g, int64_t top,
+               std::vector<uint32_t> &lds) {
+  switch (C) {
+    case 2: return run_masks<2>(p, g, top, lds);
+    case 3: return run_masks<3>(p, g, top, lds);
+    case 4: return run_masks<4>(p, g, top, lds);
+    case 5: return run_masks<5>(p, g, top, lds);
+    case 6: return run_masks<6>(p, g, top, lds);
+    case 7: return run_masks<7>(p, g, top, lds);
+    default: return run_masks<8>(p, g, top, lds);
+  }
+}
+
+}  // namespace
+
 bool run_cover(const CoverHost &p, const uint8_t *img, int W, int H, int phase, int64_t *counts) {
-  const int S = p.sh.S, R = p.sh.R, rpw = 64 / S, SR = S * R;
+  const int S = p.sh.S, R = p.sh.R, rpw = 64 / S, SR = S * R, wpr = 2 * ((W + 63) / 64);
+  const std::vector<uint32_t> rows = packed_rows(img, W, H, wpr);
   std::vector<uint32_t> lds(p.lds_bytes / 4 + 64);
   for (const CoverGroup &g : p.groups) {
     const int64_t top = (int64_t)(1 + g.nw) * g.asz + kCoverPad;
@@ -893,34 +942,16 @@ bool run_cover(const CoverHost &p, const uint8_t *img, int W, int H, int phase, 
       for (int rt = 0; rt < g.ntiles; ++rt) {
         uint32_t junk = 12345u + ct * 7 + rt;
         for (auto &d : lds) d = junk = junk * 1664525u + 1013904223u;
-        auto cell = [&](int y, int i) {
-          const int d = std::max(0, y - g.tile + 1);
-          return y * g.rst + std::max(0, (int)(((int64_t)d * g.sh_a - g.sh_b) >> 16)) + i;
-        };
-        for (int y = 0; y < g.rows; ++y)
-          for (int i = 0; i < g.wid; ++i) {
-            const int at = cell(y, i), e = at - y * g.rst + ct * SR;
-            uint32_t v = 0;
-            for (int b = 0; b < 32; ++b) {
-              int x = (int)((32ll * e + b) % W);
-              if (g.mirror) x = W - 1 - x;
-              v |= (uint32_t)((img[(size_t)((rt * g.tile + y) % H) * W + x] != 0) == (phase != 0)) << b;
-            }
-            if (at < 0 || at >= g.asz) return false;
-            lds[at] = v;
-          }
-        for (int a = 1; a <= g.nw; ++a)
-          for (int y = 0; y < g.rows; ++y)
-            for (int i = 0; i < g.wid; ++i) {
-              uint32_t v = ~0u;
-              for (int t = g.bop[a - 1]; t < g.bop[a]; ++t) {
-                const int64_t at = cell(y, i) + (int64_t)(p.bops[t] & 0xffff);
-                const int sh = (p.bops[t] >> 16) & 31;
-                if (at + 1 >= top) return false;
-                v &= (uint32_t)((((uint64_t)lds[at + 1] << 32) | lds[at]) >> sh);
-              }
-              lds[(size_t)a * g.asz + cell(y, i)] = v;
-            }
+        for (int i = 0; i < g.rows * g.wid; ++i) {
+          int y, e;
+          cover_cell(g, i, y, e);
+          const int64_t at = (int64_t)y * g.rst + e;
+          if (y < 0 || y >= g.rows || at < 0 || at >= g.asz) return false;
+          const uint32_t *row = rows.data() + (size_t)((rt * g.tile + y) % H) * wpr;
+          const uint32_t v = periodic32(row, W, word_start(W, ct * SR + e, g.mirror != 0));
+          lds[at] = (phase ? 0u : ~0u) ^ (g.mirror ? bit_reverse(v) : v);
+        }
+        if (!run_masks(cover_mask_words(R), p, g, top, lds)) return false;
         const int rows_here = std::min(g.tile, H - rt * g.tile);
         const int nsub = p.sh.wpg / g.nwb;
         for (int pc = 0; pc < nsub; ++pc)
