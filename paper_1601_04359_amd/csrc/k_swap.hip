@@ -18,36 +18,13 @@
 #include <algorithm>
 
 #include "delta_dev.h"
+#include "row_dev.h"
 #include "swap.h"
 
 namespace lpf {
 
 namespace {
 
-// 32 pixels of a row of nd dwords (even) from column x on, periodic.  One 8-byte load, and one more
-// for the lanes whose pixels go on at the row's start: with 64 candidates per wave every load is
-// 64 cache lines.
-struct __attribute__((packed, aligned(4))) Dwords2 {
-  uint64_t v;
-};
-__device__ __forceinline__ uint32_t row_word(const uint32_t *__restrict__ row, int nd, int W, int x) {
-  const int e = min(x >> 5, nd - 2);
-  const uint64_t w = ((const Dwords2 *)(row + e))->v;
-  uint32_t v = (uint32_t)(w >> (x - 32 * e));
-  const int n = W - x;
-  if (n >= 32) return v;
-  if (W >= 32) return (v & ((1u << n) - 1u)) | (row[0] << n);
-  v &= (1u << n) - 1u;
-  for (int t = n; t < 32; t += W) v |= row[0] << t;
-  return v;
-}
-// Bits t, t + W, ... of a word.
-__device__ __forceinline__ uint32_t every(int t, int W) {
-  if (W >= 32) return t < 32 ? 1u << t : 0u;
-  uint32_t v = 0;
-  for (; t < 32; t += W) v |= 1u << t;
-  return v;
-}
 // Lane i's bit j to lane j's bit i, for the 32 lanes of each half of the wave.
 __device__ __forceinline__ uint32_t transpose32(uint32_t v, int lane) {
 #pragma unroll

@@ -885,16 +885,6 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
 
 namespace {
 
-// A byte image as packed rows, the bits past W of each row set (they are not part of the image).
-std::vector<uint32_t> packed_rows(const uint8_t *img, int W, int H, int wpr) {
-  std::vector<uint32_t> rows((size_t)H * wpr, 0);
-  for (int y = 0; y < H; ++y)
-    for (int x = 0; x < 32 * wpr; ++x)
-      if (x >= W || img[(size_t)y * W + x])
-        rows[(size_t)y * wpr + (x >> 5)] |= 1u << (x & 31);
-  return rows;
-}
-
 // The masks of a group as the kernel builds them, C dwords per item; false when an access leaves
 // its array.
 template <int C>

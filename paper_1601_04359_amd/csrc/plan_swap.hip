@@ -21,6 +21,7 @@
 #include "../../include/lpf.h"
 #include "lpf_internal.h"
 #include "parallel.h"
+#include "row_dev.h"
 #include "swap.h"
 
 namespace lpf {
@@ -297,24 +298,39 @@ namespace {
 // written yet.
 bool run_swap(const SwapHost &p, const uint8_t *img, int W, int H, int a, int b, int64_t nv,
               int32_t *d0, int32_t *d1) {
-  const int w = 2 * p.cx + 1;
+  const int w = 2 * p.cx + 1, h = 2 * p.cy + 1, nd = 2 * ((W + 63) / 64);
+  const std::vector<uint32_t> rows = packed_rows(img, W, H, nd);
+  // the window around a and around b per phase, in words of 32 columns as k_swap_near writes them
+  std::vector<uint8_t> win[2][2];
+  for (int side = 0; side < 2; ++side) {
+    const int sx = (side ? b : a) % W, sy = (side ? b : a) / W;
+    for (auto &v : win[side]) v.resize((size_t)w * h);
+    for (int r = 0; r < h; ++r) {
+      const int y = (sy + r - p.cy + H) % H;
+      int x = (sx - p.cx + W) % W;
+      for (int w0 = 0; w0 < w; w0 += 32, x = (x + 32) % W) {
+        const uint32_t v = row_word(rows.data() + (size_t)y * nd, nd, W, x);
+        const uint32_t v1 = v | (y == b / W ? every((b % W - x + W) % W, W) : 0u);
+        const uint32_t v0 = ~v | (y == a / W ? every((a % W - x + W) % W, W) : 0u);
+        for (int t = 0; t < 32 && w0 + t < w; ++t) {
+          win[side][1][(size_t)r * w + w0 + t] = v1 >> t & 1;
+          win[side][0][(size_t)r * w + w0 + t] = v0 >> t & 1;
+        }
+      }
+    }
+  }
   std::vector<int> seen((size_t)nv, 0);
   std::vector<uint8_t> val((size_t)p.slots);
   for (const SwapSector &s : p.sectors) {
     std::vector<int> cnt((size_t)4 * 64 * s.ntiles, 0);
     for (int side = 0; side < 2; ++side)
       for (int ph = 0; ph < 2; ++ph) {
-        const int c = side ? b : a, x0 = c % W, y0 = c / W;
         int slot = 0;
         val[slot++] = 0;
         for (int i = 0; i < s.npix; ++i) {
           const uint32_t at = p.pix[s.pix0 + i];
-          if (at >= (uint32_t)(w * (2 * p.cy + 1))) return false;
-          const int x = (x0 + (int)(at % w) - p.cx + 2 * W) % W;
-          const int y = (y0 + (int)(at / w) - p.cy + 2 * H) % H;
-          const int q = y * W + x;
-          if (slot >= p.slots) return false;
-          val[slot++] = ph ? (img[q] || q == b) : (!img[q] || q == a);
+          if (at >= (uint32_t)(w * h) || slot >= p.slots) return false;
+          val[slot++] = win[side][ph][at];
         }
         for (int l = 1; l < kSwapLevels; ++l) {
           const int done = slot;

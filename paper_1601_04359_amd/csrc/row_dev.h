@@ -4,6 +4,8 @@
 
 #include <stdint.h>
 
+#include <vector>
+
 #include <hip/hip_runtime.h>
 
 namespace lpf {
@@ -53,6 +55,42 @@ __host__ __device__ __forceinline__ int word_start(int W, int e, bool mirror) {
     if (s < 0) s = (s % W + W) % W;
   }
   return s;
+}
+
+// 32 pixels of a row of nd dwords (even) from column x on, periodic.  One 8-byte load, and one more
+// for the lanes whose pixels go on at the row's start: with 64 candidates per wave every load is
+// 64 cache lines.
+struct __attribute__((packed, aligned(4))) Dwords2 {
+  uint64_t v;
+};
+__host__ __device__ __forceinline__ uint32_t row_word(const uint32_t *__restrict__ row, int nd, int W, int x) {
+  const int e = x >> 5 < nd - 2 ? x >> 5 : nd - 2;
+  const uint64_t w = ((const Dwords2 *)(row + e))->v;
+  uint32_t v = (uint32_t)(w >> (x - 32 * e));
+  const int n = W - x;
+  if (n >= 32) return v;
+  if (W >= 32) return (v & ((1u << n) - 1u)) | (row[0] << n);
+  v &= (1u << n) - 1u;
+  const uint32_t all = row[0] & ((1u << W) - 1u);
+  for (int t = n; t < 32; t += W) v |= all << t;
+  return v;
+}
+// Bits t, t + W, ... of a word.
+__host__ __device__ __forceinline__ uint32_t every(int t, int W) {
+  if (W >= 32) return t < 32 ? 1u << t : 0u;
+  uint32_t v = 0;
+  for (; t < 32; t += W) v |= 1u << t;
+  return v;
+}
+// A byte image as packed rows of wpr dwords, the bits past W of each row set: they are not part of the
+// image, and the host runs have to get by without them as the kernels do.
+inline std::vector<uint32_t> packed_rows(const uint8_t *img, int W, int H, int wpr) {
+  std::vector<uint32_t> rows((size_t)H * wpr, 0);
+  for (int y = 0; y < H; ++y)
+    for (int x = 0; x < 32 * wpr; ++x)
+      if (x >= W || img[(size_t)y * W + x])
+        rows[(size_t)y * wpr + (x >> 5)] |= 1u << (x & 31);
+  return rows;
 }
 
 // Byte address of a word of the workgroup's LDS.
