@@ -361,17 +361,13 @@ bool fixed_shape(lpf_ctx c, int W, int H, int cx, int cy, FixedShape &f, std::st
 }
 
 // Tile shape of the chain walk: rows staged in LDS, or (rows_in_memory) read from the extended
-// image in device memory.
+// image in device memory.  The autotuner's shapes are the cover kernel's (any R, other budgets): they
+// are not this walk's, which has R = 1, 2, 4, 8 and 16.
 bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, bool rows_in_memory, FullShape &sh,
                   std::string &why) {
   const int swd = (W + 31) / 32;
-  const TunedShape *tuned = nullptr;
-  auto tk = c->tuned.find(std::make_tuple(W, H, cx, cy));
-  if (tk != c->tuned.end()) tuned = &tk->second;
-  int fR = c->force_R ? c->force_R : (tuned ? tuned->R : 0);
-  int fW = c->force_wpg ? c->force_wpg : (tuned ? tuned->wpg : 0);
-  int fL = c->force_lds ? c->force_lds : (tuned ? tuned->lds : 0);
-  // up to 16 words per lane (the autotuner's choice at W = 128, 256, 512 and 1024)
+  const int fR = c->force_R, fW = c->force_wpg, fL = c->force_lds;
+  // up to 16 words per lane
   int R = fR ? fR : std::min(16, next_pow2(swd));
   int S = c->force_S ? c->force_S : next_pow2((swd + R - 1) / R);
   if (S > 64) {
