@@ -298,7 +298,9 @@ lpf_status lpf_batch(lpf_ctx ctx, const uint64_t *bits_pool, const lpf_image_des
 lpf_status lpf_autotune_full(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
                              unsigned phase_mask, void *stream, double *best_ms);
 
-/* The shape recorded by lpf_autotune_full for W, H, cx, cy (host outputs, each may be NULL).
+/* The shape recorded by lpf_autotune_full for W, H, cx, cy (host outputs, each may be NULL), as
+ * lpf_set_full_shape takes it: *R is 0 (automatic) where the automatic plan was the fastest and its
+ * words per lane are not a power of two.
  * Errors: LPF_E_INVAL when none was recorded. */
 lpf_status lpf_get_tuned_shape(lpf_ctx ctx, int W, int H, int cx, int cy, int *R,
                                int *waves_per_group, int *lds_bytes);

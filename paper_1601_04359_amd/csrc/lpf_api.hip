@@ -110,8 +110,11 @@ struct CoverPlan {
   void *mem = nullptr;        // one device allocation behind every table
 };
 
+// The autotuner's choice: the shape's fields to fix (all 0: the automatic plan), and what
+// lpf_get_tuned_shape reports.
 struct TunedShape {
-  int R = 0, S = 0, wpg = 0, lds = 0;
+  int R = 0, wpg = 0, lds = 0;
+  int show_R = 0, show_wpg = 0, show_lds = 0;
   double ms = 0.0;
 };
 
@@ -338,11 +341,7 @@ bool fixed_shape(lpf_ctx c, int W, int H, int cx, int cy, FixedShape &f, std::st
   f = FixedShape{c->force_R, c->force_S, c->force_wpg, c->force_lds};
   auto tk = c->tuned.find(std::make_tuple(W, H, cx, cy));
   if (tk != c->tuned.end()) {
-    // the tuned lanes go together: a forced R or S replaces both
-    if (!f.R && !f.S) {
-      f.R = tk->second.R;
-      f.S = tk->second.S;
-    }
+    if (!f.R && !f.S) f.R = tk->second.R;  // forced lanes replace the tuned ones
     if (!f.wpg) f.wpg = tk->second.wpg;
     if (!f.lds) f.lds = tk->second.lds;
   }
@@ -2638,22 +2637,19 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
       }
     }
     if (!ok || ms_best >= best.ms) return;
-    best.R = R;
-    best.S = 0;
-    best.wpg = wpg;
-    best.lds = lds;
-    best.ms = ms_best;
-    if (R == 0) {  // the automatic plan: the fields it chose
+    TunedShape t{R, wpg, lds, R, wpg, lds, ms_best};
+    if (R == 0) {
+      std::lock_guard<std::mutex> lk(c->mu);
       auto it = c->cover_plans.find({W, H, cx, cy, 0, 0, 0, 0});
-      if (it == c->cover_plans.end() || !it->second.ok) {
-        best.ms = 1e30;
-        return;
-      }
-      best.R = it->second.sh.R;
-      best.S = it->second.sh.S;
-      best.wpg = it->second.sh.wpg;
-      best.lds = it->second.sh.lds;
+      if (it == c->cover_plans.end() || !it->second.ok) return;
+      // what the automatic plan chose; its R where lpf_set_full_shape gives the same lanes for it
+      const CoverShape &sh = it->second.sh;
+      const bool same = sh.R == next_pow2(sh.R) && sh.S == next_pow2((swd + sh.R - 1) / sh.R);
+      t.show_R = same ? sh.R : 0;
+      t.show_wpg = sh.wpg;
+      t.show_lds = sh.lds;
     }
+    best = t;
   };
   for (int R : {0, 2, 4, 8, 16}) {
     if (R > 2 * next_pow2(swd) && R > 2) continue;
@@ -2690,9 +2686,9 @@ lpf_status lpf_get_tuned_shape(lpf_ctx c, int W, int H, int cx, int cy, int *R, 
   std::lock_guard<std::mutex> lk(c->mu);
   auto it = c->tuned.find(std::make_tuple(W, H, cx, cy));
   if (it == c->tuned.end()) return fail(LPF_E_INVAL, "lpf_get_tuned_shape: not tuned");
-  if (R) *R = it->second.R;
-  if (wpg) *wpg = it->second.wpg;
-  if (lds_bytes) *lds_bytes = it->second.lds;
+  if (R) *R = it->second.show_R;
+  if (wpg) *wpg = it->second.show_wpg;
+  if (lds_bytes) *lds_bytes = it->second.show_lds;
   return LPF_OK;
 }
 

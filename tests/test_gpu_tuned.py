@@ -34,3 +34,19 @@ def test_chain_walks_after_tuning(W, H, cx, cy):
         assert torch.equal(got, ref)
         ctx.set_full_shape(0, 0, 0, 1)  # rows in device memory
         assert torch.equal(ctx.full(bits, W, H, cx, cy), ref)
+
+
+# 8224 x 2300: rows fit LDS with 4 words per lane only, in 65 tiles across; a fixed R of 4 would need
+# more than 64 lanes per row
+@pytest.mark.parametrize("W,H,cx,cy", [(96, 64, 16, 16), (256, 90, 30, 30), (333, 100, 30, 20),
+                                       (700, 60, 20, 20), (8224, 2300, 1, 2250)])
+def test_recorded_shape_is_accepted(W, H, cx, cy):
+    import torch
+    from paper_1601_04359_amd import Context
+    with Context(0) as ctx:
+        bits, ref = _tuned(ctx, W, H, cx, cy)
+        counts, _, _, _ = ctx.batch([(bits, W, H, cx, cy)], 3, 0)
+        assert torch.equal(counts[:ref.numel()].view(ref.shape), ref)
+        R, wpg, lds = ctx.tuned_shape(W, H, cx, cy)
+        ctx.set_full_shape(R, 0, wpg, lds)
+        assert torch.equal(ctx.full(bits, W, H, cx, cy), ref)
