@@ -200,7 +200,7 @@ lpf_status lpf_peak_probe(lpf_ctx ctx, int kind, int64_t iters, int nwg, uint32_
  * An interchange of two pixels of the same phase, a == b, or an index outside [0, W*H) gives an
  * all-zero row (indices live on the device and are not checked on the host).  Only the
  * translations whose segment covers a or b are recounted: from shared segments (cutoffs up to 126;
- * per-cutoff tables of at most 256 MB built on the first call, and scratch of at most 64 MB), by
+ * per-cutoff tables of at most 256 MB built on the first call, and 64 MB of scratch), by
  * offset rows (cutoffs up to 255, a table of at most 256 MB likewise) or by runs of start columns
  * (any cutoff; see lpf_set_delta_method).  Same requirements on W, H, cx, cy, phase_mask as
  * lpf_full; 0 <= n <= 2^24.  Errors: LPF_E_INVAL, LPF_E_NOMEM, LPF_E_DEVICE. */

@@ -238,6 +238,8 @@ struct lpf_ctx_s {
   std::map<std::string, struct BatchPlan *> batch_plans;
   uint64_t batch_clock = 0;  // use counter of the cached batch plans
   DevBuf ext, ext3, s2ext, s2acc, sext, rank_buf;
+  DevBuf swap_near;  // windows of lpf_delta_swap: kSwapNearMax bytes from its first call on, so that
+                     // a captured call's scratch stays where it is whatever calls follow
   int s2half = 0;  // lpf_s2: which half of s2acc the next call accumulates into
   std::mutex mu;
   // shape override (autotuner): R, S, wpg, lds budget; 0 = automatic
@@ -1379,6 +1381,7 @@ void lpf_ctx_destroy(lpf_ctx c) {
     }
     c->ext.release();
     c->ext3.release();
+    c->swap_near.release();
     c->s2ext.release();
     c->s2acc.release();
     c->sext.release();
@@ -1606,8 +1609,8 @@ lpf_status lpf_delta_swap(lpf_ctx c, const uint64_t *bits, int W, int H, int cx,
     SwapPlan *sp = nullptr;
     if ((st = get_swap_plan(c, cx, cy, sp)) != LPF_OK) return st;
     if (sp->ok) {
-      const size_t need = swap_near_bytes(cx, cy, phase_mask) * swap_batch(cx, cy, phase_mask, n);
-      if ((e = c->ext3.ensure(need)) != hipSuccess) return hip_fail(e, "lpf_delta_swap: scratch");
+      if ((e = c->swap_near.ensure(kSwapNearMax)) != hipSuccess)
+        return hip_fail(e, "lpf_delta_swap: scratch");
       SwapLaunch L = sp->L;
       L.bits = bits;
       L.W = W;
@@ -1616,7 +1619,7 @@ lpf_status lpf_delta_swap(lpf_ctx c, const uint64_t *bits, int W, int H, int cx,
       L.cy = cy;
       L.cand = reinterpret_cast<const int2 *>(swaps);
       L.K = n;
-      L.near = (uint2 *)c->ext3.p;
+      L.near = (uint2 *)c->swap_near.p;
       L.phase_mask = phase_mask;
       L.nv = (int)lpf_num_vectors(cx, cy);
       L.delta_out = delta;

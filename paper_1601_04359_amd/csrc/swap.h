@@ -66,15 +66,14 @@ struct SwapLaunch {
   int nv;
   int32_t *delta_out;
 };
-constexpr size_t kSwapNearMax = (size_t)64 << 20;  // scratch of one launch
+constexpr size_t kSwapNearMax = (size_t)64 << 20;  // scratch of a context
 inline size_t swap_near_bytes(int cx, int cy, unsigned phase_mask) {
   return (size_t)(phase_mask == 3 ? 2 : 1) * (2 * cx + 1) * (2 * cy + 1) * sizeof(uint2);
 }
-// Groups of 32 candidates per launch (multiples of 8, so that calls with about as many candidates
-// use the same scratch).
+// Groups of 32 candidates per launch.
 inline int swap_batch(int cx, int cy, unsigned phase_mask, int K) {
   const int fit = (int)(kSwapNearMax / swap_near_bytes(cx, cy, phase_mask));
-  return std::min({(K + 255) / 256 * 8, fit, 32768});  // a grid's y extent
+  return std::min({(K + 31) / 32, fit, 32768});  // a grid's y extent
 }
 hipError_t launch_swap(const SwapLaunch &L, hipStream_t stream);
 
