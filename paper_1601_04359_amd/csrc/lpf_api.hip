@@ -1605,7 +1605,15 @@ lpf_status lpf_delta_swap(lpf_ctx c, const uint64_t *bits, int W, int H, int cx,
   if (!g.ok) return fail(LPF_E_DEVICE, "lpf_delta_swap: cannot select the context's device");
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
-  if (!c->force_run_delta) {
+  // A few vectors and many candidates: a workgroup of k_swap has lanes for 256 vectors, one of the
+  // offset rows for 64 candidates.  Offset rows / shared segments, both phases: 100 000 candidates at
+  // cutoff (0, 0) 14.6 / 40.7 us, (0, 5) 33.6 / 64.9, (2, 2) 41.3 / 56.9; 32 768 at (0, 5) 20.2 / 27.9,
+  // (2, 2) 20.2 / 23.4, (2, 3) 26.4 / 23.8; 65 536 at (2, 3) 34.4 / 41.2; 200 000 at (3, 3) 112 / 109,
+  // (4, 4) 191 / 120.  Up to 16 384 candidates shared segments are as fast or faster.
+  const int64_t vectors = lpf_num_vectors(cx, cy) * nph_of(phase_mask);
+  const bool few = std::max(cx, cy) <= 5 &&
+                   ((vectors <= 26 && n > 16384) || (vectors <= 36 && n > 49152));
+  if (!c->force_run_delta && !few) {
     SwapPlan *sp = nullptr;
     if ((st = get_swap_plan(c, cx, cy, sp)) != LPF_OK) return st;
     if (sp->ok) {
