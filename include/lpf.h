@@ -283,9 +283,10 @@ typedef struct {
  * fit in LDS follow one by one.  descs (host): n_images (<= 65535) descriptors; every image follows
  * lpf_full's rules.  The first call for a set of (descriptors, phases, layout) builds launch plans
  * and the item list; the context keeps the 16 most recently used sets (releasing one waits for
- * the device).  bits_pool and counts_pool may differ from call to call.  Calls on one context
- * must not overlap.  Shapes tuned by lpf_autotune_full for an image size are used.  Errors:
- * LPF_E_INVAL (a descriptor, naming its index), LPF_E_UNSUPPORTED, LPF_E_NOMEM, LPF_E_DEVICE. */
+ * the device) and those of calls captured in a graph.  bits_pool and counts_pool may differ from
+ * call to call.  Calls on one context must not overlap.  Shapes tuned by lpf_autotune_full for an
+ * image size are used.  Errors: LPF_E_INVAL (a descriptor, naming its index), LPF_E_UNSUPPORTED,
+ * LPF_E_NOMEM, LPF_E_DEVICE. */
 lpf_status lpf_batch(lpf_ctx ctx, const uint64_t *bits_pool, const lpf_image_desc *descs,
                      int n_images, unsigned phase_mask, int out_layout, uint32_t *counts_pool,
                      void *stream);

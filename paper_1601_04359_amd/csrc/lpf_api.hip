@@ -78,6 +78,13 @@ struct DevBuf {
   }
 };
 
+// True while stream s is being captured into a graph: what the call uses has to stay for the graph's
+// replays.  (The legacy stream cannot be captured.)
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // A buffer that is filled with zeros on stream s when (re)allocated; never called while s is
 // being captured.
 hipError_t ensure_zeroed(DevBuf &b, size_t n, hipStream_t s) {
@@ -297,7 +304,7 @@ constexpr int64_t kRecBudget = (int64_t)16 << 30;
 
 // The launches of one lpf_batch call: its images' plans and the work items, most work first.
 // Keyed by the descriptors, phase mask, layout and shape overrides, not by the caller's buffers.
-// At most kMaxBatchPlans are kept; the least recently used is released first.
+// At most kMaxBatchPlans are kept, the least recently used is released first; a captured call's stays.
 struct BatchPlan {
   // one launch per workgroup size: 16 waves for images whose rows need more than half of a CU's
   // LDS, 8 for the others
@@ -312,7 +319,9 @@ struct BatchPlan {
   int n_images = 0;
   bool split = false;     // some image's groups are split: its counts are zeroed first
   std::vector<int> glob;  // images whose rows do not fit in LDS
+  DevBuf ext;             // their rows, one image after the other
   uint64_t last_use = 0;
+  bool captured = false;
 };
 constexpr size_t kMaxBatchPlans = 16;
 
@@ -331,6 +340,7 @@ void free_batch_plan(BatchPlan *b) {
   (void)hipFree(b->imgs);
   (void)hipFree(b->bits_off);
   (void)hipFree(b->counts_off);
+  b->ext.release();
   delete b;
 }
 
@@ -1402,18 +1412,18 @@ lpf_status lpf_pack(lpf_ctx c, const uint8_t *img, int W, int H, uint64_t *bits,
 
 namespace {
 // The counts of one image by the chain walk on rows in device memory, for rows that do not fit
-// in LDS (arguments checked, context locked).
-lpf_status full_from_memory(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int cy,
-                            unsigned phase_mask, int out_layout, uint32_t *counts, hipStream_t s,
-                            bool skip, const uint64_t *sample) {
+// in LDS (arguments checked, context locked); rows: scratch.
+lpf_status full_from_memory(lpf_ctx c, DevBuf &rows, const uint64_t *bits, int W, int H, int cx,
+                            int cy, unsigned phase_mask, int out_layout, uint32_t *counts,
+                            hipStream_t s, bool skip, const uint64_t *sample) {
   FullPlan *plan = nullptr;
   lpf_status st = get_full_plan(c, W, H, cx, cy, plan);
   if (st != LPF_OK) return st;
   const FullShape &sh = plan->sh;
   hipError_t e;
-  if ((e = c->ext.ensure((size_t)sh.lds_rows * sh.we * sizeof(uint32_t))) != hipSuccess)
+  if ((e = rows.ensure((size_t)sh.lds_rows * sh.we * sizeof(uint32_t))) != hipSuccess)
     return hip_fail(e, "lpf_full: scratch");
-  uint32_t *ext = (uint32_t *)c->ext.p;
+  uint32_t *ext = (uint32_t *)rows.p;
   if ((e = launch_ext(bits, W, H, sh.we, ext, s, sh.lds_rows)) != hipSuccess)
     return hip_fail(e, "lpf_full: ext");
   FullImg I = make_img(*plan, ext, counts, W, H, cx, cy, out_layout);
@@ -1453,8 +1463,9 @@ lpf_status full_impl(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int 
   CoverPlan *cp = nullptr;
   lpf_status st = get_cover_plan(c, W, H, cx, cy, f, cp);
   if (st != LPF_OK) return st;
-  if (!cp->ok) return full_from_memory(c, bits, W, H, cx, cy, phase_mask, out_layout, counts, s,
-                                       skip, sample);
+  if (!cp->ok)
+    return full_from_memory(c, c->ext, bits, W, H, cx, cy, phase_mask, out_layout, counts, s, skip,
+                            sample);
   hipError_t e;
   const uint32_t *starts = nullptr;
   if (sample) {
@@ -2566,12 +2577,16 @@ lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc 
   }
   auto it = c->batch_plans.find(key);
   if (it == c->batch_plans.end() && c->batch_plans.size() >= kMaxBatchPlans) {
-    auto lru = c->batch_plans.begin();
+    auto lru = c->batch_plans.end();
     for (auto j = c->batch_plans.begin(); j != c->batch_plans.end(); ++j)
-      if (j->second->last_use < lru->second->last_use) lru = j;
-    (void)hipDeviceSynchronize();  // its last launch may still run on any stream
-    free_batch_plan(lru->second);
-    c->batch_plans.erase(lru);
+      if (!j->second->captured &&
+          (lru == c->batch_plans.end() || j->second->last_use < lru->second->last_use))
+        lru = j;
+    if (lru != c->batch_plans.end()) {
+      (void)hipDeviceSynchronize();  // its last launch may still run on any stream
+      free_batch_plan(lru->second);
+      c->batch_plans.erase(lru);
+    }
   }
   if (it == c->batch_plans.end()) {
     BatchPlan *b = nullptr;
@@ -2581,6 +2596,7 @@ lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc 
   }
   BatchPlan &b = *it->second;
   b.last_use = ++c->batch_clock;
+  b.captured = b.captured || capturing(s);
   if (b.split) {
     hipError_t e = launch_cover_zero(b.imgs, b.counts_off, b.n_images, phase_mask, counts_pool, s);
     if (e != hipSuccess) return hip_fail(e, "lpf_batch: zero");
@@ -2592,8 +2608,9 @@ lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc 
   }
   for (int i : b.glob) {
     const lpf_image_desc &d = descs[i];
-    lpf_status st = full_from_memory(c, bits_pool + d.bits_off, d.W, d.H, d.cx, d.cy, phase_mask,
-                                     out_layout, counts_pool + d.counts_off, s, false, nullptr);
+    lpf_status st = full_from_memory(c, b.ext, bits_pool + d.bits_off, d.W, d.H, d.cx, d.cy,
+                                     phase_mask, out_layout, counts_pool + d.counts_off, s, false,
+                                     nullptr);
     if (st != LPF_OK) return st;
   }
   return LPF_OK;

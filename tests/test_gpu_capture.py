@@ -68,3 +68,33 @@ def test_delta_scratch_stays():
             _junk()
         _replays(graph, out, ref, between)
         del graph
+
+
+def test_batch_tables_stay():
+    # more sets than the context keeps, and images with rows in device memory of growing sizes
+    import torch
+    from paper_1601_04359_amd import Context, _abi
+    print("[gpu] capture batch", flush=True)
+    with Context(0) as ctx:
+        def items(k):
+            sizes = [(48 + k, 40, 12, 10), (64, 33 + k, 20, 16), (70 + 60 * k, 50 + 40 * k, 9, 9)]
+            return [(ctx.pack(torch.from_numpy(wl.random_binary(W, H, 0.7, W + H)).cuda()), W, H, cx, cy)
+                    for W, H, cx, cy in sizes]
+        for lds in (0, 1):  # staged in LDS, in device memory
+            ctx.set_full_shape(0, 0, 0, lds)
+            first = items(0)
+            ref, offs, pool, descs = ctx.batch(first, 3, 0)
+            counts = torch.empty_like(ref)
+
+            def call():
+                _abi.lpf_batch(ctx.handle, pool, descs, 3, 0, counts)
+                return counts
+            graph, out = _capture(call)
+
+            def between(i):
+                for k in range(1 + 9 * i, 10 + 9 * i):
+                    ctx.batch(items(k), 3, 0)
+                torch.cuda.synchronize()
+                _junk()
+            _replays(graph, out, ref, between)
+            del graph
