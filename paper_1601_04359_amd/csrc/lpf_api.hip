@@ -2633,9 +2633,15 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
       return hip_fail(e, "lpf_autotune_full: allocation");
   }
   const int saved[4] = {c->force_R, c->force_S, c->force_wpg, c->force_lds};
+  auto same_image = [&](const std::array<int, 8> &k) {
+    return k[0] == W && k[1] == H && k[2] == cx && k[3] == cy;
+  };
+  std::vector<std::array<int, 8>> had;  // this image's plans before the tuning
   {
     std::lock_guard<std::mutex> lk(c->mu);
     c->tuned.erase(std::make_tuple(W, H, cx, cy));
+    for (const auto &kv : c->cover_plans)
+      if (same_image(kv.first)) had.push_back(kv.first);
   }
   TunedShape best{};
   best.ms = 1e30;
@@ -2697,6 +2703,21 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipFree(tmp);
+  }
+  {
+    // the plans that were made here and lost (each event above was waited for)
+    std::lock_guard<std::mutex> lk(c->mu);
+    DeviceGuard g(c->dev);
+    const std::array<int, 8> kept = {W, H, cx, cy, best.R, 0, best.wpg, best.lds};
+    for (auto it = c->cover_plans.begin(); it != c->cover_plans.end();) {
+      if (same_image(it->first) && it->first != kept &&
+          std::find(had.begin(), had.end(), it->first) == had.end()) {
+        (void)hipFree(it->second.mem);
+        it = c->cover_plans.erase(it);
+      } else {
+        ++it;
+      }
+    }
   }
   if (best.ms >= 1e29) return fail(LPF_E_UNSUPPORTED, "lpf_autotune_full: no shape ran");
   {

@@ -50,3 +50,22 @@ def test_recorded_shape_is_accepted(W, H, cx, cy):
         R, wpg, lds = ctx.tuned_shape(W, H, cx, cy)
         ctx.set_full_shape(R, 0, wpg, lds)
         assert torch.equal(ctx.full(bits, W, H, cx, cy), ref)
+
+
+def test_losing_plans_are_released():
+    # 512^2, cutoff 255: a plan is about 8 MB, the autotuner makes up to 21 of them
+    import torch
+    from paper_1601_04359_amd import Context
+    W, c = 512, 255
+    with Context(0) as ctx:
+        bits = ctx.pack(torch.from_numpy(wl.boolean_disks(W, W, 9.0, 0.5, 1)).cuda())
+        ref = ctx.full(bits, W, W, c, c)
+        print("[gpu] tuned: memory", flush=True)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        for _ in range(2):
+            ctx.autotune(bits, W, W, c, c)
+            assert torch.equal(ctx.full(bits, W, W, c, c), ref)
+        torch.cuda.synchronize()
+        # the plan from before, the chosen one, chain tables of shapes that do not fit LDS
+        assert before - torch.cuda.mem_get_info()[0] < 40 << 20
