@@ -101,7 +101,15 @@ struct FullPlan {
   int32_t *bin_off = nullptr;   // device, nbins + 1
   int64_t nv = 0;
   int64_t walk = 0, path_pixels = 0;  // pixels walked per start word; M_c
-  std::vector<int64_t> bin_cost;  // host: cost of each bin (pixels + overhead per member)
+};
+
+// Device memory of a plan (one allocation behind its tables), for trim_plans below.
+struct PlanMem {
+  void *p = nullptr;
+  size_t bytes = 0;
+  uint64_t last_use = 0;
+  int sets = 0;           // batch sets that read it
+  bool captured = false;  // read by a call that was captured in a graph
 };
 
 // Cover plan of an image size and cutoff (plan_cover.hip) on the device.  ok = false: its rows do
@@ -114,7 +122,7 @@ struct CoverPlan {
   int2 *items = nullptr;  // device: work items of one phase, most work first
   std::vector<int2> host_items;
   std::vector<int64_t> cost;  // per item
-  void *mem = nullptr;        // one device allocation behind every table
+  PlanMem mem;
 };
 
 // The autotuner's choice: the shape's fields to fix (all 0: the automatic plan), and what
@@ -145,16 +153,16 @@ struct DiagPlan {
   bool ok = false;
 };
 
-// Prefix-tree plan of the volume evaluation (plan_cover3.hip), its tables in one allocation.
+// Prefix-tree plan of the volume evaluation (plan_cover3.hip).
 struct Cover3Plan {
-  void *mem = nullptr;
+  PlanMem mem;
   Cover3Launch L{};
   bool ok = false;
 };
 
-// Tables of the interchange delta by shared segments (plan_swap.hip), in one allocation.
+// Tables of the interchange delta by shared segments (plan_swap.hip).
 struct SwapPlan {
-  void *mem = nullptr;
+  PlanMem mem;
   SwapLaunch L{};  // the tables' addresses and sizes
   bool ok = false;
 };
@@ -242,6 +250,9 @@ struct lpf_ctx_s {
   };
   std::map<std::tuple<int, int, int>, Vec3> vec3;
   std::map<std::array<int, 6>, Cover3Plan> cover3_plans;  // (W, H, D, cx, cy, cz)
+  // the memory of cover_plans, cover3_plans and swap_plans, and a clock of their uses
+  size_t plan_bytes = 0;
+  uint64_t plan_clock = 0;
   std::map<std::string, struct BatchPlan *> batch_plans;
   uint64_t batch_clock = 0;  // use counter of the cached batch plans
   DevBuf ext, ext3, s2ext, s2acc, sext, rank_buf;
@@ -320,6 +331,7 @@ struct BatchPlan {
   bool split = false;     // some image's groups are split: its counts are zeroed first
   std::vector<int> glob;  // images whose rows do not fit in LDS
   DevBuf ext;             // their rows, one image after the other
+  std::vector<std::array<int, 8>> plans;  // the cover plans that imgs points into
   uint64_t last_use = 0;
   bool captured = false;
 };
@@ -334,8 +346,9 @@ struct lpf_cnn_s {
 
 namespace {
 
-void free_batch_plan(BatchPlan *b) {
+void free_batch_plan(lpf_ctx c, BatchPlan *b) {
   if (!b) return;
+  for (const auto &k : b->plans) --c->cover_plans.find(k)->second.mem.sets;
   for (auto &l : b->launches) (void)hipFree(l.items);
   (void)hipFree(b->imgs);
   (void)hipFree(b->bits_off);
@@ -507,14 +520,57 @@ lpf_status get_full_plan(lpf_ctx c, int W, int H, int cx, int cy, FullPlan *&pla
     (void)hipFree(p.bin_off);
     return hip_fail(e, "lpf_full: plan upload");
   }
-  p.bin_cost = bp.cost;
   auto res = c->full_plans.emplace(key, p);
   plan = &res.first->second;
   return LPF_OK;
 }
 
-// Vectors above which the chain walk is used: a cover plan takes about 40 bytes of records per
-// vector and its construction grows with the summed path lengths.
+// Device memory that a context's plans may take together: a plan is 38 bytes per vector at cutoff 128
+// (1.3 MB), 68 at cutoff 512 (36 MB), 102 at the whole domain of 1448 x 1448 (430 MB).
+constexpr size_t kPlanBytes = (size_t)4 << 30;
+
+// Releases the plans used longest ago until `need` more bytes fit kPlanBytes.  Plans that a batch set
+// or a captured call reads stay, even if the rest is not enough.
+void trim_plans(lpf_ctx c, size_t need) {
+  bool waited = false;
+  while (c->plan_bytes + need > kPlanBytes) {
+    auto oldest = [](auto &plans) {
+      auto lru = plans.end();
+      for (auto it = plans.begin(); it != plans.end(); ++it) {
+        const PlanMem &m = it->second.mem;
+        if (m.p && !m.sets && !m.captured &&
+            (lru == plans.end() || m.last_use < lru->second.mem.last_use))
+          lru = it;
+      }
+      return lru;
+    };
+    const auto a = oldest(c->cover_plans);
+    const auto b = oldest(c->cover3_plans);
+    const auto d = oldest(c->swap_plans);
+    const uint64_t ta = a == c->cover_plans.end() ? UINT64_MAX : a->second.mem.last_use;
+    const uint64_t tb = b == c->cover3_plans.end() ? UINT64_MAX : b->second.mem.last_use;
+    const uint64_t td = d == c->swap_plans.end() ? UINT64_MAX : d->second.mem.last_use;
+    const uint64_t t = std::min({ta, tb, td});
+    if (t == UINT64_MAX) return;
+    if (!waited) (void)hipDeviceSynchronize();  // a last call may still read it on any stream
+    waited = true;
+    auto drop = [&](auto &plans, auto it) {
+      (void)hipFree(it->second.mem.p);
+      c->plan_bytes -= it->second.mem.bytes;
+      plans.erase(it);
+    };
+    if (t == ta) drop(c->cover_plans, a);
+    else if (t == tb) drop(c->cover3_plans, b);
+    else drop(c->swap_plans, d);
+  }
+}
+// A call on stream s is about to read the plan.
+void use_plan(lpf_ctx c, PlanMem &m, hipStream_t s) {
+  m.last_use = ++c->plan_clock;
+  m.captured = m.captured || capturing(s);
+}
+
+// Vectors above which the chain walk is used: plans of that size take some 400 MB and 5 s.
 constexpr int64_t kCoverVectors = (int64_t)1 << 22;
 
 // The cover plan for an image size and cutoff with the fields of `f` fixed; plan->ok is false when
@@ -548,14 +604,16 @@ lpf_status get_cover_plan(lpf_ctx c, int W, int H, int cx, int cy, const FixedSh
       std::vector<char> all(off[6]);
       for (int i = 0; i < 6; ++i)
         if (len[i]) memcpy(all.data() + off[i], src[i], len[i]);
-      hipError_t e = hipMalloc(&p.mem, off[6]);
+      trim_plans(c, off[6]);
+      hipError_t e = hipMalloc(&p.mem.p, off[6]);
       if (e != hipSuccess) return hip_fail(e, "lpf_full: plan allocation");
-      e = hipMemcpy(p.mem, all.data(), off[6], hipMemcpyHostToDevice);
+      e = hipMemcpy(p.mem.p, all.data(), off[6], hipMemcpyHostToDevice);
       if (e != hipSuccess) {
-        (void)hipFree(p.mem);
+        (void)hipFree(p.mem.p);
         return hip_fail(e, "lpf_full: plan upload");
       }
-      char *m = (char *)p.mem;
+      p.mem.bytes = off[6];
+      char *m = (char *)p.mem.p;
       p.img = CoverImg{(const CoverGroup *)(m + off[0]), (const int32_t *)(m + off[1]),
                        (const int4 *)(m + off[2]),       (const uint32_t *)(m + off[3]),
                        (const MemDesc *)(m + off[4]),    W, H, cx, cy, h.sh.R, h.sh.S, h.nct,
@@ -568,8 +626,9 @@ lpf_status get_cover_plan(lpf_ctx c, int W, int H, int cx, int cy, const FixedSh
       p.ok = true;
     }
     plan = &c->cover_plans.emplace(key, std::move(p)).first->second;
+    c->plan_bytes += plan->mem.bytes;
   } catch (const std::exception &) {
-    (void)hipFree(p.mem);
+    (void)hipFree(p.mem.p);
     return fail(LPF_E_NOMEM, "lpf_full: host memory for the plan");
   }
   return LPF_OK;
@@ -891,14 +950,16 @@ lpf_status get_cover3_plan(lpf_ctx c, int W, int H, int D, int cx, int cy, int c
       for (int i = 0; i < 4; ++i) off[i + 1] = off[i] + (len[i] + 255) / 256 * 256;
       std::vector<char> all(off[4]);
       for (int i = 0; i < 4; ++i) memcpy(all.data() + off[i], src[i], len[i]);
-      hipError_t e = hipMalloc(&p.mem, off[4]);
+      trim_plans(c, off[4]);
+      hipError_t e = hipMalloc(&p.mem.p, off[4]);
       if (e != hipSuccess) return hip_fail(e, "lpf_full3d: plan allocation");
-      e = hipMemcpy(p.mem, all.data(), off[4], hipMemcpyHostToDevice);
+      e = hipMemcpy(p.mem.p, all.data(), off[4], hipMemcpyHostToDevice);
       if (e != hipSuccess) {
-        (void)hipFree(p.mem);
+        (void)hipFree(p.mem.p);
         return hip_fail(e, "lpf_full3d: plan upload");
       }
-      char *m = (char *)p.mem;
+      p.mem.bytes = off[4];
+      char *m = (char *)p.mem.p;
       p.L.sh = h.sh;
       p.L.groups = (const Cover3Group *)(m + off[0]);
       p.L.piece_off = (const int32_t *)(m + off[1]);
@@ -909,8 +970,9 @@ lpf_status get_cover3_plan(lpf_ctx c, int W, int H, int D, int cx, int cy, int c
       p.L.nv = (int)nv;
     }
     plan = &c->cover3_plans.emplace(key, p).first->second;
+    c->plan_bytes += plan->mem.bytes;
   } catch (const std::exception &) {
-    (void)hipFree(p.mem);
+    (void)hipFree(p.mem.p);
     return fail(LPF_E_NOMEM, "lpf_full3d: host memory for the plan");
   }
   return LPF_OK;
@@ -939,14 +1001,16 @@ lpf_status get_swap_plan(lpf_ctx c, int cx, int cy, SwapPlan *&plan) {
       std::vector<char> all(off[7]);
       for (int i = 0; i < 7; ++i)
         if (len[i]) memcpy(all.data() + off[i], src[i], len[i]);
-      hipError_t e = hipMalloc(&p.mem, off[7]);
+      trim_plans(c, off[7]);
+      hipError_t e = hipMalloc(&p.mem.p, off[7]);
       if (e != hipSuccess) return hip_fail(e, "lpf_delta_swap: plan allocation");
-      e = hipMemcpy(p.mem, all.data(), off[7], hipMemcpyHostToDevice);
+      e = hipMemcpy(p.mem.p, all.data(), off[7], hipMemcpyHostToDevice);
       if (e != hipSuccess) {
-        (void)hipFree(p.mem);
+        (void)hipFree(p.mem.p);
         return hip_fail(e, "lpf_delta_swap: plan upload");
       }
-      char *m = (char *)p.mem;
+      p.mem.bytes = off[7];
+      char *m = (char *)p.mem.p;
       p.L.sectors = (const SwapSector *)(m + off[0]);
       p.L.tiles = (const SwapTile *)(m + off[1]);
       p.L.idx = (const int32_t *)(m + off[2]);
@@ -959,8 +1023,9 @@ lpf_status get_swap_plan(lpf_ctx c, int cx, int cy, SwapPlan *&plan) {
       p.ok = true;
     }
     plan = &c->swap_plans.emplace(key, p).first->second;
+    c->plan_bytes += plan->mem.bytes;
   } catch (const std::exception &) {
-    (void)hipFree(p.mem);
+    (void)hipFree(p.mem.p);
     return fail(LPF_E_NOMEM, "lpf_delta_swap: host memory for the plan");
   }
   return LPF_OK;
@@ -1365,15 +1430,15 @@ void lpf_ctx_destroy(lpf_ctx c) {
       (void)hipFree(kv.second.mems);
       (void)hipFree(kv.second.bin_off);
     }
-    for (auto &kv : c->cover_plans) (void)hipFree(kv.second.mem);
-    for (auto &kv : c->batch_plans) free_batch_plan(kv.second);
+    for (auto &kv : c->batch_plans) free_batch_plan(c, kv.second);
+    for (auto &kv : c->cover_plans) (void)hipFree(kv.second.mem.p);
     for (auto &kv : c->delta_plans) {
       (void)hipFree(kv.second.vecs);
       (void)hipFree(kv.second.chunk_off);
       (void)hipFree(kv.second.runs);
     }
-    for (auto &kv : c->cover3_plans) (void)hipFree(kv.second.mem);
-    for (auto &kv : c->swap_plans) (void)hipFree(kv.second.mem);
+    for (auto &kv : c->cover3_plans) (void)hipFree(kv.second.mem.p);
+    for (auto &kv : c->swap_plans) (void)hipFree(kv.second.mem.p);
     for (auto &kv : c->diag_plans) {
       (void)hipFree(kv.second.groups);
       (void)hipFree(kv.second.rows);
@@ -1466,6 +1531,7 @@ lpf_status full_impl(lpf_ctx c, const uint64_t *bits, int W, int H, int cx, int 
   if (!cp->ok)
     return full_from_memory(c, c->ext, bits, W, H, cx, cy, phase_mask, out_layout, counts, s, skip,
                             sample);
+  use_plan(c, cp->mem, s);
   hipError_t e;
   const uint32_t *starts = nullptr;
   if (sample) {
@@ -1628,6 +1694,7 @@ lpf_status lpf_delta_swap(lpf_ctx c, const uint64_t *bits, int W, int H, int cx,
     SwapPlan *sp = nullptr;
     if ((st = get_swap_plan(c, cx, cy, sp)) != LPF_OK) return st;
     if (sp->ok) {
+      use_plan(c, sp->mem, s);
       if ((e = c->swap_near.ensure(kSwapNearMax)) != hipSuccess)
         return hip_fail(e, "lpf_delta_swap: scratch");
       SwapLaunch L = sp->L;
@@ -1765,6 +1832,7 @@ lpf_status lpf_full3d(lpf_ctx c, const uint64_t *bits, int W, int H, int D, int 
   const lpf_status st = get_cover3_plan(c, W, H, D, cx, cy, cz, cp);
   if (st != LPF_OK) return st;
   if (cp->ok) {
+    use_plan(c, cp->mem, (hipStream_t)stream);
     Cover3Launch L = cp->L;
     L.bits = bits;
     L.phase_mask = phase_mask;
@@ -2485,7 +2553,7 @@ lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images
         st = fail(LPF_E_UNSUPPORTED, "lpf_batch: " + why);
       if (st == LPF_OK) st = get_cover_plan(c, d.W, d.H, d.cx, d.cy, f, p);
       if (st != LPF_OK) {
-        free_batch_plan(b);
+        free_batch_plan(c, b);
         return st;
       }
       bits_off[i] = d.bits_off;
@@ -2494,6 +2562,8 @@ lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images
         b->glob.push_back(i);
         continue;
       }
+      b->plans.push_back({d.W, d.H, d.cx, d.cy, f.R, f.S, f.wpg, f.lds});
+      ++p->mem.sets;
       imgs[i] = p->img;
       imgs[i].layout = out_layout;
       b->split = b->split || imgs[i].nsplit > 1;
@@ -2533,11 +2603,11 @@ lpf_status build_batch_plan(lpf_ctx c, const lpf_image_desc *descs, int n_images
       upload(l.items, list);
     }
     if (e != hipSuccess) {
-      free_batch_plan(b);
+      free_batch_plan(c, b);
       return hip_fail(e, "lpf_batch: plan");
     }
   } catch (const std::exception &) {
-    free_batch_plan(b);
+    free_batch_plan(c, b);
     return fail(LPF_E_NOMEM, "lpf_batch: host memory");
   }
   out = b;
@@ -2584,7 +2654,7 @@ lpf_status lpf_batch(lpf_ctx c, const uint64_t *bits_pool, const lpf_image_desc 
         lru = j;
     if (lru != c->batch_plans.end()) {
       (void)hipDeviceSynchronize();  // its last launch may still run on any stream
-      free_batch_plan(lru->second);
+      free_batch_plan(c, lru->second);
       c->batch_plans.erase(lru);
     }
   }
@@ -2712,7 +2782,8 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
     for (auto it = c->cover_plans.begin(); it != c->cover_plans.end();) {
       if (same_image(it->first) && it->first != kept &&
           std::find(had.begin(), had.end(), it->first) == had.end()) {
-        (void)hipFree(it->second.mem);
+        (void)hipFree(it->second.mem.p);
+        c->plan_bytes -= it->second.mem.bytes;
         it = c->cover_plans.erase(it);
       } else {
         ++it;

@@ -75,12 +75,11 @@ struct ChainSet {
 void build_chains(int cx, int cy, ChainSet &out);
 // Chains cut into pieces of at most kSlotWords / 4 members and packed into bins (one workgroup
 // each), longest processing time first: chains in bin order with their members (m0 indexes
-// mems), off[nbins + 1] chain offsets, cost = pixels walked + 3 per member of each bin.
+// mems), off[nbins + 1] chain offsets.
 struct BinPlan {
   std::vector<ChainDesc> chains;
   std::vector<MemDesc> mems;
   std::vector<int32_t> off;
-  std::vector<int64_t> cost;
   int nbins = 0;
 };
 void pack_bins(const ChainSet &all, int64_t nb_want, BinPlan &out);

@@ -195,7 +195,6 @@ void pack_bins(const ChainSet &all, int64_t nb_want, BinPlan &out) {
     }
   }
   out.off[nb] = (int32_t)out.chains.size();
-  out.cost = bload;
 }
 
 }  // namespace lpf
