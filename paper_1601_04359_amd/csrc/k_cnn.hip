@@ -383,22 +383,35 @@ __device__ __forceinline__ void conv_bwd_data(int64_t block, const uint16_t *__r
 // dZ[p][co]; MFMA with M = co, N = ci, K = 16 pixels.
 //
 // Its operands hold four pixels of one channel per lane where memory holds four channels of one
-// pixel: the fragments are loaded as in the forward pass (8 bytes a lane) and transposed by an
-// MFMA with the identity, which copies bf16 values exactly (a value that is not finite reaches the
-// other channels of its pixel as NaN; the loss is not finite then either).  A row's three
-// transposed fragments serve three output rows.  (The gather of single 2-byte values that this
-// replaces took 121 us a layer for 8 images of 256 x 256, this 14.)
+// pixel.  Lane 16 g + 4 a + b loads channels 4 a .. 4 a + 3 of pixel 4 g + b (8 bytes), so that the
+// four lanes of a quad hold a 4 x 4 block, which they transpose among themselves: eight vector
+// operations, whatever values the channels hold.  (A product with the identity is one MFMA and two
+// operations, and as fast, but makes NaN of every channel of a pixel with a value that is not
+// finite.)  A row's three transposed fragments serve three output rows.  (The gather of single
+// 2-byte values that this replaces took 121 us a layer for 8 images of 256 x 256, this 14.)
 constexpr int kWeightStrip = 16;
 constexpr int kWeightBlocks = 512;
 
-__device__ __forceinline__ s4v transpose16(s4v a, s4v eye) {
-  const f4v d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, eye, f4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+// Channel c of pixel b in lane b, c = 0 .. 3, becomes channel b of pixel c.
+__device__ __forceinline__ s4v transpose4(s4v a) {
   union {
-    uint32_t u[2];
     s4v v;
+    uint32_t u[2];
   } o;
-  o.u[0] = __builtin_amdgcn_perm(__float_as_uint(d[1]), __float_as_uint(d[0]), 0x07060302u);
-  o.u[1] = __builtin_amdgcn_perm(__float_as_uint(d[3]), __float_as_uint(d[2]), 0x07060302u);
+  o.v = a;
+  const bool odd = threadIdx.x & 1, upper = threadIdx.x & 2;
+  const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {  // lanes 0 and 1, 2 and 3 exchange halves
+    const uint32_t x = (uint32_t)__builtin_amdgcn_mov_dpp((int)o.u[h], 0xb1, 0xf, 0xf, true);
+    o.u[h] = __builtin_amdgcn_perm(x, o.u[h], sel);
+  }
+  // lanes 0 and 2, 1 and 3 exchange words
+  const uint32_t t0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)o.u[0], 0x4e, 0xf, 0xf, true);
+  const uint32_t t1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)o.u[1], 0x4e, 0xf, 0xf, true);
+  const uint32_t w0 = upper ? t1 : o.u[0], w1 = upper ? o.u[1] : t0;
+  o.u[0] = w0;
+  o.u[1] = w1;
   return o.v;
 }
 
@@ -419,22 +432,20 @@ k_cnn_conv_bwd(const uint16_t *__restrict__ dZ, const uint16_t *__restrict__ X, 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, m = lane & 15;
-  s4v eye;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) eye[j] = (short)(4 * g + j == m ? 0x3f80 : 0);
+  const int chunk = m >> 2, pixel = 4 * g + (m & 3);  // what the lane loads
   f4v acc[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) acc[t] = f4v{0.f, 0.f, 0.f, 0.f};
   float dbl = 0.f;
   const s4v zero = {0, 0, 0, 0};
   for (int64_t i = (int64_t)blockIdx.x * 4 + wave; i < nstrips; i += (int64_t)wb * 4) {
-    const Strip q = strip_of(i, W, H, kWeightStrip, m);
+    const Strip q = strip_of(i, W, H, kWeightStrip, pixel);
     s4v xt[3][3];  // transposed rows y - 1, y, y + 1 (slot: row mod 3)
     auto row = [&](int y, s4v(&t)[3]) {
       s4v a[3];
-      strip_row<C>(X, q, y, W, H, g, a);
+      strip_row<C>(X, q, y, W, H, chunk, a);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) t[d] = transpose16(q.in ? a[d] : zero, eye);
+      for (int d = 0; d < 3; ++d) t[d] = transpose4(q.in ? a[d] : zero);
     };
     row(q.y0 - 1, xt[0]);
     row(q.y0, xt[1]);
@@ -445,9 +456,9 @@ k_cnn_conv_bwd(const uint16_t *__restrict__ dZ, const uint16_t *__restrict__ X, 
         if (r0 + u >= rows) break;
         const int y = q.y0 + r0 + u;
         const s4v z =
-            *reinterpret_cast<const s4v *>(dZ + (q.img + (int64_t)y * W + q.x) * 16 + 4 * g);
+            *reinterpret_cast<const s4v *>(dZ + (q.img + (int64_t)y * W + q.x) * 16 + 4 * chunk);
         row(y + 1, xt[(u + 2) % 3]);
-        const s4v a = transpose16(q.in ? z : zero, eye);
+        const s4v a = transpose4(q.in ? z : zero);
 #pragma unroll
         for (int j = 0; j < 4; ++j) dbl += bf2f((uint16_t)a[j]);
 #pragma unroll
