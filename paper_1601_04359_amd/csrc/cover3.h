@@ -38,6 +38,44 @@ struct Cover3Shape {
   int npieces;       // per group
 };
 
+// The staged cells that one thread of a workgroup writes: dword e of row pr, which is row yh of plane
+// pl; carried forward, not divided out.  For the kernel and for the planner's host run.
+struct Cover3Cell {
+  int e, pr, pl, yh;
+  int dq, dr;
+  __host__ __device__ __forceinline__ Cover3Cell(int thread, int wid, int hh) {
+    constexpr int step = 64 * kCover3Waves;
+    dq = step / wid;
+    dr = step - dq * wid;
+    pr = thread / wid;
+    e = thread - pr * wid;
+    pl = pr / hh;
+    yh = pr - pl * hh;
+  }
+  __host__ __device__ __forceinline__ void next(int wid, int hh) {
+    e += dr;
+    int adv = dq;
+    if (e >= wid) {
+      e -= wid;
+      ++adv;
+    }
+    pr += adv;
+    yh += adv;
+    while (yh >= hh) {
+      yh -= hh;
+      ++pl;
+    }
+  }
+  // The volume's row that is staged there, of a slab from plane Z0 on.
+  __host__ __device__ __forceinline__ size_t row(const Cover3Shape &g, bool down, int Z0) const {
+    int z = Z0 + pl, y = yh - (down ? g.cy : 0);
+    z -= z >= g.D ? g.D : 0;  // cz <= D - 1, cy <= H - 1
+    y += y < 0 ? g.H : 0;
+    y -= y >= g.H ? g.H : 0;
+    return (size_t)z * g.H + y;
+  }
+};
+
 struct Cover3Host {
   Cover3Shape sh{};
   std::vector<Cover3Group> groups;

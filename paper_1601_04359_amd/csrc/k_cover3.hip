@@ -101,34 +101,11 @@ k_cover3(Cover3Shape g, const Cover3Group *__restrict__ groups,
   uint32_t *slots = lds + (g.zb + g.cz) * g.ps + kCoverPad;
   for (int t = tid; t < 2 * kCover3Slots; t += 64 * kCover3Waves) slots[t] = 0u;
   const int HH = g.H + g.cy, wpr = 2 * ((g.W + 63) >> 6);
-  {
-    // cell i = dword e of staged row pr = (plane, y): carried forward, not divided out
-    constexpr int step = 64 * kCover3Waves;
-    const int dq = step / g.wid, dr = step - dq * g.wid;
-    int pr = tid / g.wid, e = tid - pr * g.wid;
-    int pl = pr / HH, yh = pr - pl * HH;
-    const int total = (planes + g.cz) * HH;
-    while (pr < total) {
-      int z = Z0 + pl, y = yh - (gr.down ? g.cy : 0);
-      z -= z >= g.D ? g.D : 0;  // cz <= D - 1, cy <= H - 1
-      y += y < 0 ? g.H : 0;
-      y -= y >= g.H ? g.H : 0;
-      const uint32_t v = periodic32(bits + ((size_t)z * g.H + y) * wpr, g.W,
-                                    word_start(g.W, e, gr.mirror != 0));
-      lds[pl * g.ps + yh * g.rst + e] = flip ^ (gr.mirror ? __builtin_bitreverse32(v) : v);
-      e += dr;
-      int adv = dq;
-      if (e >= g.wid) {
-        e -= g.wid;
-        ++adv;
-      }
-      pr += adv;
-      yh += adv;
-      while (yh >= HH) {
-        yh -= HH;
-        ++pl;
-      }
-    }
+  const int total = (planes + g.cz) * HH;
+  for (Cover3Cell c(tid, g.wid, HH); c.pr < total; c.next(g.wid, HH)) {
+    const uint32_t v = periodic32(bits + c.row(g, gr.down != 0, Z0) * wpr, g.W,
+                                  word_start(g.W, c.e, gr.mirror != 0));
+    lds[c.pl * g.ps + c.yh * g.rst + c.e] = flip ^ (gr.mirror ? bit_reverse(v) : v);
   }
   __syncthreads();
   const int nwb = kCover3Waves / g.npieces, piece = wave / nwb, bw = wave - piece * nwb;

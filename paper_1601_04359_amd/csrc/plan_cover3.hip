@@ -15,6 +15,7 @@
 #include "cover3.h"
 #include "lpf_internal.h"
 #include "parallel.h"
+#include "row_dev.h"
 
 namespace lpf {
 
@@ -305,27 +306,26 @@ namespace {
 // The plan run on the host for one phase, every access checked.  False when one is out of bounds.
 bool run_cover3(const Cover3Host &p, const uint8_t *vol, int phase, uint32_t *counts) {
   const Cover3Shape &s = p.sh;
-  const int rpw = 64 / s.S, SP = s.S * s.P, Q = cover3_rows(s.P, false);
+  const int rpw = 64 / s.S, SP = s.S * s.P, Q = cover3_rows(s.P, false), wpr = 2 * ((s.W + 63) / 64);
+  const std::vector<uint32_t> rows = packed_rows(vol, s.W, s.D * s.H, wpr);
   std::vector<uint32_t> lds(p.lds_bytes / 4);
   const size_t rows_end = lds.size() - 2 * kCover3Slots;
   for (const Cover3Group &g : p.groups) {
     for (int slab = 0; slab < s.nslab; ++slab) {
       const int Z0 = slab * s.zb, planes = std::min(s.zb, s.D - Z0);
-      std::fill(lds.begin(), lds.end(), 0u);
-      for (int z = 0; z < planes + s.cz; ++z)
-        for (int y = 0; y < s.H + s.cy; ++y) {
-          const int vz = (Z0 + z) % s.D, vy = (y - (g.down ? s.cy : 0) + s.H) % s.H;
-          const uint8_t *row = vol + ((size_t)vz * s.H + vy) * s.W;
-          for (int x = 0; x < 32 * s.wid; ++x) {
-            const int vx = g.mirror ? s.W - 1 - x % s.W : x % s.W;
-            const size_t at = (size_t)z * s.ps + (size_t)y * s.rst + (x >> 5);
-            if (at >= rows_end) return false;
-            if ((row[vx] != 0) == (phase != 0)) lds[at] |= 1u << (x & 31);
-          }
+      std::fill(lds.begin(), lds.end(), 0x5a5a5a5au);  // cells that are not staged: any value
+      const int hh = s.H + s.cy, total = (planes + s.cz) * hh;
+      for (int t = 0; t < 64 * kCover3Waves; ++t)
+        for (Cover3Cell c(t, s.wid, hh); c.pr < total; c.next(s.wid, hh)) {
+          const size_t at = (size_t)c.pl * s.ps + (size_t)c.yh * s.rst + c.e;
+          const size_t row = c.row(s, g.down != 0, Z0);
+          if (at >= rows_end || row >= (size_t)s.D * s.H) return false;
+          const uint32_t v = periodic32(rows.data() + row * wpr, s.W, word_start(s.W, c.e, g.mirror != 0));
+          lds[at] = (phase ? 0u : ~0u) ^ (g.mirror ? bit_reverse(v) : v);
         }
       for (int pc = 0; pc < s.npieces; ++pc) {
         const int r0 = p.piece_off[g.piece0 + pc], r1 = p.piece_off[g.piece0 + pc + 1];
-        const int rows = planes * s.H, bands = (rows + rpw * Q - 1) / (rpw * Q);
+        const int nrows = planes * s.H, bands = (nrows + rpw * Q - 1) / (rpw * Q);
         for (int band = 0; band < bands; ++band) {
           const int nw = 64 * Q * s.P;
           std::vector<uint32_t> st((size_t)nw, 0), A, S1, S2;
@@ -334,13 +334,13 @@ bool run_cover3(const Cover3Host &p, const uint8_t *vol, int phase, uint32_t *co
             for (int q = 0; q < Q; ++q)
               for (int i = 0; i < s.P; ++i) {
                 const int r = (band * Q + q) * rpw + l % rpw, w = l / rpw * s.P + i;
-                const int row = r < rows ? r : 0;
+                const int row = r < nrows ? r : 0;
                 const int j = (l * Q + q) * s.P + i;
                 base[j] = (size_t)(row / s.H) * s.ps + (size_t)(row % s.H) * s.rst + w;
                 const size_t own = base[j] + (g.down ? (size_t)s.cy * s.rst : 0);
                 if (own >= rows_end || w >= SP) return false;
                 const int left = s.W - 32 * w;
-                st[j] = r < rows && left > 0 ? lds[own] & (left >= 32 ? ~0u : (1u << left) - 1) : 0;
+                st[j] = r < nrows && left > 0 ? lds[own] & (left >= 32 ? ~0u : (1u << left) - 1) : 0;
               }
           for (int r = r0; r < r1;) {
             const int4 rec = p.recs.at(r);
