@@ -126,10 +126,10 @@ void build_octant(int cx, int cy, bool xm, bool mir, Octant &o) {
   });
 }
 
-// Steps of a path along the minor axis, bit k - 1 = q_k - q_{k-1}.
-using Bits = std::vector<uint64_t>;
-void letters(const Path &p, int len, Bits &b) {
-  b.assign((size_t)(len >> 6) + 2, 0);
+// Steps of a path along the minor axis, bit k - 1 = q_k - q_{k-1}; bit_words(len) words.
+inline int bit_words(int len) { return (len >> 6) + 2; }
+void letters(const Path &p, int len, uint64_t *b) {
+  std::fill(b, b + bit_words(len), 0);
   int err = p.n;
   for (int k = 0; k < len; ++k) {
     err += 2 * p.m;
@@ -139,11 +139,11 @@ void letters(const Path &p, int len, Bits &b) {
     }
   }
 }
-inline uint64_t bits64(const Bits &b, int j) {
+inline uint64_t bits64(const uint64_t *b, int j) {
   const int w = j >> 6, s = j & 63;
   return s ? (b[w] >> s) | (b[w + 1] << (64 - s)) : b[w];
 }
-int common(const Bits &a, const Bits &b, int len) {
+int common(const uint64_t *a, const uint64_t *b, int len) {
   for (int w = 0; w * 64 < len; ++w) {
     const uint64_t d = a[w] ^ b[w];
     if (d) return std::min(len, w * 64 + __builtin_ctzll(d));
@@ -154,22 +154,21 @@ int common(const Bits &a, const Bits &b, int len) {
 // A word: L steps (L + 1 pixels).
 struct Word {
   int L = 0;
-  Bits b;
+  const uint64_t *b = nullptr;
 };
-Word sub_word(const Bits &b, int j, int L) {
-  Word w;
-  w.L = L;
-  w.b.assign((size_t)(L >> 6) + 2, 0);
+// Letters j .. j + L - 1 of b as a word in `at`, bit_words(L) words.
+Word sub_word(const uint64_t *b, int j, int L, uint64_t *at) {
+  std::fill(at, at + bit_words(L), 0);
   for (int k = 0; k < L; k += 64) {
     uint64_t v = bits64(b, j + k);
     if (L - k < 64) v &= (1ull << (L - k)) - 1;
-    w.b[k >> 6] = v;
+    at[k >> 6] = v;
   }
-  return w;
+  return Word{L, at};
 }
 // Where a word starts on a path: bit j of occ (words of 64 pixels, occ_words(len) of them).
 inline int occ_words(int len) { return (len >> 6) + 1; }
-void find_word(const Bits &b, int len, const Word &w, uint64_t *occ) {
+void find_word(const uint64_t *b, int len, const Word &w, uint64_t *occ) {
   const int top = len - w.L;  // the last pixel where the word fits
   for (int x = 0; x < occ_words(len); ++x) {
     uint64_t o = 0;
@@ -216,6 +215,7 @@ int best_step(const Word *words, int nw, const uint64_t *occ, int width, int c, 
 
 struct GroupOut {
   CoverGroup g{};
+  int nw = 0;  // words, at most
   size_t lds_dw = 0;
   std::vector<int32_t> piece_off;  // within recs
   std::vector<int4> recs;
@@ -270,8 +270,9 @@ struct Geometry {
       const int d = std::max(0, y - tile + 1);
       return std::max(0, (int)(((int64_t)d * g.sh_a - g.sh_b) >> 16));
     };
+    // (rows before the tile's last one start at dword 0, and hi does not fall)
     int wid = 0;
-    for (int y = 0; y < g.rows; ++y)
+    for (int y = tile - 1; y < g.rows; ++y)
       wid = std::max(wid, SR + (hi[std::min(y, maxpy)] >> 5) - xs(y) + 1);
     g.wid = wid;
     g.wid_magic = (uint32_t)((((uint64_t)1 << 32) + wid - 1) / wid);
@@ -297,24 +298,25 @@ struct Geometry {
 // paths a..b-1 share.
 struct Node {
   int a, b, m;
-  std::vector<int> kids;
+  int kid = -1, next = -1;  // first child; next child of the same parent
+  int memo = -1;            // its entries in memo_
 };
 
 class GroupBuilder {
  public:
-  GroupBuilder(const Octant &o, int a, int b, int H, const CoverShape &sh)
-      : o_(o), a_(a), b_(b), H_(H), sh_(sh) {}
+  GroupBuilder(int H, const CoverShape &sh) : H_(H), sh_(sh) {}
 
-  // Tile and LDS layout of the group; false when its rows do not fit.
-  bool fit(GroupOut &out) {
+  // The group of paths a .. b - 1 of an octant: tile and LDS layout; false when its rows do not fit.
+  bool fit(const Octant &o, int a, int b, GroupOut &out) {
+    set(o, a, b);
     int len = 0, nmem = 0;
     for (int i = a_; i < b_; ++i) {
-      len = std::max(len, o_.paths[i].len);
-      nmem += o_.paths[i].nm;
+      len = std::max(len, o_->paths[i].len);
+      nmem += o_->paths[i].nm;
     }
     const int rpw = 64 / sh_.S;
     const int bands = (H_ + rpw - 1) / rpw;
-    Geometry geo(o_, o_.paths[a_], o_.paths[b_ - 1], len, sh_.S * sh_.R);
+    Geometry geo(*o_, o_->paths[a_], o_->paths[b_ - 1], len, sh_.S * sh_.R);
     CoverGroup &g = out.g;
     g.nmem = nmem;
     const int avail = sh_.lds / 4 - nmem - kCoverPad;
@@ -350,7 +352,7 @@ class GroupBuilder {
                 best = walk + build;
                 pick = t;
                 pick.nwb = nwb;
-                nw_ = w;
+                out.nw = w;
               }
               break;
             }
@@ -363,34 +365,51 @@ class GroupBuilder {
     return best < 1e300;
   }
 
-  void build(GroupOut &out) {
+  // Its words and records, in the layout that fit() chose.
+  void build(const Octant &o, int a, int b, GroupOut &out) {
+    set(o, a, b);
+    words_.clear();
+    slot0_.clear();
     CoverGroup &g = out.g;
     const int nmem = g.nmem;
     g.ntiles = (H_ + g.tile - 1) / g.tile;
-    g.mirror = o_.mir ? 1 : 0;
-    let_.resize(b_ - a_);
-    for (int i = a_; i < b_; ++i) letters(o_.paths[i], o_.paths[i].len, let_[i - a_]);
-    choose_words(nw_, out);
+    g.mirror = o_->mir ? 1 : 0;
+    int len = 0;
+    for (int i = a_; i < b_; ++i) len = std::max(len, o_->paths[i].len);
+    width_ = occ_words(len);
+    bits_.resize((size_t)(b_ - a_) * bit_words(len));
+    for (int i = a_; i < b_; ++i) letters(o_->paths[i], o_->paths[i].len, let(i - a_));
+    out.mems.reserve(nmem);
+    choose_words(out.nw, out);
     g.nw = (int)words_.size();
     out.lds_dw = (size_t)(1 + g.nw) * g.asz + kCoverPad + nmem;
     // members: slots in path order
     for (int i = a_; i < b_; ++i) {
-      const Path &p = o_.paths[i];
+      const Path &p = o_->paths[i];
       slot0_.push_back((int)out.mems.size());
-      out.mems.insert(out.mems.end(), o_.mems.begin() + p.m0, o_.mems.begin() + p.m0 + p.nm);
+      out.mems.insert(out.mems.end(), o_->mems.begin() + p.m0, o_->mems.begin() + p.m0 + p.nm);
     }
     pieces(out);
     out.counts = nmem;
   }
 
  private:
-  const Octant &o_;
-  const int a_, b_, H_;
+  const int H_;
   const CoverShape sh_;
-  int nw_ = 0;
-  std::vector<Bits> let_;
+  // the group, and what is kept of one for the next is the memory only
+  const Octant *o_ = nullptr;
+  int a_ = 0, b_ = 0;
+  void set(const Octant &o, int a, int b) {
+    o_ = &o;
+    a_ = a;
+    b_ = b;
+  }
+  int width_ = 0;               // words of the longest path's pixels
+  std::vector<uint64_t> bits_;  // the paths' letters
+  uint64_t *let(int i) { return bits_.data() + (size_t)i * (width_ + 1); }
   std::vector<int> slot0_;
   std::vector<Word> words_;
+  std::vector<uint64_t> cand_bits_;  // letters of the words tried
 
   uint32_t encode(const CoverGroup &g, int arr, int x, int y) const {
     return (uint32_t)(arr * g.asz + y * g.rst + (x >> 5)) | ((uint32_t)(x & 31) << 16);
@@ -408,15 +427,22 @@ class GroupBuilder {
     for (int s = 0; s < ns; ++s) smp.push_back((int)((2ll * s + 1) * np / (2 * ns)));
     int mid = np / 2;
     for (int i = 0; i < np; ++i)  // the longest path near the middle
-      if (std::abs(i - np / 2) <= np / 4 && o_.paths[a_ + i].len > o_.paths[a_ + mid].len) mid = i;
-    const int ml = o_.paths[a_ + mid].len;
+      if (std::abs(i - np / 2) <= np / 4 && o_->paths[a_ + i].len > o_->paths[a_ + mid].len) mid = i;
+    const int ml = o_->paths[a_ + mid].len;
+    auto longer = [&](int L) { return L + std::max(1, quick ? L / 2 : L / 3); };
+    int most_cand = 0;
+    for (int L = 1; L <= ml; L = longer(L)) most_cand += 2;
+    const int wb = bit_words(ml);
+    cand_bits_.resize((size_t)most_cand * wb);
     std::vector<Word> cand;
-    for (int L = 1; L <= ml; L += std::max(1, quick ? L / 2 : L / 3)) {
+    cand.reserve(most_cand);
+    for (int L = 1; L <= ml; L = longer(L)) {
       for (int j : {0, ml - L}) {
-        Word w = sub_word(let_[mid], j, L);
-        bool seen = false;
-        for (const Word &c : cand) seen = seen || (c.L == w.L && c.b == w.b);
-        if (!seen) cand.push_back(std::move(w));
+        const Word w = sub_word(let(mid), j, L, &cand_bits_[cand.size() * wb]);
+        // (the two words of a length follow each other)
+        const bool seen = !cand.empty() && cand.back().L == L &&
+                          std::equal(w.b, w.b + bit_words(L), cand.back().b);
+        if (!seen) cand.push_back(w);
       }
     }
     const int nc = (int)cand.size();
@@ -424,11 +450,11 @@ class GroupBuilder {
     std::vector<std::vector<uint64_t>> occ(ns);
     std::vector<int> width(ns);
     for (int s = 0; s < ns; ++s) {
-      const int len = o_.paths[a_ + smp[s]].len;
+      const int len = o_->paths[a_ + smp[s]].len;
       width[s] = occ_words(len);
       occ[s].resize((size_t)nc * width[s]);
       for (int c = 0; c < nc; ++c)
-        find_word(let_[smp[s]], len, cand[c], &occ[s][(size_t)c * width[s]]);
+        find_word(let(smp[s]), len, cand[c], &occ[s][(size_t)c * width[s]]);
     }
     const double scale = (double)np / ns;
     const double ratio = 1.5 * (double)g.rows * g.wid / ((double)g.tile * sh_.S * sh_.R);
@@ -444,13 +470,15 @@ class GroupBuilder {
         bc += sub ? (double)L / (sub + 1) + 2 : L + 1;
       }
       bc *= ratio;
+      if (bc >= most) return most;
+      const int64_t limit = most < 1e200 ? (int64_t)((most - bc) / scale) + 1 : INT64_MAX;
       int64_t n = 0;
-      for (int s = 0; s < ns && n * scale + bc < most; ++s) {
-        const Path &p = o_.paths[a_ + smp[s]];
+      for (int s = 0; s < ns; ++s) {
+        const Path &p = o_->paths[a_ + smp[s]];
         const uint64_t *oc = occ[s].data();
         int c = p.len / 3;
         for (int t = 0; t < p.nm; ++t) {
-          const int l = o_.mems[p.m0 + t].l;
+          const int l = o_->mems[p.m0 + t].l;
           while (c <= l) {
             int end = c;
             for (int x = 0; x < k; ++x) {
@@ -460,7 +488,7 @@ class GroupBuilder {
               if (j >= 0) end = std::max(end, j + L);
             }
             c = end + 1;
-            ++n;
+            if (++n > limit) return most;
           }
         }
       }
@@ -508,7 +536,7 @@ class GroupBuilder {
         c = best_step(words_.data(), (int)w, oc.data(), wd_words, c, wd.L, s) + 1;
         int q = 0;
         for (int k = 0; k < s.j; ++k) q += (int)((wd.b[k >> 6] >> (k & 63)) & 1);
-        out.bops.push_back(o_.xm ? encode(g, s.arr, s.j, q) : encode(g, s.arr, q, s.j));
+        out.bops.push_back(o_->xm ? encode(g, s.arr, s.j, q) : encode(g, s.arr, q, s.j));
       }
       g.bop[w + 1] = (int)out.bops.size();
     }
@@ -517,50 +545,57 @@ class GroupBuilder {
   }
 
   // ---- the walks of one piece ----
+  struct Memo {
+    int s, k, cost;
+    bool save;
+    int next;
+  };
   std::vector<Node> nodes_;
+  std::vector<Memo> memo_;
   std::vector<int> lcp_;
-  std::vector<std::vector<std::pair<int64_t, std::pair<int, bool>>>> memo_;
-  std::vector<std::vector<uint64_t>> occ_;  // per path: the words' starts
+  std::vector<uint64_t> occ_;  // the words' starts on each path, width_ words each
+  const uint64_t *occ(int i) const { return occ_.data() + (size_t)i * words_.size() * width_; }
 
   int tree(int a, int b) {
-    Node t{a, b, 0, {}};
+    Node t{a, b, 0};
     if (b - a == 1) {
-      t.m = o_.paths[a].len;
+      t.m = o_->paths[a].len;
     } else {
       int m = INT_MAX;
       for (int i = a; i + 1 < b; ++i) m = std::min(m, lcp_[i - a_]);
       t.m = m;
-      int s = a;
-      for (int i = a; i + 1 < b; ++i)
-        if (lcp_[i - a_] == m) {
-          t.kids.push_back(tree(s, i + 1));
+      int s = a, last = -1;
+      for (int i = a; i < b; ++i)
+        if (i + 1 == b || lcp_[i - a_] == m) {
+          const int u = tree(s, i + 1);
+          (last < 0 ? t.kid : nodes_[last].next) = u;
+          last = u;
           s = i + 1;
         }
-      t.kids.push_back(tree(s, b));
     }
-    nodes_.push_back(std::move(t));
+    nodes_.push_back(t);
     return (int)nodes_.size() - 1;
   }
 
   // Least cost, in pixels, of the walks below node v from a product saved at depth s with k saves
   // left, and whether to save at v's depth.  A save or a restore copies the product: about 6.
   std::pair<int, bool> best_save(int v, int s, int k) {
-    const int64_t key = (int64_t)(s + 1) * 4 + k;
-    for (auto &e : memo_[v])
-      if (e.first == key) return e.second;
+    for (int e = nodes_[v].memo; e >= 0; e = memo_[e].next)
+      if (memo_[e].s == s && memo_[e].k == k) return std::make_pair(memo_[e].cost, memo_[e].save);
     std::pair<int, bool> r(0, false);
-    const Node &t = nodes_[v];
-    if (t.kids.empty()) {
+    const Node t = nodes_[v];
+    if (t.kid < 0) {
       r.first = t.m - s + 6;
     } else {
-      for (int u : t.kids) r.first += best_save(u, s, k).first;
+      for (int u = t.kid; u >= 0; u = nodes_[u].next) r.first += best_save(u, s, k).first;
       if (k > 0 && t.m - s >= 6) {
         int c = t.m - s + 12;
-        for (int u : t.kids) c += best_save(u, t.m, k - 1).first;
+        for (int u = t.kid; u >= 0; u = nodes_[u].next) c += best_save(u, t.m, k - 1).first;
         if (c < r.first) r = std::make_pair(c, true);
       }
     }
-    memo_[v].push_back({key, r});
+    memo_.push_back(Memo{s, k, r.first, r.second, nodes_[v].memo});
+    nodes_[v].memo = (int)memo_.size() - 1;
     return r;
   }
 
@@ -572,18 +607,16 @@ class GroupBuilder {
     const int np = b_ - a_;
     lcp_.assign(np, 0);
     for (int i = 0; i + 1 < np; ++i)
-      lcp_[i] = common(let_[i], let_[i + 1],
-                       std::min(o_.paths[a_ + i].len, o_.paths[a_ + i + 1].len));
-    occ_.resize(np);
-    for (int i = 0; i < np; ++i) {
-      const int len = o_.paths[a_ + i].len, width = occ_words(len);
-      occ_[i].resize(words_.size() * width);
+      lcp_[i] = common(let(i), let(i + 1),
+                       std::min(o_->paths[a_ + i].len, o_->paths[a_ + i + 1].len));
+    occ_.resize((size_t)np * words_.size() * width_);
+    for (int i = 0; i < np; ++i)
       for (size_t w = 0; w < words_.size(); ++w)
-        find_word(let_[i], len, words_[w], &occ_[i][w * width]);
-    }
+        find_word(let(i), o_->paths[a_ + i].len, words_[w], &occ_[(i * words_.size() + w) * width_]);
+    out.recs.reserve((size_t)4 * out.g.nmem);
     const int nsub = sh_.wpg / out.g.nwb;
     work_.resize(np);
-    for (int i = 0; i < np; ++i) work_[i] = 4 + 3 * o_.paths[a_ + i].nm;
+    for (int i = 0; i < np; ++i) work_[i] = 4 + 3 * o_->paths[a_ + i].nm;
     for (int pass = 0; pass < (nsub > 1 ? 2 : 1); ++pass) {
       const std::vector<int> w = work_;
       int64_t total = 0;
@@ -601,7 +634,7 @@ class GroupBuilder {
         if (i == s) continue;
         nodes_.clear();
         const int root = tree(a_ + s, a_ + i);
-        memo_.assign(nodes_.size(), {});
+        memo_.clear();
         in_acc_ = -1;
         emit(out, root, -1, 0, 0, 2);
       }
@@ -616,10 +649,10 @@ class GroupBuilder {
 
   // Records for `steps` on path i; the last one carries the count.
   void put(GroupOut &out, int i, const std::vector<Step> &steps, int level, int slot) {
-    const Path &p = o_.paths[i];
+    const Path &p = o_->paths[i];
     auto code = [&](const Step &s) {
       const int q = p.q(s.j);
-      return o_.xm ? encode(out.g, s.arr, s.j, q) : encode(out.g, s.arr, q, s.j);
+      return o_->xm ? encode(out.g, s.arr, s.j, q) : encode(out.g, s.arr, q, s.j);
     };
     for (size_t t = 0; t < steps.size(); t += 2) {
       int4 r = make_int4((int)code(steps[t]), 0, 0, 0);
@@ -635,7 +668,6 @@ class GroupBuilder {
       if (slot >= 0 && t + 2 >= steps.size()) {
         r.x |= (int)kRecCount;
         r.z = slot;
-        counted_.push_back((int)out.recs.size());
       }
       out.recs.push_back(r);
     }
@@ -643,67 +675,63 @@ class GroupBuilder {
     work_[i - a_] += (int)(steps.size() * (3 * sh_.R / 2 + 6)) + (slot >= 0 ? sh_.R + 12 : 0);
   }
   bool started_ = false;
-  std::vector<int> counted_;
+  // of one call of emit, before it goes on to the nodes below
+  std::vector<std::pair<int, int>> ends_;
+  std::vector<Step> st_;
 
   // Walks below node v; products covered below pixel c are saved at `level` (depth s).
   void emit(GroupOut &out, int v, int s, int c, int level, int k) {
-    const Node &t = nodes_[v];
-    const bool leaf = t.kids.empty();
+    const Node t = nodes_[v];
+    const bool leaf = t.kid < 0;
     if (!leaf && !(level < 2 && best_save(v, std::max(s, 0), k).second)) {
-      for (int u : t.kids) emit(out, u, s, c, level, k);
+      for (int u = t.kid; u >= 0; u = nodes_[u].next) emit(out, u, s, c, level, k);
       return;
     }
-    // counts on the shared pixels s < l <= m of the paths below
-    std::vector<std::pair<int, int>> ends;  // (l, slot)
+    // counts on the shared pixels s < l <= m of the paths below: (l, slot)
+    ends_.clear();
     for (int i = t.a; i < t.b; ++i)
-      for (int x = 0; x < o_.paths[i].nm; ++x) {
-        const int l = o_.mems[o_.paths[i].m0 + x].l;
-        if (l > s && l <= t.m) ends.push_back({l, slot0_[i - a_] + x});
+      for (int x = 0; x < o_->paths[i].nm; ++x) {
+        const int l = o_->mems[o_->paths[i].m0 + x].l;
+        if (l > s && l <= t.m) ends_.push_back({l, slot0_[i - a_] + x});
       }
-    std::sort(ends.begin(), ends.end());
-    const uint64_t *occ = occ_[t.a - a_].data();
-    const int width = occ_words(o_.paths[t.a].len), nw = (int)words_.size();
+    std::sort(ends_.begin(), ends_.end());
+    const uint64_t *oc = occ(t.a - a_);
+    const int nw = (int)words_.size();
     int cv = c;
-    std::vector<Step> st;
     const size_t rec0 = out.recs.size();
     started_ = false;
-    std::vector<int> outer;
-    outer.swap(counted_);
-    for (const auto &e : ends) {
-      st.clear();
+    for (const auto &e : ends_) {
+      st_.clear();
       while (cv <= e.first) {
         Step x;
-        cv = best_step(words_.data(), nw, occ, width, cv, e.first, x) + 1;
-        st.push_back(x);
+        cv = best_step(words_.data(), nw, oc, width_, cv, e.first, x) + 1;
+        st_.push_back(x);
       }
-      put(out, t.a, st, level, e.second);
+      put(out, t.a, st_, level, e.second);
     }
-    std::vector<int> mine;
+    size_t rec1 = out.recs.size();  // the records up to here: counts of this node
     if (!leaf) {
       // on towards the branch, while steps are worth it
-      st.clear();
+      st_.clear();
       for (;;) {
         if (cv > t.m) break;
         Step x;
-        const int end = best_step(words_.data(), nw, occ, width, cv, t.m, x);
+        const int end = best_step(words_.data(), nw, oc, width_, cv, t.m, x);
         if (end - cv < 3) break;
         cv = end + 1;
-        st.push_back(x);
+        st_.push_back(x);
       }
-      if (!st.empty()) put(out, t.a, st, level, -1);
-      mine.swap(counted_);
+      if (!st_.empty()) put(out, t.a, st_, level, -1);
       if (out.recs.size() > rec0) {
         out.recs.back().x |= (level + 1) << kRecSave;
         in_acc_ = level + 1;
-        for (int u : t.kids) emit(out, u, t.m, cv, level + 1, k - 1);
+        for (int u = t.kid; u >= 0; u = nodes_[u].next) emit(out, u, t.m, cv, level + 1, k - 1);
       } else {
-        for (int u : t.kids) emit(out, u, s, c, level, k);
+        for (int u = t.kid; u >= 0; u = nodes_[u].next) emit(out, u, s, c, level, k);
       }
-    } else {
-      mine.swap(counted_);
     }
-    for (int r : mine) out.recs[r].w = (int)out.recs.size();
-    counted_.swap(outer);
+    for (size_t r = rec0; r < rec1; ++r)
+      if (out.recs[r].x & (int)kRecCount) out.recs[r].w = (int)out.recs.size();
   }
 };
 
@@ -774,16 +802,29 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
   }
   const int ng = (int)ranges.size();
   std::vector<GroupOut> go(ng);
-  std::vector<GroupBuilder> gb;
-  gb.reserve(ng);
-  for (int i = 0; i < ng; ++i) gb.emplace_back(oct[ranges[i].o], ranges[i].a, ranges[i].b, H, sh);
   std::atomic<bool> fits(true);
-  const int threads = std::min(16, ng / 4);
-  parallel(ng, threads, [&](int i) {
-    if (fits && !gb[i].fit(go[i])) fits = false;
-  });
+  // A thread for about 300 vectors (their plan takes some 200 us, starting a thread 30), a few runs
+  // of groups each; fit() tries tiles of as many heights as there are bands.
+  int64_t members = 0;
+  for (const Octant &o : oct) members += (int64_t)o.mems.size();
+  const int threads = (int)std::min<int64_t>(16, std::min<int64_t>(ng / 4, 1 + members / 300));
+  const int bands = (H + 64 / sh.S - 1) / (64 / sh.S);
+  const int runs = std::min(ng, 8 * std::max(1, threads));
+  auto groups = [&](int thr, auto &&f) {
+    parallel(runs, thr, [&](int run) {
+      GroupBuilder gb(H, sh);
+      for (int i = (int)((int64_t)ng * run / runs); i < (int)((int64_t)ng * (run + 1) / runs); ++i)
+        f(gb, oct[ranges[i].o], ranges[i].a, ranges[i].b, go[i]);
+    });
+  };
+  groups((int64_t)ng * bands > 256 ? threads : 1,
+         [&](GroupBuilder &gb, const Octant &o, int a, int b, GroupOut &x) {
+           if (fits && !gb.fit(o, a, b, x)) fits = false;
+         });
   if (!fits) return false;
-  parallel(ng, threads, [&](int i) { gb[i].build(go[i]); });
+  groups(threads, [&](GroupBuilder &gb, const Octant &o, int a, int b, GroupOut &x) {
+    gb.build(o, a, b, x);
+  });
   size_t nrec = 64, dw = 0;
   for (auto &x : go) nrec += x.recs.size();
   out.recs.reserve(nrec);

@@ -27,8 +27,10 @@ struct Seg {
   uint64_t key;
   int n, idx;
   int cls;  // mirror | down << 1, then the major axis
-  bool operator<(const Seg &o) const {
-    return cls != o.cls ? cls < o.cls : (key != o.key ? key < o.key : n < o.n);
+  // class, steps, length: a number that sorts like the three
+  uint64_t order() const {
+    static_assert(kCover3Cut <= 24, "steps in the upper 48 bits of the key, n in 5 bits");
+    return (uint64_t)cls << 53 | (key >> 16) << 5 | (uint64_t)n;
   }
 };
 
@@ -63,19 +65,25 @@ int common_steps(const Seg &a, const Seg &b) {
   return d ? std::min(m, __builtin_clzll(d) / 2) : m;
 }
 
-// The records of segments s[0 .. n) (sorted, one mirror and down), slots from slot0 on.
+// The records of a group's pieces.
 class Walker {
  public:
-  Walker(const Seg *s, int n, const Cover3Shape &sh, int slot0, std::vector<int4> &recs)
-      : s_(s), sh_(sh), slot0_(slot0), recs_(recs), rec0_((int)recs.size()) {
+  explicit Walker(const Cover3Shape &sh) : sh_(sh) {}
+  // The records of segments s[0 .. n) (sorted, one mirror and down), slots from slot0 on.
+  void piece(const Seg *s, int n, int slot0, std::vector<int4> &recs) {
+    out_ = &recs;
+    s_ = s;
+    slot0_ = slot0;
     lcp_.resize(n);
     for (int i = 0; i + 1 < n; ++i) lcp_[i] = common_steps(s[i], s[i + 1]);
     int a = 0;
     for (int i = 0; i < n; ++i)
       if (i + 1 == n || lcp_[i] < 0) {
         nodes_.clear();
+        stride_ = 0;
+        for (int j = a; j <= i; ++j) stride_ = std::max(stride_, s_[j].n + 1);
         const int root = tree(a, i + 1);
-        memo_.assign(nodes_.size() * 3 * (kCover3Cut + 2), -1);
+        memo_.assign(nodes_.size() * 3 * stride_, kUnset);
         emit(root, 0, 0);
         a = i + 1;
       }
@@ -83,66 +91,73 @@ class Walker {
 
  private:
   struct Node {
-    int a, b, m;  // segments a .. b - 1 share their first m steps
-    std::vector<int> kids;
+    int a, b, m;           // segments a .. b - 1 share their first m steps
+    int kid = -1, next = -1;  // first child; next child of the same parent
   };
-  const Seg *s_;
+  const Seg *s_ = nullptr;
   const Cover3Shape &sh_;
-  const int slot0_;
-  std::vector<int4> &recs_;
-  const int rec0_;
-  std::vector<int> lcp_, memo_;
+  int slot0_ = 0;
+  std::vector<int4> *out_ = nullptr;
+  std::vector<int> lcp_;
+  // costs by node, saves left and depth; at most kCover3Slots (kCover3Cut + 2) < 2^15
+  std::vector<uint16_t> memo_;
+  static constexpr uint16_t kUnset = 0xffff;
+  int stride_ = 0;
   std::vector<Node> nodes_;
 
   int tree(int a, int b) {
-    Node t{a, b, s_[a].n, {}};
+    Node t{a, b, s_[a].n};
     for (int i = a; i + 1 < b; ++i) t.m = std::min(t.m, lcp_[i]);
     if (b - a > 1) {
       int c = s_[a].n == t.m ? a + 1 : a;  // a segment that ends here is counted at this node
+      int last = -1;
       for (int i = c; i < b; ++i)
         if (i + 1 == b || lcp_[i] == t.m) {
-          t.kids.push_back(tree(c, i + 1));
+          const int u = tree(c, i + 1);
+          (last < 0 ? t.kid : nodes_[last].next) = u;
+          last = u;
           c = i + 1;
         }
     }
-    nodes_.push_back(std::move(t));
+    nodes_.push_back(t);
     return (int)nodes_.size() - 1;
   }
   // Steps (a save or a restore: one) of the walks below node v from a product of the first d
   // steps, k saves left.
   static constexpr int kCopy = 1;
   int cost(int v, int d, int k) {
-    int &c = memo_[((size_t)v * 3 + k) * (kCover3Cut + 2) + d];
-    if (c >= 0) return c;
+    uint16_t &c = memo_[((size_t)v * 3 + k) * stride_ + d];
+    if (c != kUnset) return c;
     const Node &t = nodes_[v];
-    if (t.kids.empty()) return c = t.m - d + kCopy;
-    c = unsaved(v, d, k);
-    if (k > 0) c = std::min(c, saved(v, d, k));
-    return c;
+    int x;
+    if (t.kid < 0) {
+      x = t.m - d + kCopy;
+    } else {
+      x = unsaved(v, d, k);
+      if (k > 0) x = std::min(x, saved(v, d, k));
+    }
+    return c = (uint16_t)x;
   }
   int own(const Node &t, int d) const { return s_[t.a].n == t.m ? t.m - d + kCopy : 0; }
   int unsaved(int v, int d, int k) {
     const Node &t = nodes_[v];
     int c = own(t, d);
-    for (int u : t.kids) c += cost(u, d, k);
+    for (int u = t.kid; u >= 0; u = nodes_[u].next) c += cost(u, d, k);
     return c;
   }
   int saved(int v, int d, int k) {
     const Node &t = nodes_[v];
     if (t.m == d) return INT_MAX;
     int c = t.m - d + 2 * kCopy;
-    for (int u : t.kids) c += cost(u, t.m, k - 1);
+    for (int u = t.kid; u >= 0; u = nodes_[u].next) c += cost(u, t.m, k - 1);
     return c;
   }
   // Step 0 of a record: voxel k of segment i (the lane's own voxel is in the start pixels).
   uint32_t code(int i, int k) const {
     const Seg &s = s_[i];
-    int qa = 0, qb = 0;
-    for (int j = 0; j < k; ++j) {
-      const int st = (int)(s.key >> (62 - 2 * j)) & 3;
-      qa += st & 1;
-      qb += st >> 1;
-    }
+    const uint64_t steps = k ? s.key >> (64 - 2 * k) : 0;
+    const int qa = __builtin_popcountll(steps & 0x5555555555555555ull);
+    const int qb = __builtin_popcountll(steps & 0xaaaaaaaaaaaaaaaaull);
     const int maj = s.cls & 3, down = (s.cls >> 3) & 1;
     const int x = maj == 0 ? k : qa, y = maj == 1 ? k : (maj == 0 ? qa : qb), z = maj == 2 ? k : qb;
     return (uint32_t)(z * sh_.ps + (down ? sh_.cy - y : y) * sh_.rst + (x >> 5)) |
@@ -162,30 +177,31 @@ class Walker {
         r.x |= (int)kRecCount;
         r.z = slot0_ + i;
       }
-      recs_.push_back(r);
+      out_->push_back(r);
     }
   }
   void emit(int v, int d, int level) {
     const Node t = nodes_[v];
+    std::vector<int4> &recs = *out_;
     const int k = 2 - level;
-    if (t.kids.empty()) {
+    if (t.kid < 0) {
       walk(t.a, d, t.m, level, true);
-      recs_.back().w = (int)recs_.size();
+      recs.back().w = (int)recs.size();
       return;
     }
     const bool ends = s_[t.a].n == t.m;
-    const size_t r0 = recs_.size();
+    const size_t r0 = recs.size();
     if (k > 0 && t.m > d && saved(v, d, k) < unsaved(v, d, k)) {
       walk(t.a, d, t.m, level, ends);
-      const size_t at = recs_.size() - 1;
-      recs_[at].x |= (level + 1) << kRecSave;
-      for (int u : t.kids) emit(u, t.m, level + 1);
-      recs_[at].w = (int)recs_.size();  // a zero count here: nothing below counts
+      const size_t at = recs.size() - 1;
+      recs[at].x |= (level + 1) << kRecSave;
+      for (int u = t.kid; u >= 0; u = nodes_[u].next) emit(u, t.m, level + 1);
+      recs[at].w = (int)recs.size();  // a zero count here: nothing below counts
     } else {
       if (ends) walk(t.a, d, t.m, level, true);
-      const size_t at = recs_.size() - 1;
-      for (int u : t.kids) emit(u, d, level);
-      if (ends && recs_.size() > r0) recs_[at].w = (int)recs_.size();
+      const size_t at = recs.size() - 1;
+      for (int u = t.kid; u >= 0; u = nodes_[u].next) emit(u, d, level);
+      if (ends && recs.size() > r0) recs[at].w = (int)recs.size();
     }
   }
 };
@@ -228,8 +244,16 @@ bool plan_cover3(int W, int H, int D, int cx, int cy, int cz, const int16_t *vec
   sh.npieces = kCover3Waves / nwb;
 
   std::vector<Seg> seg((size_t)nv);
-  for (int64_t i = 0; i < nv; ++i) seg[i] = segment_of(vec + 3 * i, (int)i);
-  std::sort(seg.begin(), seg.end());
+  {
+    std::vector<Seg> can((size_t)nv);
+    std::vector<std::pair<uint64_t, int>> by((size_t)nv);
+    for (int64_t i = 0; i < nv; ++i) {
+      can[i] = segment_of(vec + 3 * i, (int)i);
+      by[i] = {can[i].order(), (int)i};
+    }
+    std::sort(by.begin(), by.end());
+    for (int64_t i = 0; i < nv; ++i) seg[i] = can[by[i].second];
+  }
   // groups of about equal work (steps not shared with the segment before, and a count), cut where
   // the signs change; one workgroup per compute unit, since each stages its slab and starts its
   // trees anew (60^3, cutoff 8: 28 us, with two 41, with four 66; 100^3, cutoff 16: 555, 563, 597)
@@ -266,19 +290,30 @@ bool plan_cover3(int W, int H, int D, int cx, int cy, int cz, const int16_t *vec
   const int ng = (int)cut.size();
   std::vector<std::vector<int4>> recs((size_t)ng);
   std::vector<std::vector<int32_t>> off((size_t)ng);
-  parallel(ng, 16, [&](int g) {
-    const int64_t a = cut[g].first, e = cut[g].second;
-    int64_t s = a;
-    for (int k = 0; k < sh.npieces; ++k) {
+  // A thread for about 1 000 segments (starting one takes as long as planning 200 of them), a few
+  // runs of groups each.
+  const int threads = (int)std::min<int64_t>(16, 1 + nv / 1000), runs = std::min(ng, 8 * threads);
+  parallel(runs, threads, [&](int run) {
+    Walker w(sh);
+    for (int g = (int)((int64_t)ng * run / runs); g < (int)((int64_t)ng * (run + 1) / runs); ++g) {
+      const int64_t a = cut[g].first, e = cut[g].second;
+      recs[g].reserve((size_t)(4 * (e - a)));
+      off[g].reserve((size_t)sh.npieces + 1);
+      int64_t s = a;
+      for (int k = 0; k < sh.npieces; ++k) {
+        off[g].push_back((int32_t)recs[g].size());
+        const int64_t to = work[a] + (work[e] - work[a]) * (k + 1) / sh.npieces;
+        int64_t t = s;
+        while (t < e && (k + 1 == sh.npieces || work[t + 1] <= to)) ++t;
+        if (t > s) w.piece(seg.data() + s, (int)(t - s), (int)(s - a), recs[g]);
+        s = t;
+      }
       off[g].push_back((int32_t)recs[g].size());
-      const int64_t to = work[a] + (work[e] - work[a]) * (k + 1) / sh.npieces;
-      int64_t t = s;
-      while (t < e && (k + 1 == sh.npieces || work[t + 1] <= to)) ++t;
-      if (t > s) Walker(seg.data() + s, (int)(t - s), sh, (int)(s - a), recs[g]);
-      s = t;
     }
-    off[g].push_back((int32_t)recs[g].size());
   });
+  size_t nrec = 2;
+  for (const auto &r : recs) nrec += r.size();
+  p.recs.reserve(nrec);
   for (int g = 0; g < ng; ++g) {
     const Seg &s = seg[cut[g].first];
     const int32_t base = (int32_t)p.recs.size();
