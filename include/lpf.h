@@ -138,10 +138,11 @@ lpf_status lpf_full_sampled(lpf_ctx ctx, const uint64_t *bits, int W, int H, int
 lpf_status lpf_full_noalloc(lpf_ctx ctx, const uint64_t *bits, int W, int H, int cx, int cy,
                             unsigned phase_mask, int out_layout, uint32_t *counts, void *stream);
 
-/* Statistics of the chains that lpf_full walks when it reads rows from device memory, for cutoff (cx, cy) (host only; no device, no
- * context).  A chain is one walked vector v and every vector u of D_c whose digitised path is,
- * up to a translation, pixels 0..n_u of v's path (a "shorter overlapping segment" of v, Sec.
- * 3.2); one walk gives the counts of all of them.  out (host, 4 int64): |D_c|, number of chains,
+/* Statistics of the chains that lpf_full walks when it reads rows from device memory, for cutoff
+ * (cx, cy) (host only; no device, no context).  A chain is one walked vector v and every vector u
+ * of D_c whose digitised path is, up to a translation, pixels 0..n_u of v's path (a "shorter
+ * overlapping segment" of v, Sec. 3.2); one walk gives the counts of all of them.  out (host, 4
+ * int64): |D_c|, number of chains,
  * pixels walked per 32 start pixels (sum over chains of the walked length + 1), and M_c = sum
  * over D_c of (n + 1), the pixels a walk per vector would take.  Returns LPF_E_INVAL for a NULL
  * out or a cutoff outside [0, 32767], LPF_E_UNSUPPORTED above 2^26 vectors; sets no message. */
@@ -303,7 +304,7 @@ lpf_status lpf_autotune_full(lpf_ctx ctx, const uint64_t *bits, int W, int H, in
 
 /* The shape recorded by lpf_autotune_full for W, H, cx, cy (host outputs, each may be NULL), as
  * lpf_set_full_shape takes it: *R is 0 (automatic) where the automatic plan was the fastest and its
- * words per lane are not a power of two.
+ * lanes are not those that lpf_set_full_shape derives from an R.
  * Errors: LPF_E_INVAL when none was recorded. */
 lpf_status lpf_get_tuned_shape(lpf_ctx ctx, int W, int H, int cx, int cy, int *R,
                                int *waves_per_group, int *lds_bytes);

@@ -48,7 +48,8 @@ struct CoverGroup {
 // Index arithmetic of a group's LDS rows, for the kernel and for the planner's host run of it (G: a
 // CoverGroup in whatever address space).
 //
-// i / n for i < 2^16 times n's rounding error below 2^32, magic = ceil(2^32 / n), n >= 2.
+// i / n, magic = ceil(2^32 / n), n >= 2: exact for i (n magic - 2^32) < 2^32, and so for the at most
+// 2^16 cells of a group.
 __host__ __device__ __forceinline__ int cover_div(int i, uint32_t magic) {
   return (int)(((uint64_t)(uint32_t)i * magic) >> 32);
 }

@@ -385,12 +385,18 @@ bool fixed_shape(lpf_ctx c, int W, int H, int cx, int cy, FixedShape &f, std::st
 }
 
 // Tile shape of the chain walk: rows staged in LDS, or (rows_in_memory) read from the extended
-// image in device memory.  The autotuner's shapes are the cover kernel's (any R, other budgets): they
-// are not this walk's, which has R = 1, 2, 4, 8 and 16.
+// image in device memory.  Staged rows keep their own lanes and budget whatever was tuned: the
+// autotuner times the cover kernel, or, where its rows do not fit, rows in device memory.
 bool choose_shape(lpf_ctx c, int W, int H, int cx, int cy, bool rows_in_memory, FullShape &sh,
                   std::string &why) {
   const int swd = (W + 31) / 32;
-  const int fR = c->force_R, fW = c->force_wpg, fL = c->force_lds;
+  TunedShape tuned;
+  if (rows_in_memory) {
+    auto tk = c->tuned.find(std::make_tuple(W, H, cx, cy));
+    if (tk != c->tuned.end()) tuned = tk->second;
+  }
+  const int fR = c->force_R ? c->force_R : tuned.R;
+  const int fW = c->force_wpg ? c->force_wpg : tuned.wpg, fL = c->force_lds;
   // up to 16 words per lane
   int R = fR ? fR : std::min(16, next_pow2(swd));
   int S = c->force_S ? c->force_S : next_pow2((swd + R - 1) / R);
