@@ -27,19 +27,24 @@ struct Seg {
   uint64_t key;
   int n, idx;
   int cls;  // mirror | down << 1, then the major axis
-  // class, steps, length: a number that sorts like the three
+  // steps, then length: a number that sorts like the two
   uint64_t order() const {
-    static_assert(kCover3Cut <= 24, "steps in the upper 48 bits of the key, n in 5 bits");
-    return (uint64_t)cls << 53 | (key >> 16) << 5 | (uint64_t)n;
+    static_assert(kCover3Cut <= 24, "steps in the upper 48 bits of the key");
+    return key | (uint64_t)n;
   }
 };
 
-Seg segment_of(const int16_t *v, int idx) {
+int class_of(const int16_t *v) {
+  const int a = std::abs(v[0]), b = std::abs(v[1]), c = std::abs(v[2]);
+  const int maj = a >= b && a >= c ? 0 : (b >= c ? 1 : 2);
+  return ((v[0] < 0) | (v[1] < 0) << 1) * 4 + maj;
+}
+
+Seg segment_of(const int16_t *v, int idx, int cls) {
   const int a[3] = {std::abs(v[0]), std::abs(v[1]), std::abs(v[2])};
-  const int n = std::max(a[0], std::max(a[1], a[2]));
-  const int maj = a[0] == n ? 0 : (a[1] == n ? 1 : 2);
+  const int maj = cls & 3, n = a[maj];
   const int ma = maj == 0 ? a[1] : a[0], mb = maj == 2 ? a[1] : a[2];
-  Seg s{0, n, idx, ((v[0] < 0) | (v[1] < 0) << 1) * 4 + maj};
+  Seg s{0, n, idx, cls};
   int ea = n, eb = n;  // the rounding of the 2-D segments per minor axis
   for (int k = 0; k < n; ++k) {
     uint64_t st = 0;
@@ -126,16 +131,12 @@ class Walker {
   // steps, k saves left.
   static constexpr int kCopy = 1;
   int cost(int v, int d, int k) {
+    const Node &t = nodes_[v];
+    if (t.kid < 0) return t.m - d + kCopy;
     uint16_t &c = memo_[((size_t)v * 3 + k) * stride_ + d];
     if (c != kUnset) return c;
-    const Node &t = nodes_[v];
-    int x;
-    if (t.kid < 0) {
-      x = t.m - d + kCopy;
-    } else {
-      x = unsaved(v, d, k);
-      if (k > 0) x = std::min(x, saved(v, d, k));
-    }
+    int x = unsaved(v, d, k);
+    if (k > 0) x = std::min(x, saved(v, d, k));
     return c = (uint16_t)x;
   }
   int own(const Node &t, int d) const { return s_[t.a].n == t.m ? t.m - d + kCopy : 0; }
@@ -243,16 +244,27 @@ bool plan_cover3(int W, int H, int D, int cx, int cy, int cz, const int16_t *vec
   while (nwb < kCover3Waves && 2 * nwb <= bands) nwb *= 2;
   sh.npieces = kCover3Waves / nwb;
 
+  // the segments class by class, sorted in each; a thread for about 3 000 of them
   std::vector<Seg> seg((size_t)nv);
   {
-    std::vector<Seg> can((size_t)nv);
-    std::vector<std::pair<uint64_t, int>> by((size_t)nv);
-    for (int64_t i = 0; i < nv; ++i) {
-      can[i] = segment_of(vec + 3 * i, (int)i);
-      by[i] = {can[i].order(), (int)i};
-    }
-    std::sort(by.begin(), by.end());
-    for (int64_t i = 0; i < nv; ++i) seg[i] = can[by[i].second];
+    constexpr int kClasses = 16;
+    int64_t at[kClasses + 1] = {}, fill[kClasses];
+    std::vector<uint8_t> cls((size_t)nv);
+    for (int64_t i = 0; i < nv; ++i) ++at[(cls[i] = (uint8_t)class_of(vec + 3 * i)) + 1];
+    for (int c = 0; c < kClasses; ++c) fill[c] = at[c + 1] += at[c];
+    std::vector<int> by((size_t)nv);
+    for (int64_t i = nv; i-- > 0;) by[--fill[cls[i]]] = (int)i;
+    parallel(kClasses, (int)std::min<int64_t>(6, 1 + nv / 3000), [&](int c) {
+      const int64_t a = at[c], n = at[c + 1] - a;
+      std::vector<std::pair<uint64_t, int>> order((size_t)n);
+      std::vector<Seg> own((size_t)n);
+      for (int64_t i = 0; i < n; ++i) {
+        own[i] = segment_of(vec + 3 * by[a + i], by[a + i], c);
+        order[i] = {own[i].order(), (int)i};
+      }
+      std::sort(order.begin(), order.end());
+      for (int64_t i = 0; i < n; ++i) seg[a + i] = own[order[i].second];
+    });
   }
   // groups of about equal work (steps not shared with the segment before, and a count), cut where
   // the signs change; one workgroup per compute unit, since each stages its slab and starts its
