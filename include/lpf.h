@@ -95,7 +95,7 @@ lpf_status lpf_pack(lpf_ctx ctx, const uint8_t *img, int W, int H, uint64_t *bit
  * more than 2^22 vectors, are read from a periodically extended copy in device memory instead
  * (same counts).  The first call for an image size and cutoff builds its launch plan on the host
  * and keeps it in the context, so a call to be captured in a graph follows one made outside the
- * capture.  The plans of lpf_full, lpf_full3d and lpf_delta_swap take at most 4 GiB of device memory
+ * capture.  The plans of lpf_full, lpf_full3d and lpf_delta_swap take at most 2 GiB of device memory
  * together: beyond that, those used longest ago are released (the device is waited for) and built
  * again when they are needed, except those that a captured call or a kept batch set reads.
  * Errors: LPF_E_INVAL (arguments), LPF_E_UNSUPPORTED (a cutoff above 32767, the int16 range of

@@ -531,9 +531,9 @@ lpf_status get_full_plan(lpf_ctx c, int W, int H, int cx, int cy, FullPlan *&pla
   return LPF_OK;
 }
 
-// Device memory that a context's plans may take together: a plan is 38 bytes per vector at cutoff 128
-// (1.3 MB), 68 at cutoff 512 (36 MB), 102 at the whole domain of 1448 x 1448 (430 MB).
-constexpr size_t kPlanBytes = (size_t)4 << 30;
+// Device memory that a context's plans may take together: a plan is 26 bytes per vector at cutoff 128
+// (0.9 MB), 40 at cutoff 512 (21 MB), 57 at the whole domain of 1448 x 1448 (240 MB).
+constexpr size_t kPlanBytes = (size_t)2 << 30;
 
 // Releases the plans used longest ago until `need` more bytes fit kPlanBytes.  Plans that a batch set
 // or a captured call reads stay, even if the rest is not enough.
@@ -576,7 +576,7 @@ void use_plan(lpf_ctx c, PlanMem &m, hipStream_t s) {
   m.captured = m.captured || capturing(s);
 }
 
-// Vectors above which the chain walk is used: plans of that size take some 400 MB and 5 s.
+// Vectors above which the chain walk is used: plans of that size take some 240 MB and 3 s.
 constexpr int64_t kCoverVectors = (int64_t)1 << 22;
 
 // The cover plan for an image size and cutoff with the fields of `f` fixed; plan->ok is false when

@@ -39,10 +39,13 @@ struct Path {
   int q(int k) const { return n ? (int)((2ll * k * m + n) / (2ll * n)) : 0; }
 };
 
+// The vectors of an octant with dx < 0 lie on the same paths on the mirrored image, but for the
+// axis, the first `axis` paths: it holds no vector with dx < 0 (the longest one takes all of it).
 struct Octant {
-  bool xm = true, mir = false;
+  bool xm = true;
   std::vector<Path> paths;   // by slope, then length
   std::vector<MemDesc> mems;
+  int axis = 0;
 };
 
 // Canonical index of (dx, dy): [0,cx] x [0,cy] row by row, then [-cx,-1] x [1,cy].
@@ -54,28 +57,26 @@ int64_t index_of(int cx, int cy, int dx, int dy) {
 // The vectors of one octant as walked paths: longest first, each with the vectors not yet taken
 // whose paths are its prefixes (u = pixel k of the walk, a prefix when u's slope lies in the
 // interval of slopes that digitise to pixels 0..k; see plan_full.hip).  The octant owns the
-// vectors with |dx| >= dy (xm) or |dx| < dy, dx < 0 (mir) or dx >= 0, so that octants are
-// independent.
-void build_octant(int cx, int cy, bool xm, bool mir, Octant &o) {
+// vectors dx >= 0 with dx >= dy (xm) or dx < dy, so that octants are independent.
+void build_octant(int cx, int cy, bool xm, Octant &o) {
   o.xm = xm;
-  o.mir = mir;
   const int N = xm ? cx : cy, M = xm ? cy : cx;
-  const int mlo = mir ? 1 : 0;
   auto put = [&](int k, int q) {
-    const int dx = (xm ? k : q) * (mir ? -1 : 1), dy = xm ? q : k;
+    const int dx = xm ? k : q, dy = xm ? q : k;
     o.mems.push_back(MemDesc{(int32_t)index_of(cx, cy, dx, dy), (int16_t)dx, (int16_t)dy, k});
   };
-  const bool zero = !mir && (xm ? (cx > 0 || cy == 0) : (cx == 0 && cy > 0));
+  const bool zero = xm ? (cx > 0 || cy == 0) : (cx == 0 && cy > 0);
   if (zero && N == 0) {  // the 1 x 1 domain: the zero vector alone
     o.paths.push_back(Path{0, 0, 0, 0, 1});
     put(0, 0);
+    o.axis = 1;
     return;
   }
   bool zero_done = !zero;
   std::vector<char> placed((size_t)(N + 1) * (M + 1), 0);
   for (int n = N; n >= 1; --n) {
     const int mhi = std::min(xm ? n : n - 1, M);
-    for (int m = mlo; m <= mhi; ++m) {
+    for (int m = 0; m <= mhi; ++m) {
       if (placed[(size_t)n * (M + 1) + m]) continue;
       Path p{n, m, n, (int)o.mems.size(), 0};
       if (!zero_done) {
@@ -91,7 +92,7 @@ void build_octant(int cx, int cy, bool xm, bool mir, Octant &o) {
           err -= 2 * n;
           ++q;
         }
-        if (q >= mlo && (xm || q < k) && !(q * lq < lp * k) && q * hq < hp * k) {
+        if ((xm || q < k) && !(q * lq < lp * k) && q * hq < hp * k) {
           char &t = placed[(size_t)k * (M + 1) + q];
           if (!t) {
             t = 1;
@@ -124,6 +125,7 @@ void build_octant(int cx, int cy, bool xm, bool mir, Octant &o) {
     const int64_t x = (int64_t)a.m * b.n, y = (int64_t)b.m * a.n;
     return x != y ? x < y : a.len < b.len;
   });
+  while (o.axis < (int)o.paths.size() && o.paths[o.axis].m == 0) ++o.axis;
 }
 
 // Steps of a path along the minor axis, bit k - 1 = q_k - q_{k-1}; bit_words(len) words.
@@ -373,7 +375,6 @@ class GroupBuilder {
     CoverGroup &g = out.g;
     const int nmem = g.nmem;
     g.ntiles = (H_ + g.tile - 1) / g.tile;
-    g.mirror = o_->mir ? 1 : 0;
     int len = 0;
     for (int i = a_; i < b_; ++i) len = std::max(len, o_->paths[i].len);
     width_ = occ_words(len);
@@ -759,7 +760,7 @@ void cover_lanes(int W, int H, int *R, int *S) {
 namespace {
 
 // The plan for given octants and shape; false when some group's rows do not fit sh.lds.
-bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape &sh,
+bool build_cover(const std::vector<Octant> &oct, int W, int H, int cx, int cy, const CoverShape &sh,
                  int groups_want, CoverHost &out, std::vector<int64_t> &tile_cost) {
   out = CoverHost();
   out.sh = sh;
@@ -769,28 +770,49 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
   auto cost = [](const Path &p) { return 4 + 3 * (int64_t)p.nm; };
   int64_t total = 0;
   for (auto &o : oct)
-    for (auto &p : o.paths) total += cost(p);
+    for (int p = 0; p < (int)o.paths.size(); ++p) total += (p < o.axis ? 1 : 2) * cost(o.paths[p]);
+  // Groups of dx >= 0 and, right after them, the same of dx < 0: a group without an axis path has its
+  // mirrored image's words and records (src); only the first ones are planned apart.
   struct Range {
     int o, a, b;
+    bool mirror;
+    int src;
   };
   std::vector<Range> ranges;
-  for (int i = 0; i < 4; ++i) {
-    int64_t oc = 0;
-    for (auto &p : oct[i].paths) oc += cost(p);
-    if (oct[i].paths.empty()) continue;
-    // (groups full of members would leave remnants between them)
-    int64_t om = 0;
-    for (auto &p : oct[i].paths) om += p.nm;
-    const int want = (int)std::max<int64_t>(
-        std::max<int64_t>(1, std::llround((double)groups_want * oc / total)),
-        (om * 5 / 4 + kCoverSlots - 1) / kCoverSlots);
+  for (int i = 0; i < 2; ++i) {
+    const Octant &o = oct[i];
+    if (o.paths.empty()) continue;
+    int64_t oc = 0, om = 0, ac = 0, am = 0;  // cost and members; the axis's
+    for (int p = 0; p < (int)o.paths.size(); ++p) {
+      oc += cost(o.paths[p]);
+      om += o.paths[p].nm;
+      if (p < o.axis) {
+        ac += cost(o.paths[p]);
+        am += o.paths[p].nm;
+      }
+    }
+    // Both signs of dx together get their share of the groups: `want` with the axis and as many without
+    // the groups that are axis only.  (One group more than groups_want can mean one more round of
+    // workgroups: 512 x 512, cutoff 128: 128 groups 147 us, 130 158.)
+    const double share = (double)groups_want * (2 * oc - ac) / total;
+    const int64_t alone = (int64_t)(ac * share / (2 * oc - ac));
+    int want = std::max(1, (int)std::llround((share + alone) / 2));
+    // Groups full of members would leave remnants between them.  Where that sets their number, an axis
+    // that fills a third of one has a group of its own (1024 x 1024, cutoff 512: 8.05 ms, with others in
+    // its group 8.2); a shorter one does not (512 x 512, cutoff 255: 2 412 mask steps, apart 2 626).
+    const int np = (int)o.paths.size(), first = (int)ranges.size();
+    auto full = [](int64_t m) { return (int)((m * 5 / 4 + kCoverSlots - 1) / kCoverSlots); };
+    const bool apart = full(om - am / 2) > want && am * 3 > kCoverSlots && o.axis < np;
+    const int start = apart ? o.axis : 0;
+    want = std::max(want, full(apart ? om - am : om - am / 2));
+    if (apart) oc -= ac;
+    int a = start;
     int64_t acc = 0;
-    int a = 0, mem = 0, k = 1;
-    const int np = (int)oct[i].paths.size();
-    for (int p = 0; p < np; ++p) {
-      const Path &pt = oct[i].paths[p];
+    int mem = 0, k = 1;
+    for (int p = a; p < np; ++p) {
+      const Path &pt = o.paths[p];
       if (p > a && (mem + pt.nm > kCoverSlots || (acc + cost(pt) / 2) * want >= oc * k)) {
-        ranges.push_back({i, a, p});
+        ranges.push_back({i, a, p, false, -1});
         a = p;
         mem = 0;
         while ((acc + cost(pt) / 2) * want >= oc * k) ++k;
@@ -798,7 +820,13 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
       acc += cost(pt);
       mem += pt.nm;
     }
-    ranges.push_back({i, a, np});
+    ranges.push_back({i, a, np, false, -1});
+    for (int r = first, e = (int)ranges.size(); r < e; ++r) {
+      const Range g = ranges[r];
+      if (g.b > o.axis)
+        ranges.push_back({i, std::max(g.a, o.axis), g.b, true, g.a >= o.axis ? r : -1});
+    }
+    if (start) ranges.push_back({i, 0, start, false, -1});
   }
   const int ng = (int)ranges.size();
   std::vector<GroupOut> go(ng);
@@ -814,7 +842,7 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
     parallel(runs, thr, [&](int run) {
       GroupBuilder gb(H, sh);
       for (int i = (int)((int64_t)ng * run / runs); i < (int)((int64_t)ng * (run + 1) / runs); ++i)
-        f(gb, oct[ranges[i].o], ranges[i].a, ranges[i].b, go[i]);
+        if (ranges[i].src < 0) f(gb, oct[ranges[i].o], ranges[i].a, ranges[i].b, go[i]);
     });
   };
   groups((int64_t)ng * bands > 256 ? threads : 1,
@@ -828,18 +856,30 @@ bool build_cover(const std::vector<Octant> &oct, int W, int H, const CoverShape 
   size_t nrec = 64, dw = 0;
   for (auto &x : go) nrec += x.recs.size();
   out.recs.reserve(nrec);
+  out.mems.reserve((size_t)(cx + 1) * (cy + 1) + (size_t)cx * cy);
   tile_cost.clear();
-  for (auto &x : go) {
-    CoverGroup g = x.g;
-    g.piece0 = (int32_t)out.piece_off.size();
+  for (int i = 0; i < ng; ++i) {
+    const Range &rg = ranges[i];
+    const GroupOut &x = go[rg.src < 0 ? i : rg.src];
+    CoverGroup g = rg.src < 0 ? x.g : out.groups[rg.src];  // (records and words: the source's)
+    if (rg.src < 0) {
+      g.piece0 = (int32_t)out.piece_off.size();
+      const int r0 = (int)out.recs.size(), b0 = (int)out.bops.size();
+      for (int &b : g.bop) b += b0;
+      for (int32_t p : x.piece_off) out.piece_off.push_back(p + r0);
+      out.recs.insert(out.recs.end(), x.recs.begin(), x.recs.end());
+      for (size_t r = r0; r < out.recs.size(); ++r) out.recs[r].w += r0;
+      out.bops.insert(out.bops.end(), x.bops.begin(), x.bops.end());
+    }
+    g.mirror = rg.mirror ? 1 : 0;
     g.mem0 = (int32_t)out.mems.size();
-    const int r0 = (int)out.recs.size(), b0 = (int)out.bops.size();
-    for (int &b : g.bop) b += b0;
-    for (int32_t p : x.piece_off) out.piece_off.push_back(p + r0);
-    out.recs.insert(out.recs.end(), x.recs.begin(), x.recs.end());
-    for (size_t r = r0; r < out.recs.size(); ++r) out.recs[r].w += r0;
-    out.bops.insert(out.bops.end(), x.bops.begin(), x.bops.end());
     out.mems.insert(out.mems.end(), x.mems.begin(), x.mems.end());
+    if (rg.mirror)
+      for (size_t m = g.mem0; m < out.mems.size(); ++m) {
+        MemDesc &v = out.mems[m];
+        v.dx = (int16_t)-v.dx;
+        v.idx = (int32_t)index_of(cx, cy, v.dx, v.dy);
+      }
     // vector instructions of a tile: its masks (8 dwords a lane, about 40 instructions a step with
     // the waits between them), its rows, the walks of its bands
     const int bands = g.tile / (64 / sh.S);
@@ -869,8 +909,8 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
     if (fS) S = fS;
   }
   const int64_t nv = (int64_t)(cx + 1) * (cy + 1) + (int64_t)cx * cy;
-  std::vector<Octant> oct(4);
-  parallel(4, nv > 3000 ? 4 : 1, [&](int i) { build_octant(cx, cy, i < 2, i & 1, oct[i]); });
+  std::vector<Octant> oct(2);
+  parallel(2, nv > 3000 ? 2 : 1, [&](int i) { build_octant(cx, cy, i == 0, oct[i]); });
   for (;; R = R / 2) {
     for (int big = 0; big < 2; ++big) {
       if (fL && big) break;
@@ -897,7 +937,7 @@ bool plan_cover(int W, int H, int cx, int cy, int fR, int fS, int fW, int fL, in
       int64_t g = std::max<int64_t>(slots / tiles, 64);
       g = std::max<int64_t>(4, std::min<int64_t>(g, paths / (3 * nsub)));
       std::vector<int64_t> tile_cost;
-      if (!build_cover(oct, W, H, sh, (int)g, out, tile_cost)) continue;
+      if (!build_cover(oct, W, H, cx, cy, sh, (int)g, out, tile_cost)) continue;
       int64_t most = 1;
       for (const CoverGroup &x : out.groups) most = std::max<int64_t>(most, x.ntiles * out.nct);
       // up to eight items per CU and phase, so that the last ones are short (1 024 x 1 024, cutoff
