@@ -11,12 +11,12 @@
 //    staged rows (one mask array in LDS), a step takes the whole word at once, and overlapping
 //    words cover a path exactly: greedily, the step that reaches furthest without passing the
 //    next count.
-// At cutoff 128 both together leave about 2 steps per vector (86 without them, 38 with prefixes
+// At cutoff 128 both together leave 2.6 steps per vector (86 without them, 38 with prefixes
 // shared by whole chains only).
 //
 // A group is a range of slopes of one octant with up to kCoverWords words, walked by one
 // workgroup; a piece is the part of it that one wave walks.  Vectors with dx < 0 are walked on the
-// mirrored image, so every offset is >= 0.
+// mirrored image, so every offset is >= 0, with the words and records of the group of dx >= 0.
 #include <algorithm>
 #include <climits>
 #include <cmath>
