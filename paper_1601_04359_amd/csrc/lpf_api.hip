@@ -2781,15 +2781,17 @@ lpf_status lpf_autotune_full(lpf_ctx c, const uint64_t *bits, int W, int H, int 
     (void)hipFree(tmp);
   }
   {
-    // the plans that were made here and lost (each event above was waited for)
+    // the plans that were made here and lost; another thread's calls may have taken one meanwhile
     std::lock_guard<std::mutex> lk(c->mu);
     DeviceGuard g(c->dev);
+    (void)hipDeviceSynchronize();
     const std::array<int, 8> kept = {W, H, cx, cy, best.R, 0, best.wpg, best.lds};
     for (auto it = c->cover_plans.begin(); it != c->cover_plans.end();) {
-      if (same_image(it->first) && it->first != kept &&
+      const PlanMem &m = it->second.mem;
+      if (same_image(it->first) && it->first != kept && !m.sets && !m.captured &&
           std::find(had.begin(), had.end(), it->first) == had.end()) {
-        (void)hipFree(it->second.mem.p);
-        c->plan_bytes -= it->second.mem.bytes;
+        (void)hipFree(m.p);
+        c->plan_bytes -= m.bytes;
         it = c->cover_plans.erase(it);
       } else {
         ++it;
